@@ -64,3 +64,17 @@ def test_index_scale_8k_contexts_sampled():
     sub = np.vstack([C[rows], C])                    # oracle on (sample + all), take the block
     want = oracle.context_distance(sub, np.concatenate([L[rows], L]), np.float32(0.001))[:64, 64:]
     assert np.abs(got[rows] - want).max() <= TOL
+
+
+@pytest.mark.parametrize("n,stride", [(31, 16), (33, 12), (257, 16), (288, 16), (511, 8), (514, 16), (272, 32), (545, 24)])
+def test_tile_edges_and_crowded_dictionary_buckets(n, stride):
+    """Sizes around the tiles (32 or 16 rows, 256 columns, rows written 16 bytes at a time or not), with
+    ids of which many fall into one bucket of the kernel's dictionary: more than a bucket holds."""
+    rng = np.random.default_rng(n)
+    back = pow(0x9E3779B1, -1, 1 << 32)               # undoes the hash: hashes with the same top 10 bits
+    crowd = [(h * back) % (1 << 32) for h in (0x12400000 + np.arange(64)).tolist()]
+    crowd = [i for i in crowd if i < 1 << 31][:12]
+    ids = np.array(crowd + list(range(40)) + [(1 << 31) - 1], dtype=np.int64)
+    C = np.stack([rng.permutation(ids)[:stride] for _ in range(n)]).astype(np.int32)
+    L = rng.integers(0, stride + 1, size=n).astype(np.int32)
+    _check(C, L, 0.001)
