@@ -70,7 +70,8 @@ struct AttnParams {
     int32_t dec_row_blocks; // decode kernel: blocks of 32 (head, token) rows per (request, KV head)
     int32_t items_per_head; // work units per KV head * nsplit
     int32_t total_items;    // items_per_head * Hkv
-    int32_t items_per_xcd;  // ceil(total_items / 8)
+    int32_t items_per_xcd;  // list positions of each XCD, see work_item
+    int32_t xcds_per_head;  // XCDs that share the items of one KV head
     float scale_log2;       // softmax_scale * log2(e)
 };
 
@@ -86,6 +87,30 @@ __device__ __forceinline__ float halfwave_sum(float x)
 {
     auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// The item list of a call is KV head by KV head, items_per_head each.  Consecutive workgroup ids go
+// round the XCDs, and an XCD works on one KV head at a time, so that the workgroups resident on it
+// stream the same K/V through its L2.  With 8 KV heads or more an XCD gets a contiguous range of the
+// list.  With 1, 2 or 4 several XCDs share a head: a contiguous range each is right when that is the
+// same number of equal requests for all of them (4 requests, P = 4000, E = 3000, 8/2 heads: 288 us,
+// 299 dealt out), otherwise it leaves unequal shares, because the longest row tiles of a request
+// come first, and the head's items are dealt out one at a time (one prompt of 32768 tokens, 8/2
+// heads: 2.81 -> 1.85 ms; of 8192: 211 -> 151 us).
+// Position of this workgroup's item in the list, or -1.
+__device__ __forceinline__ int work_item(int bid, const AttnParams &p, int &kvh)
+{
+    const int xcd = bid % kXcds, at = bid / kXcds;
+    int item;
+    if (p.xcds_per_head > 1) {
+        kvh = xcd / p.xcds_per_head;
+        item = at * p.xcds_per_head + xcd % p.xcds_per_head;
+        return item < p.items_per_head ? item : -1;
+    }
+    item = xcd * p.items_per_xcd + at;
+    if (item >= p.total_items) return -1;
+    kvh = item / p.items_per_head;
+    return item - kvh * p.items_per_head;
 }
 
 // Number of q heads of one KV head that share a workgroup (GQA head sharing): short extends
@@ -151,14 +176,9 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const AttnParams 
     const int j = lane & 31; // query row within the wave; also key row / d row of A operands
     const int h = lane >> 5; // half-wave
 
-    // ---- which work item: consecutive workgroup ids land on different XCDs, so give each
-    // XCD a contiguous range of the item list (one KV head per XCD when Hkv == 8) and keep the
-    // items that stream the same K/V next to each other in time.
-    const int bid = blockIdx.x;
-    const int vid = (bid % kXcds) * p.items_per_xcd + bid / kXcds;
-    if (vid >= p.total_items) return;
-    const int kvh = vid / p.items_per_head;
-    int rem = vid - kvh * p.items_per_head;
+    int kvh = 0;
+    const int rem = work_item(blockIdx.x, p, kvh);
+    if (rem < 0) return;
     const int split = rem % p.nsplit;
     int unit = rem / p.nsplit;
 
@@ -1255,6 +1275,12 @@ Plan make_plan(const cp_shape *s)
     return pl;
 }
 
+bool equal_lengths(const cp_shape *s)
+{
+    for (int r = 1; r < s->batch; ++r)
+        if (s->h_prefix_lens[r] != s->h_prefix_lens[0] || s->h_extend_lens[r] != s->h_extend_lens[0]) return false;
+    return true;
+}
 
 // Launches the merge of nsplit partial results for n_rh (row, head) pairs.
 void launch_merge(const AttnParams &p, int nsplit, hipStream_t hs)
@@ -1496,7 +1522,10 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     p.dec_row_blocks = pl.row_blocks;
     p.items_per_head = (int32_t)per_head;
     p.total_items = (int32_t)total;
-    p.items_per_xcd = (int32_t)((total + kXcds - 1) / kXcds);
+    p.xcds_per_head = p.Hkv < kXcds && kXcds % p.Hkv == 0 ? kXcds / p.Hkv : 1;
+    if (p.batch % p.xcds_per_head == 0 && equal_lengths(shape)) p.xcds_per_head = 1;
+    p.items_per_xcd = (int32_t)(p.xcds_per_head > 1 ? (per_head + p.xcds_per_head - 1) / p.xcds_per_head
+                                                    : (total + kXcds - 1) / kXcds);
     p.scale_log2 = shape->softmax_scale * 1.4426950408889634f;
 
     hipStream_t hs = static_cast<hipStream_t>(stream);
