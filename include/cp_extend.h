@@ -78,14 +78,15 @@ typedef struct cp_shape {
 } cp_shape;
 
 /*
- * Bytes of device scratch that cp_extend_attention needs for this shape (0 when the keys
- * are not split).  A pure function of *shape, including the host length arrays.  Returns 0
+ * Bytes of device scratch with which cp_extend_attention takes its best plan for this shape (0 when
+ * the keys are not split).  A batch of unequal lengths also runs with less, on a plan that fits.  A pure function of *shape, including the host length arrays.  Returns 0
  * for an invalid shape (cp_extend_attention then reports the error).
  */
 size_t cp_workspace_bytes(const cp_shape *shape);
 
 /* The number of key ranges whose partial results cp_extend_attention will merge for this shape
- * (1 = no split; up to 64 when forced, up to 256 when chosen by the library; 0 if invalid). */
+ * (1 = no split; up to 64 when forced, up to 256 when chosen by the library; 0 if invalid).  For a
+ * batch of unequal lengths, whose requests are split one by one: the largest. */
 int32_t cp_num_splits(const cp_shape *shape);
 
 /*
@@ -96,7 +97,8 @@ int32_t cp_num_splits(const cp_shape *shape);
 enum {
     CP_PLAN_INVALID = 0,
     CP_PLAN_ROW_TILED = 1,       /* extend_attn_kernel, keys not split */
-    CP_PLAN_ROW_TILED_SPLIT = 2, /* extend_attn_kernel over key ranges + merge_splits_kernel */
+    CP_PLAN_ROW_TILED_SPLIT = 2, /* extend_attn_kernel over key ranges + a merge; in a batch of unequal
+                                    lengths decode-shaped requests take decode_attn_kernel's form inside it */
     CP_PLAN_DECODE = 3           /* decode_attn_kernel (a wavefront per key chunk) + merge_splits_kernel */
 };
 int32_t cp_plan_kind(const cp_shape *shape);
@@ -118,8 +120,9 @@ int32_t cp_plan_kind(const cp_shape *shape);
  * result does not depend on whether cp_write_kv ran before, after or not at all.  kv_pages is
  * only read.  Results are bitwise reproducible for a fixed shape (no atomics).
  *
- * workspace: DEVICE scratch of at least cp_workspace_bytes(shape) bytes, 256-byte aligned;
- * may be NULL when that size is 0.  Its contents are undefined afterwards.
+ * workspace: DEVICE scratch of cp_workspace_bytes(shape) bytes, 256-byte aligned; may be NULL when
+ * that size is 0.  With less, a batch of unequal lengths takes a plan that fits (not bit for bit the
+ * same result), any other call is refused.  Its contents are undefined afterwards.
  * Requests with E_r = 0 produce no rows.  Asynchronous on `stream`.
  */
 int cp_extend_attention(const void *q, const void *k_new, const void *v_new,
@@ -134,7 +137,7 @@ int cp_extend_attention(const void *q, const void *k_new, const void *v_new,
  * arguments, result and checks as cp_extend_attention without the last two; the split-K /
  * decode partial results go to an array of cp_noalloc_scratch_bytes() bytes (64 MiB) that lives
  * inside the library, once per device, from the moment the library is loaded until the process
- * ends.  A shape whose cp_workspace_bytes exceeds that size is refused with CP_ERR_WORKSPACE
+ * ends.  A shape for which every plan needs more is refused with CP_ERR_WORKSPACE
  * and nothing is launched.  The call allocates nothing and frees nothing (the array's device
  * address is looked up on the first call on each device).  All calls on one device share the
  * array: two such calls that overlap in time (different streams, different host threads) race

@@ -3,9 +3,10 @@
 // Kernels behind the C ABI of cp_extend.h:
 //   write_kv_kernel       cache append (paper, Section 1: the prefix cache stores prior K/V)
 //   extend_attn_kernel    suffix rows attend to cached prefix pages + their own K/V
-//                         (paper, Section 1 / Section 2.1: prefill over a prefix cache)
+//                         (paper, Section 1 / Section 2.1: prefill over a prefix cache); in batches of
+//                         unequal lengths also the decode-shaped requests, next to the others
 //   decode_attn_kernel    the same for calls with few rows per KV head (a wavefront per key chunk)
-//   merge_splits_kernel, merge_few_splits_kernel   combine partial results over key ranges
+//   merge_splits_kernel, merge_few_splits_kernel, merge_mixed_kernel   combine partial results over key ranges
 //   check_tables_kernel   optional check of block_table against the pool size
 //
 // Attention kernel layout.  One workgroup = 8 wavefronts = 256 query rows of one q head; each
@@ -63,7 +64,7 @@ struct AttnParams {
     const int32_t *prefix_lens;
     const int32_t *extend_lens;
     uint16_t *out;
-    float *part_o;  // [nsplit][T][Hq][D]   unnormalised partial outputs
+    float *part_o;  // [nsplit][T][Hq][D]   unnormalised partial outputs (mixed: [part_rows][Hq][D])
     float *part_ml; // [nsplit][T][Hq][2]   running max (log2 domain) and sum
     int32_t batch, Hq, Hkv, G, max_pages, T;
     int32_t nsplit;
@@ -73,6 +74,13 @@ struct AttnParams {
     int32_t items_per_xcd;  // list positions of each XCD, see work_item
     int32_t xcds_per_head;  // XCDs that share the items of one KV head
     float scale_log2;       // softmax_scale * log2(e)
+};
+constexpr int kMixedMaxBatch = 512; // requests of a mixed batch; beyond, planning costs the host more than the call takes
+struct MixedParams : AttnParams {
+    int32_t seg_tiles;  // key tiles per work item of a row-tiled request, at most
+    int32_t dec_blocks; // key blocks of 32 per wavefront of a decode-shaped request, at most
+    int32_t row_items;  // row-tiled items per KV head; decode-shaped work follows them
+    uint8_t order[kMixedMaxBatch]; // per group of 64 requests: which lane's request is first, second, ...
 };
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
@@ -130,6 +138,19 @@ __host__ __device__ inline int units_of_request(int E, int G, int pack)
     while ((1 << shift) < pack) ++shift;
     return ((E * pack + kBM - 1) / kBM) * (G >> shift);
 }
+// Few new tokens: the rows of a KV head (G heads x E tokens) fit into kDecMaxRowBlocks blocks.
+constexpr int kDecRows = 32;        // (head, token) rows per wavefront
+constexpr int kDecMaxRowBlocks = 2; // row blocks per (request, KV head): G x E_r <= 64 (beyond, the row-tiled kernel is faster)
+__host__ __device__ inline bool decode_shaped(int E, int G) { return E <= kDecRows * kDecMaxRowBlocks && E * G <= kDecRows * kDecMaxRowBlocks; }
+// Mixed batches: key ranges of a request (partial results per row; 1 = the result is written directly).
+__host__ __device__ inline int splits_of_request(int P, int E, int G, int seg_tiles, int dec_blocks)
+{
+    if (E <= 0) return 0;
+    if (decode_shaped(E, G)) return ((P + E + 31) / 32 + dec_blocks - 1) / dec_blocks;
+    const int tiles = (P + kBN - 1) / kBN + (E + kBN - 1) / kBN;
+    const int ns = (tiles + seg_tiles - 1) / seg_tiles;
+    return ns < kMaxSplits ? ns : kMaxSplits;
+}
 // Inclusive prefix sum over the 64 lanes of a wavefront.
 __device__ __forceinline__ int wave_inclusive_scan(int x, int lane)
 {
@@ -139,6 +160,311 @@ __device__ __forceinline__ int wave_inclusive_scan(int x, int lane)
         if (lane >= off) x += y;
     }
     return x;
+}
+
+// A request of a mixed batch and the place of one unit of its work.
+struct Owner {
+    int r;      // request, batch: none
+    int unit;   // index among the request's units
+    int P, E;
+    int cu;     // packed row of its first new token
+    int parts;  // rows of partial results of the requests before it
+    int splits; // its key ranges
+};
+// The request that owns position `at` of a list of units.  kDecode: the decode-shaped requests, row
+// blocks x key chunks each.  Otherwise the row-tiled requests, row tiles x head groups x key ranges
+// each.  The list takes the requests of a group of 64 in the order that the host gives (most keys
+// first, so that the items that start last are short).  Every lane takes one request; the first unit
+// of each is a sum over the lanes.
+template <bool kDecode>
+__device__ __forceinline__ Owner find_owner(int at, const MixedParams &p, int lane)
+{
+    Owner w{p.batch, at, 0, 0, 0, 0, 1};
+    for (int base = 0; base < p.batch; base += 64) {
+        const int rr = base + lane;
+        const int e = rr < p.batch ? p.extend_lens[rr] : 0;
+        const int pl = rr < p.batch ? p.prefix_lens[rr] : 0;
+        const int from = p.order[rr];
+        const int ns = splits_of_request(pl, e, p.G, p.seg_tiles, p.dec_blocks);
+        int units = 0;
+        if (e > 0 && decode_shaped(e, p.G) == kDecode)
+            units = (kDecode ? (e * p.G + kDecRows - 1) / kDecRows : units_of_request(e, p.G, heads_per_tile(e, p.G))) * ns;
+        const int sorted = __shfl(units, from, 64);
+        const int incl = wave_inclusive_scan(sorted, lane);
+        const int parts = ns > 1 ? ns * e : 0;
+        const int incl_e = wave_inclusive_scan(e, lane);
+        const int incl_p = wave_inclusive_scan(parts, lane);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
+        if (w.unit < total) {
+            const int place = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl > w.unit));
+            const int first = __builtin_amdgcn_readlane(from, place);
+            w.r = base + first;
+            w.unit -= __builtin_amdgcn_readlane(incl - sorted, place);
+            w.cu += __builtin_amdgcn_readlane(incl_e - e, first);
+            w.parts += __builtin_amdgcn_readlane(incl_p - parts, first);
+            w.E = __builtin_amdgcn_readlane(e, first);
+            w.P = __builtin_amdgcn_readlane(pl, first);
+            w.splits = __builtin_amdgcn_readlane(ns, first);
+            return w;
+        }
+        w.unit -= total;
+        w.cu += __builtin_amdgcn_readlane(incl_e, 63);
+        w.parts += __builtin_amdgcn_readlane(incl_p, 63);
+    }
+    return w;
+}
+
+// ---- decode-shaped calls ------------------------------------------------------------------
+// When every request brings so few new tokens that all its rows for one KV head (G heads x E_r
+// tokens) fit a few 32-column MFMA tiles, the call is bound by reading the cached K/V once,
+// and the row-tiled kernel above wastes its wavefronts (most hold no valid row) and keeps too
+// little in flight.  This kernel turns the work around: a wavefront is the unit, owns 32 rows
+// of one (request, KV head) and a contiguous chunk of the keys, and runs alone - no barrier, no
+// shared tile.  Per block of 32 keys it loads the K and V rows with fully coalesced 16-byte
+// loads (one instruction = four whole rows), stages them in registers while the previous block
+// is computed, and passes them through a private LDS area from which the MFMA operands are read
+// (K rows as they are, V rows transposed).  Every wavefront writes an unnormalised partial
+// (m, l, O) and merge_splits_kernel combines them, exactly as for split-K.  Prefix and suffix
+// keys form one sequence of N = P + E keys; blocks inside the prefix take their two pages from
+// the block table with scalar loads, the last blocks resolve every row on its own.
+constexpr int kDecWaves = 4;            // wavefronts per workgroup (independent of each other)
+// LDS bytes per K row / V row: 256 + padding.  16 consecutive K rows at the same column fall into
+// 16 different 16-byte bank groups, the four consecutive V rows of a transposing read into four
+// different 64-byte bank groups, and every read address is a per-lane base plus an immediate.
+constexpr int kDecPitchK = 272;
+constexpr int kDecPitchV = 320;
+constexpr int kDecLdsK = 32 * kDecPitchK;
+constexpr int kDecLdsPerWave = kDecLdsK + 32 * kDecPitchV;
+constexpr int kDecMaxChunks = 256;      // key chunks (= partial results) per (request, KV head)
+
+struct DecBlock { // one block of 32 keys as loaded: piece i is row (lane / 16) + 4 i, chunk lane % 16
+    u32x4 k[8];
+    u32x4 v[8];
+};
+
+// One wavefront: row block rb of (request r, KV head kvh) against the key blocks b0 .. b1 - 1.  The
+// partial result of token e goes to row part_row + e of the partial results; part_row < 0 says that
+// these are all the keys and writes the finished rows instead.
+__device__ __forceinline__ void decode_chunk(const AttnParams &p, char *lds_k, int lane, int r, int kvh, int P, int E,
+                                             int cu, int rb, int b0, int b1, int64_t part_row)
+{
+    char *const lds_v = lds_k + kDecLdsK;
+    const int j = lane & 31; // (head, token) row of the accumulators; key row of the K operand
+    const int h = lane >> 5;
+    // row 32 rb + j of the (request, KV head) is token e of head hg of the group; rows beyond
+    // G E are padding
+    if (rb * kDecRows >= p.G * E) return;
+    const int row = rb * kDecRows + j;
+    const bool row_valid = row < p.G * E;
+    const int hg = row_valid ? row / E : 0;
+    const int e = row_valid ? row - hg * E : 0;
+    const int head = kvh * p.G + hg;
+    const int64_t out_row = cu + e;
+    const int N = P + E;
+    const int64_t prow = (part_row + e) * p.Hq + head;
+    if (b0 >= b1) { // nothing to do for this chunk: the merge skips entries whose sum is zero
+        if (row_valid && h == 0) {
+            p.part_ml[prow * 2] = -INFINITY;
+            p.part_ml[prow * 2 + 1] = 0.f;
+        }
+        return;
+    }
+
+    // Q fragments, B operand of S^T = K Q^T: lane (row j, h) holds q[row][16 kk + 8 h .. + 8)
+    u32x4 qf[8];
+    {
+        const uint16_t *qp = p.q + (out_row * p.Hq + head) * kD + 8 * h;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) qf[kk] = *(const __attribute__((address_space(1))) u32x4 *)(qp + 16 * kk);
+    }
+
+    // loads: lane covers rows ld_sub + 4 i (i = 0..7) of the block, 16-byte chunk ld_chunk
+    const int ld_sub = lane >> 4, ld_chunk = lane & 15;
+    const __attribute__((address_space(4))) int32_t *table =
+        (const __attribute__((address_space(4))) int32_t *)(p.block_table + (int64_t)r * p.max_pages);
+    const int64_t v_plane = (int64_t)p.Hkv * kPS * kD;
+    const int64_t page_stride = 2 * v_plane;
+    const uint16_t *pages_head = p.kv_pages + (int64_t)kvh * (kPS * kD) + ld_chunk * 8;
+    auto load_block = [&](int b, DecBlock &blk) {
+        if (b * 32 + 32 <= P) {
+            // inside the prefix: rows 0..15 in page 2 b, rows 16..31 in page 2 b + 1
+            const int64_t pg[2] = {table[2 * b], table[2 * b + 1]};
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint16_t *krow = pages_head + pg[i >> 2] * page_stride + ((ld_sub + 4 * i) & 15) * kD;
+                blk.k[i] = *(const __attribute__((address_space(1))) u32x4 *)(krow);
+                blk.v[i] = *(const __attribute__((address_space(1))) u32x4 *)(krow + v_plane);
+            }
+        } else {
+            // last blocks: every row resolves its own key (clamped to the last one; masked below)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const int key = min(b * 32 + ld_sub + 4 * i, N - 1);
+                const uint16_t *krow, *vrow;
+                if (key < P) {
+                    krow = pages_head + (int64_t)p.block_table[(int64_t)r * p.max_pages + (key >> 4)] * page_stride +
+                           (key & 15) * kD;
+                    vrow = krow + v_plane;
+                } else {
+                    const int64_t off = ((int64_t)(cu + key - P) * p.Hkv + kvh) * kD + ld_chunk * 8;
+                    krow = p.k_new + off;
+                    vrow = p.v_new + off;
+                }
+                blk.k[i] = *(const __attribute__((address_space(1))) u32x4 *)(krow);
+                blk.v[i] = *(const __attribute__((address_space(1))) u32x4 *)(vrow);
+            }
+        }
+    };
+    const int st_k = ld_sub * kDecPitchK + ld_chunk * 16;
+    const int st_v = ld_sub * kDecPitchV + ld_chunk * 16;
+    auto store_block = [&](const DecBlock &blk) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            *reinterpret_cast<u32x4 *>(lds_k + st_k + 4 * i * kDecPitchK) = blk.k[i];
+            *reinterpret_cast<u32x4 *>(lds_v + st_v + 4 * i * kDecPitchV) = blk.v[i];
+        }
+    };
+    // operand reads, as in the kernel above
+    const int k_lane = j * kDecPitchK + h * 16;
+    const int v_lane = (4 * h + ((lane & 15) >> 2)) * kDecPitchV + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+
+    f32x16 o[4];
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
+    float m_run = -INFINITY, l_run = 0.f; // log2 domain; sum over this half-wave's keys
+    const float c = p.scale_log2;
+    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
+
+    DecBlock blk;
+    load_block(b0, blk);
+    for (int b = b0; b < b1; ++b) {
+        // block b: registers -> private LDS (one wavefront's LDS operations are served in order,
+        // so these writes come after the reads of block b - 1), then block b + 1 into flight
+        store_block(blk);
+        if (b + 1 < b1) load_block(b + 1, blk);
+        f32x16 s;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) {
+            const u32x4 a = *reinterpret_cast<const u32x4 *>(lds_k + k_lane + kk * 32);
+            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                         __builtin_bit_cast(bf16x8, qf[kk]), s, 0, 0, 0);
+        }
+        // accumulator element v is key 32 b + 8 (v / 4) + 4 h + v % 4; row j sees keys <= P + e
+        if (b * 32 + 31 > P) {
+            const int vis = P + e - b * 32 - 4 * h; // visible: 8 (v / 4) + v % 4 <= vis
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                if (8 * (v >> 2) + (v & 3) > vis) s[v] = -INFINITY;
+        }
+        float mx = s[0];
+#pragma unroll
+        for (int v = 1; v + 1 < 16; v += 2) mx = fmaxf(fmaxf(mx, s[v]), s[v + 1]);
+        mx = halfwave_max(fmaxf(mx, s[15]));
+        const float m_new = fmaxf(m_run, mx * c);
+        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+        const float alpha = fast_exp2(m_run - m_use);
+        u32x4 pb[2];
+        float psum = 0.f;
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                f32x2 x;
+                x[0] = fast_exp2(fmaf(s[8 * u + 2 * w], c, -m_use));
+                x[1] = fast_exp2(fmaf(s[8 * u + 2 * w + 1], c, -m_use));
+                const bf16x2 y = __builtin_convertvector(x, bf16x2);
+                psum = __builtin_amdgcn_fdot2_f32_bf16(y, ones, psum, false);
+                pb[u][w] = __builtin_bit_cast(unsigned, y);
+            }
+        l_run = l_run * alpha + psum;
+        m_run = m_new;
+        if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+        }
+        // O^T += V^T P^T: 2 steps of 16 keys x 4 blocks of 32 d
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+            for (int db = 0; db < 4; ++db) {
+                const char *a = lds_v + v_lane + db * 64 + ks * 16 * kDecPitchV;
+                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4 *)(a));
+                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4 *)(a + 8 * kDecPitchV));
+                const s16x8 vv = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv),
+                                                                 __builtin_bit_cast(bf16x8, pb[ks]), o[db], 0, 0, 0);
+            }
+    }
+
+    // partial result of this chunk; o[db][v] is O^T[d = db*32 + 8*(v/4) + 4*h + v%4][row j]
+    const float l_tot = halfwave_sum(l_run);
+    if (!row_valid) return;
+    if (part_row < 0) {
+        const float inv = 1.f / l_tot;
+        uint16_t *po = p.out + (out_row * p.Hq + head) * kD;
+#pragma unroll
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int gq = 0; gq < 4; ++gq) {
+                bf16x4 x;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) x[i] = (__bf16)(o[db][4 * gq + i] * inv);
+                *reinterpret_cast<bf16x4 *>(po + db * 32 + 8 * gq + 4 * h) = x;
+            }
+        return;
+    }
+    float *po = p.part_o + prow * kD;
+#pragma unroll
+    for (int db = 0; db < 4; ++db)
+#pragma unroll
+        for (int gq = 0; gq < 4; ++gq) {
+            f32x4 x = {o[db][4 * gq], o[db][4 * gq + 1], o[db][4 * gq + 2], o[db][4 * gq + 3]};
+            *reinterpret_cast<f32x4 *>(po + db * 32 + 8 * gq + 4 * h) = x;
+        }
+    if (h == 0) {
+        p.part_ml[prow * 2] = m_run;
+        p.part_ml[prow * 2 + 1] = l_tot;
+    }
+}
+
+__global__ __launch_bounds__(kDecWaves * 64, 2) void decode_attn_kernel(const AttnParams p)
+{
+    __shared__ __attribute__((aligned(16))) char lds[kDecWaves * kDecLdsPerWave];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lane = threadIdx.x & 63;
+
+    // work unit: row block fastest (neighbouring wavefronts then read the same keys), then key
+    // chunk, KV head, request
+    const int64_t unit = (int64_t)blockIdx.x * kDecWaves + wave;
+    const int rb = (int)(unit % p.dec_row_blocks);
+    const int64_t uc = unit / p.dec_row_blocks;
+    const int chunk = (int)(uc % p.nsplit);
+    const int64_t rk = uc / p.nsplit;
+    const int kvh = (int)(rk % p.Hkv);
+    const int r = (int)(rk / p.Hkv);
+    if (r >= p.batch) return;
+    const int E = p.extend_lens[r];
+    if (E <= 0) return;
+    const int P = p.prefix_lens[r];
+    // packed row of the request's first token: sum of the earlier extend lengths, 64 per step
+    int cu = 0;
+    for (int base = 0; base < r; base += 64) cu += base + lane < r ? p.extend_lens[base + lane] : 0;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) cu += __shfl_xor(cu, off, 64);
+    cu = __builtin_amdgcn_readfirstlane(cu);
+    const int nblk = (P + E + 31) >> 5;
+    const int per = (nblk + p.nsplit - 1) / p.nsplit;
+    const int b0 = chunk * per;
+    const int b1 = min(nblk, b0 + per);
+    decode_chunk(p, lds + wave * kDecLdsPerWave, lane, r, kvh, P, E, cu, rb, b0, b1, (int64_t)chunk * p.T + cu);
 }
 
 // LDS: four K buffers and five V buffers of one 64-key tile (16 KiB) each, K of tile t in buffer
@@ -163,8 +489,18 @@ constexpr int kTileBytesV = kBN * kPitchV;
 constexpr int kNumBufsV = 5;
 constexpr int kLdsBytes = kNumBufs * kTileBytesK + kNumBufsV * kTileBytesV;
 
-template <bool kSplit>
-__global__ __launch_bounds__(kThreads) void extend_attn_kernel(const AttnParams p)
+constexpr int kMixedLdsBytes = kWaves * kDecLdsPerWave > kLdsBytes ? kWaves * kDecLdsPerWave : kLdsBytes;
+
+// What one launch works on: whole key ranges, a split of every request's keys, or a mixed batch:
+// requests of unequal lengths, each split by its own length, decode-shaped ones next to row-tiled ones.
+// One number of splits for all leaves the longest request to finish alone, and a token that is
+// decoded on a row tile of 256 rows occupies a CU for all its keys.  8 chunks of prompts next to 32
+// decoding requests, up to 12000 cached tokens, 32/8 heads: 246 -> 157 us; 5 and 43, 8/2 heads: 144 -> 69;
+// 21 prompts of 20 to 125 tokens, 64/8 heads: 87 -> 54.  Bound by the row-tiled items, which fill the CUs;
+// the decode work behind them on the list runs where CUs fall free.
+enum Mode { kWhole, kSplit, kMixed };
+template <Mode kMode>
+__global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::conditional_t<kMode == kMixed, MixedParams, AttnParams> p)
 {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     char *const lds_k = lds;                          // [4][64 rows][256 B]
@@ -179,15 +515,38 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const AttnParams 
     int kvh = 0;
     const int rem = work_item(blockIdx.x, p, kvh);
     if (rem < 0) return;
-    const int split = rem % p.nsplit;
-    int unit = rem / p.nsplit;
-
+    int r, cu, E, P, unit, split, nsplit, parts = 0;
+    if constexpr (kMode == kMixed) {
+        if (rem >= p.row_items) { // eight wavefronts of decode-shaped work, each on its own
+            const Owner w = find_owner<true>((rem - p.row_items) * kWaves + wave, p, lane);
+            if (w.r >= p.batch) return;
+            const int row_blocks = (w.E * p.G + kDecRows - 1) / kDecRows;
+            const int rb = w.unit % row_blocks, chunk = w.unit / row_blocks; // row blocks of the same keys side by side
+            const int nblk = (w.P + w.E + 31) / 32, per = (nblk + w.splits - 1) / w.splits;
+            decode_chunk(p, lds + wave * kDecLdsPerWave, lane, w.r, kvh, w.P, w.E, w.cu, rb, chunk * per,
+                         min(nblk, chunk * per + per), w.splits > 1 ? w.parts + (int64_t)chunk * w.E : -1);
+            return;
+        }
+        const Owner w = find_owner<false>(rem, p, lane);
+        r = w.r;
+        cu = w.cu;
+        E = w.E;
+        P = w.P;
+        parts = w.parts;
+        nsplit = max(w.splits, 1);
+        split = w.unit % nsplit;
+        unit = w.unit / nsplit;
+    } else {
+        nsplit = p.nsplit;
+        split = rem % nsplit;
+        unit = rem / nsplit;
+        r = p.batch;
+        cu = E = P = 0;
     // Units of a KV head: requests in order; within a request the last (longest) row tile
     // first, and for each row tile the groups of q heads that are packed into one workgroup.
     // The request that owns the unit is found 64 requests at a time: every lane takes one
     // request, a prefix sum over the wavefront gives the first unit of each (a sequential scan
     // costs a dependent scalar load and several integer divisions per request, ~1.5 us each).
-    int r = p.batch, cu = 0, E = 0, t = 0, pack = 1, hgroup = 0;
     for (int base = 0; base < p.batch; base += 64) {
         const int rr = base + lane;
         const int e_l = rr < p.batch ? p.extend_lens[rr] : 0;
@@ -206,17 +565,16 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const AttnParams 
         unit -= total_u;
         cu += __builtin_amdgcn_readlane(incl_e, 63);
     }
-    if (r < p.batch) {
-        pack = heads_per_tile(E, p.G);
-        int shift = 0;
-        while ((1 << shift) < pack) ++shift;
-        const int groups = p.G >> shift;
-        const int nt = (E * pack + kBM - 1) / kBM; // row tiles of kBM / pack rows
-        hgroup = unit % groups;
-        t = nt - 1 - unit / groups;
+    if (r < p.batch) P = p.prefix_lens[r];
     }
     if (r >= p.batch) return;
-    const int P = p.prefix_lens[r];
+    const int pack = heads_per_tile(E, p.G);
+    int shift = 0;
+    while ((1 << shift) < pack) ++shift;
+    const int groups = p.G >> shift;
+    const int nt = (E * pack + kBM - 1) / kBM; // row tiles of kBM / pack rows
+    const int hgroup = unit % groups;
+    const int t = nt - 1 - unit / groups;
 
     // GQA head sharing: `pack` q heads of the KV head share the workgroup's K/V tiles, each
     // with kBM / pack query rows; a wavefront belongs to exactly one of them.
@@ -229,18 +587,23 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const AttnParams 
     const int np_tiles = (P + kBN - 1) / kBN;        // prefix key tiles
     const int ns_tiles = (rows_end + kBN - 1) / kBN; // suffix key tiles up to the diagonal
     const int n_tiles = np_tiles + ns_tiles;
-    const int per_split = (n_tiles + p.nsplit - 1) / p.nsplit;
+    // mixed: a row tile with fewer keys than the last one of its request takes fewer ranges, the rest stay empty
+    int n_ranges = nsplit;
+    if constexpr (kMode == kMixed) n_ranges = min(nsplit, (n_tiles + p.seg_tiles - 1) / p.seg_tiles);
+    const int per_split = (n_tiles + n_ranges - 1) / n_ranges;
     const int kt_begin = split * per_split;
     const int kt_end = min(n_tiles, kt_begin + per_split);
     const int n_it = kt_end - kt_begin;              // key tiles of this work item
 
     const int64_t out_row = (int64_t)(cu + min(row_i, E - 1));
     const bool row_valid = row_i < E;
+    const bool partial = kMode == kMixed ? nsplit > 1 : kMode == kSplit;
+    auto part_row = [&] { return kMode == kMixed ? parts + (int64_t)split * E + row_i : (int64_t)split * p.T + out_row; };
 
     if (n_it <= 0) {
         // empty split: the merge skips entries whose sum is zero
-        if (kSplit && row_valid && h == 0) {
-            float *ml = p.part_ml + (((int64_t)split * p.T + out_row) * p.Hq + head) * 2;
+        if (partial && row_valid && h == 0) {
+            float *ml = p.part_ml + (part_row() * p.Hq + head) * 2;
             ml[0] = -INFINITY;
             ml[1] = 0.f;
         }
@@ -665,8 +1028,8 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const AttnParams 
     // ---- epilogue.  o[db][v] is O^T[d = db*32 + 8*(v/4) + 4*h + v%4][row j]
     const float l_tot = halfwave_sum(l_run);
     if (!row_valid) return;
-    if (kSplit) {
-        const int64_t prow = ((int64_t)split * p.T + out_row) * p.Hq + head;
+    if (partial) {
+        const int64_t prow = part_row() * p.Hq + head;
         float *po = p.part_o + prow * kD;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -804,240 +1167,83 @@ __global__ __launch_bounds__(256) void merge_few_splits_kernel(const float *__re
     *reinterpret_cast<bf16x4 *>(out + rh * kD + d4) = y;
 }
 
-// ---- decode-shaped calls ------------------------------------------------------------------
-// When every request brings so few new tokens that all its rows for one KV head (G heads x E_r
-// tokens) fit a few 32-column MFMA tiles, the call is bound by reading the cached K/V once,
-// and the row-tiled kernel above wastes its wavefronts (most hold no valid row) and keeps too
-// little in flight.  This kernel turns the work around: a wavefront is the unit, owns 32 rows
-// of one (request, KV head) and a contiguous chunk of the keys, and runs alone - no barrier, no
-// shared tile.  Per block of 32 keys it loads the K and V rows with fully coalesced 16-byte
-// loads (one instruction = four whole rows), stages them in registers while the previous block
-// is computed, and passes them through a private LDS area from which the MFMA operands are read
-// (K rows as they are, V rows transposed).  Every wavefront writes an unnormalised partial
-// (m, l, O) and merge_splits_kernel combines them, exactly as for split-K.  Prefix and suffix
-// keys form one sequence of N = P + E keys; blocks inside the prefix take their two pages from
-// the block table with scalar loads, the last blocks resolve every row on its own.
-constexpr int kDecRows = 32;            // (head, token) rows per wavefront
-constexpr int kDecMaxRowBlocks = 2;     // row blocks per (request, KV head): G x E_r <= 64 (beyond, the row-tiled kernel is faster)
-constexpr int kDecWaves = 4;            // wavefronts per workgroup (independent of each other)
-// LDS bytes per K row / V row: 256 + padding.  16 consecutive K rows at the same column fall into
-// 16 different 16-byte bank groups, the four consecutive V rows of a transposing read into four
-// different 64-byte bank groups, and every read address is a per-lane base plus an immediate.
-constexpr int kDecPitchK = 272;
-constexpr int kDecPitchV = 320;
-constexpr int kDecLdsK = 32 * kDecPitchK;
-constexpr int kDecLdsPerWave = kDecLdsK + 32 * kDecPitchV;
-constexpr int kDecMaxChunks = 256;      // key chunks (= partial results) per (request, KV head)
 static_assert(kDecMaxChunks <= kMergeGroups * kMergePerGroup && kMaxSplits <= kMergeGroups * kMergePerGroup,
               "the merge kernel holds all partial results of a row in registers");
 
-struct DecBlock { // one block of 32 keys as loaded: piece i is row (lane / 16) + 4 i, chunk lane % 16
-    u32x4 k[8];
-    u32x4 v[8];
-};
-
-__global__ __launch_bounds__(kDecWaves * 64, 2) void decode_attn_kernel(const AttnParams p)
+// Mixed batches: the rows whose requests have more than one key range (at most kMaxSplits), packed.  A
+// workgroup takes one of them and eight heads, 32 threads each: thread t first reads (m, l) of the
+// splits t and t + 32, then every thread adds up 4 consecutive d over the splits in order.
+constexpr int kMergeHeads = 8;
+__global__ __launch_bounds__(32 * kMergeHeads) void merge_mixed_kernel(const MixedParams p)
 {
-    __shared__ __attribute__((aligned(16))) char lds[kDecWaves * kDecLdsPerWave];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int lane = threadIdx.x & 63;
-    const int j = lane & 31; // (head, token) row of the accumulators; key row of the K operand
-    const int h = lane >> 5;
-    char *const lds_k = lds + wave * kDecLdsPerWave;
-    char *const lds_v = lds_k + kDecLdsK;
-
-    // work unit: row block fastest (neighbouring wavefronts then read the same keys), then key
-    // chunk, KV head, request
-    const int64_t unit = (int64_t)blockIdx.x * kDecWaves + wave;
-    const int rb = (int)(unit % p.dec_row_blocks);
-    const int64_t uc = unit / p.dec_row_blocks;
-    const int chunk = (int)(uc % p.nsplit);
-    const int64_t rk = uc / p.nsplit;
-    const int kvh = (int)(rk % p.Hkv);
-    const int r = (int)(rk / p.Hkv);
-    if (r >= p.batch) return;
-    const int E = p.extend_lens[r];
-    if (E <= 0) return;
-    const int P = p.prefix_lens[r];
-    // packed row of the request's first token: sum of the earlier extend lengths, 64 per step
-    int cu = 0;
-    for (int base = 0; base < r; base += 64) cu += base + lane < r ? p.extend_lens[base + lane] : 0;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) cu += __shfl_xor(cu, off, 64);
-    cu = __builtin_amdgcn_readfirstlane(cu);
-    const int N = P + E;
-    const int nblk = (N + 31) >> 5;
-    const int per = (nblk + p.nsplit - 1) / p.nsplit;
-    const int b0 = chunk * per;
-    const int b1 = min(nblk, b0 + per);
-
-    // row 32 rb + j of the (request, KV head) is token e of head hg of the group; rows beyond
-    // G E are padding
-    if (rb * kDecRows >= p.G * E) return;
-    const int row = rb * kDecRows + j;
-    const bool row_valid = row < p.G * E;
-    const int hg = row_valid ? row / E : 0;
-    const int e = row_valid ? row - hg * E : 0;
-    const int head = kvh * p.G + hg;
-    const int64_t out_row = cu + e;
-    const int64_t prow = ((int64_t)chunk * p.T + out_row) * p.Hq + head;
-    if (b0 >= b1) { // nothing to do for this chunk: the merge skips entries whose sum is zero
-        if (row_valid && h == 0) {
-            p.part_ml[prow * 2] = -INFINITY;
-            p.part_ml[prow * 2 + 1] = 0.f;
+    const int head_blocks = (p.Hq + kMergeHeads - 1) / kMergeHeads;
+    const int head = (int)(blockIdx.x % head_blocks) * kMergeHeads + (threadIdx.x >> 5);
+    const int lane = threadIdx.x & 63, t = threadIdx.x & 31;
+    int row = blockIdx.x / head_blocks; // among the rows to merge
+    int ns = 0, E = 0, cu = 0;
+    int64_t parts = 0;
+    for (int base = 0; base < p.batch; base += 64) {
+        const int rr = base + lane;
+        const int e = rr < p.batch ? p.extend_lens[rr] : 0;
+        const int pl = rr < p.batch ? p.prefix_lens[rr] : 0;
+        const int s = splits_of_request(pl, e, p.G, p.seg_tiles, p.dec_blocks);
+        const int rows = s > 1 ? e : 0;
+        const int incl_r = wave_inclusive_scan(rows, lane);
+        const int incl_e = wave_inclusive_scan(e, lane);
+        const int incl_p = wave_inclusive_scan(rows * s, lane);
+        const int total = __builtin_amdgcn_readlane(incl_r, 63);
+        if (row < total) {
+            const int first = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl_r > row));
+            row -= __builtin_amdgcn_readlane(incl_r - rows, first);
+            cu += __builtin_amdgcn_readlane(incl_e - e, first);
+            parts += __builtin_amdgcn_readlane(incl_p - rows * s, first);
+            E = __builtin_amdgcn_readlane(e, first);
+            ns = __builtin_amdgcn_readlane(s, first);
+            break;
         }
-        return;
+        row -= total;
+        cu += __builtin_amdgcn_readlane(incl_e, 63);
+        parts += __builtin_amdgcn_readlane(incl_p, 63);
     }
-
-    // Q fragments, B operand of S^T = K Q^T: lane (row j, h) holds q[row][16 kk + 8 h .. + 8)
-    u32x4 qf[8];
-    {
-        const uint16_t *qp = p.q + (out_row * p.Hq + head) * kD + 8 * h;
+    if (head >= p.Hq) return;
+    const int64_t first = (parts + row) * p.Hq + head, step = (int64_t)E * p.Hq; // partial result s: first + s * step
+    f32x2 ml[2];
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qf[kk] = *(const __attribute__((address_space(1))) u32x4 *)(qp + 16 * kk);
-    }
-
-    // loads: lane covers rows ld_sub + 4 i (i = 0..7) of the block, 16-byte chunk ld_chunk
-    const int ld_sub = lane >> 4, ld_chunk = lane & 15;
-    const __attribute__((address_space(4))) int32_t *table =
-        (const __attribute__((address_space(4))) int32_t *)(p.block_table + (int64_t)r * p.max_pages);
-    const int64_t v_plane = (int64_t)p.Hkv * kPS * kD;
-    const int64_t page_stride = 2 * v_plane;
-    const uint16_t *pages_head = p.kv_pages + (int64_t)kvh * (kPS * kD) + ld_chunk * 8;
-    auto load_block = [&](int b, DecBlock &blk) {
-        if (b * 32 + 32 <= P) {
-            // inside the prefix: rows 0..15 in page 2 b, rows 16..31 in page 2 b + 1
-            const int64_t pg[2] = {table[2 * b], table[2 * b + 1]};
+    for (int i = 0; i < 2; ++i)
+        ml[i] = t + 32 * i < ns ? *reinterpret_cast<const f32x2 *>(p.part_ml + (first + (t + 32 * i) * step) * 2) : f32x2{0.f, 0.f};
+    float m_star = fmaxf(ml[0][1] > 0.f ? ml[0][0] : -INFINITY, ml[1][1] > 0.f ? ml[1][0] : -INFINITY);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint16_t *krow = pages_head + pg[i >> 2] * page_stride + ((ld_sub + 4 * i) & 15) * kD;
-                blk.k[i] = *(const __attribute__((address_space(1))) u32x4 *)(krow);
-                blk.v[i] = *(const __attribute__((address_space(1))) u32x4 *)(krow + v_plane);
-            }
-        } else {
-            // last blocks: every row resolves its own key (clamped to the last one; masked below)
+    for (int off = 16; off > 0; off >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, off, 32));
+    float w[2];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const int key = min(b * 32 + ld_sub + 4 * i, N - 1);
-                const uint16_t *krow, *vrow;
-                if (key < P) {
-                    krow = pages_head + (int64_t)p.block_table[(int64_t)r * p.max_pages + (key >> 4)] * page_stride +
-                           (key & 15) * kD;
-                    vrow = krow + v_plane;
-                } else {
-                    const int64_t off = ((int64_t)(cu + key - P) * p.Hkv + kvh) * kD + ld_chunk * 8;
-                    krow = p.k_new + off;
-                    vrow = p.v_new + off;
-                }
-                blk.k[i] = *(const __attribute__((address_space(1))) u32x4 *)(krow);
-                blk.v[i] = *(const __attribute__((address_space(1))) u32x4 *)(vrow);
+    for (int i = 0; i < 2; ++i) w[i] = ml[i][1] > 0.f ? fast_exp2(ml[i][0] - m_star) : 0.f;
+    float denom = ml[0][1] * w[0] + ml[1][1] * w[1];
+#pragma unroll
+    for (int off = 16; off > 0; off >>= 1) denom += __shfl_xor(denom, off, 32);
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    // `many` loads in flight at a time: a decode row has up to kMaxSplits partial results and few others beside it
+    auto add_up = [&](auto many) {
+        constexpr int kMany = decltype(many)::value;
+        for (int s0 = 0; s0 < ns; s0 += kMany) {
+            f32x4 x[kMany];
+#pragma unroll
+            for (int i = 0; i < kMany; ++i)
+                x[i] = s0 + i < ns ? *reinterpret_cast<const f32x4 *>(p.part_o + (first + (s0 + i) * step) * kD + t * 4)
+                                   : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < kMany; ++i) {
+                const float ws = __shfl(s0 < 32 ? w[0] : w[1], (s0 + i) & 31, 32);
+                if (ws > 0.f) acc += x[i] * ws; // an empty range left no values
             }
         }
     };
-    const int st_k = ld_sub * kDecPitchK + ld_chunk * 16;
-    const int st_v = ld_sub * kDecPitchV + ld_chunk * 16;
-    auto store_block = [&](const DecBlock &blk) {
+    if (ns <= 4) add_up(std::integral_constant<int, 4>{});
+    else add_up(std::integral_constant<int, 16>{});
+    const float inv = denom > 0.f ? 1.f / denom : 0.f;
+    bf16x4 y;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            *reinterpret_cast<u32x4 *>(lds_k + st_k + 4 * i * kDecPitchK) = blk.k[i];
-            *reinterpret_cast<u32x4 *>(lds_v + st_v + 4 * i * kDecPitchV) = blk.v[i];
-        }
-    };
-    // operand reads, as in the kernel above
-    const int k_lane = j * kDecPitchK + h * 16;
-    const int v_lane = (4 * h + ((lane & 15) >> 2)) * kDecPitchV + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
-
-    f32x16 o[4];
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f; // log2 domain; sum over this half-wave's keys
-    const float c = p.scale_log2;
-    const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-
-    DecBlock blk;
-    load_block(b0, blk);
-    for (int b = b0; b < b1; ++b) {
-        // block b: registers -> private LDS (one wavefront's LDS operations are served in order,
-        // so these writes come after the reads of block b - 1), then block b + 1 into flight
-        store_block(blk);
-        if (b + 1 < b1) load_block(b + 1, blk);
-        f32x16 s;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = 0.f;
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk) {
-            const u32x4 a = *reinterpret_cast<const u32x4 *>(lds_k + k_lane + kk * 32);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                         __builtin_bit_cast(bf16x8, qf[kk]), s, 0, 0, 0);
-        }
-        // accumulator element v is key 32 b + 8 (v / 4) + 4 h + v % 4; row j sees keys <= P + e
-        if (b * 32 + 31 > P) {
-            const int vis = P + e - b * 32 - 4 * h; // visible: 8 (v / 4) + v % 4 <= vis
-#pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (8 * (v >> 2) + (v & 3) > vis) s[v] = -INFINITY;
-        }
-        float mx = s[0];
-#pragma unroll
-        for (int v = 1; v + 1 < 16; v += 2) mx = fmaxf(fmaxf(mx, s[v]), s[v + 1]);
-        mx = halfwave_max(fmaxf(mx, s[15]));
-        const float m_new = fmaxf(m_run, mx * c);
-        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = fast_exp2(m_run - m_use);
-        u32x4 pb[2];
-        float psum = 0.f;
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                f32x2 x;
-                x[0] = fast_exp2(fmaf(s[8 * u + 2 * w], c, -m_use));
-                x[1] = fast_exp2(fmaf(s[8 * u + 2 * w + 1], c, -m_use));
-                const bf16x2 y = __builtin_convertvector(x, bf16x2);
-                psum = __builtin_amdgcn_fdot2_f32_bf16(y, ones, psum, false);
-                pb[u][w] = __builtin_bit_cast(unsigned, y);
-            }
-        l_run = l_run * alpha + psum;
-        m_run = m_new;
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
-#pragma unroll
-            for (int db = 0; db < 4; ++db)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
-        }
-        // O^T += V^T P^T: 2 steps of 16 keys x 4 blocks of 32 d
-#pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-            for (int db = 0; db < 4; ++db) {
-                const char *a = lds_v + v_lane + db * 64 + ks * 16 * kDecPitchV;
-                const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) s16x4 *)(a));
-                const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) s16x4 *)(a + 8 * kDecPitchV));
-                const s16x8 vv = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv),
-                                                                 __builtin_bit_cast(bf16x8, pb[ks]), o[db], 0, 0, 0);
-            }
-    }
-
-    // partial result of this chunk; o[db][v] is O^T[d = db*32 + 8*(v/4) + 4*h + v%4][row j]
-    const float l_tot = halfwave_sum(l_run);
-    if (!row_valid) return;
-    float *po = p.part_o + prow * kD;
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-        for (int gq = 0; gq < 4; ++gq) {
-            f32x4 x = {o[db][4 * gq], o[db][4 * gq + 1], o[db][4 * gq + 2], o[db][4 * gq + 3]};
-            *reinterpret_cast<f32x4 *>(po + db * 32 + 8 * gq + 4 * h) = x;
-        }
-    if (h == 0) {
-        p.part_ml[prow * 2] = m_run;
-        p.part_ml[prow * 2 + 1] = l_tot;
-    }
+    for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[e] * inv);
+    *reinterpret_cast<bf16x4 *>(p.out + ((int64_t)(cu + row) * p.Hq + head) * kD + t * 4) = y;
 }
 
 // One workgroup copies 16 consecutive packed rows.  Its first wavefront finds the request, the
@@ -1168,6 +1374,10 @@ struct Plan {
     int32_t nsplit;
     bool decode;       // few rows per (request, KV head): decode_attn_kernel
     int32_t row_blocks; // ... in this many blocks of 32 rows
+    bool mixed = false; // unequal lengths: extend_attn_kernel<kMixed>, with
+    int32_t seg_tiles = 1, dec_blocks = 1;       // at most so many keys per item
+    int64_t row_items = 0, dec_units = 0;        // row-tiled items and decode wavefronts per KV head
+    int64_t merge_rows = 0, part_rows = 0;       // rows with more than one key range, their partial results
 };
 
 // Compute units of the device the first caller runs on (every device this library is built
@@ -1192,11 +1402,13 @@ bool allow_large_lds()
     static std::once_flag once;
     static bool ok = false;
     std::call_once(once, [] {
-        const hipError_t a = hipFuncSetAttribute(reinterpret_cast<const void *>(&extend_attn_kernel<false>),
+        const hipError_t a = hipFuncSetAttribute(reinterpret_cast<const void *>(&extend_attn_kernel<kWhole>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-        const hipError_t b = hipFuncSetAttribute(reinterpret_cast<const void *>(&extend_attn_kernel<true>),
+        const hipError_t b = hipFuncSetAttribute(reinterpret_cast<const void *>(&extend_attn_kernel<kSplit>),
                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
-        ok = a == hipSuccess && b == hipSuccess;
+        const hipError_t c = hipFuncSetAttribute(reinterpret_cast<const void *>(&extend_attn_kernel<kMixed>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, kMixedLdsBytes);
+        ok = a == hipSuccess && b == hipSuccess && c == hipSuccess;
     });
     return ok;
 }
@@ -1223,7 +1435,138 @@ int validate(const cp_shape *s)
     return CP_OK;
 }
 
-Plan make_plan(const cp_shape *s)
+bool equal_lengths(const cp_shape *s)
+{
+    for (int r = 1; r < s->batch; ++r)
+        if (s->h_prefix_lens[r] != s->h_prefix_lens[0] || s->h_extend_lens[r] != s->h_extend_lens[0]) return false;
+    return true;
+}
+
+size_t part_bytes(size_t rows, int heads)
+{
+    const size_t n = rows * (size_t)heads;
+    return ((n * kD * sizeof(float) + 255) / 256) * 256 + ((n * 2 * sizeof(float) + 255) / 256) * 256;
+}
+
+// Plan of a mixed batch: the key ranges with the least estimated time.  What the estimate is made of,
+// in us: a row-tiled item costs kItemUs and kTileUs per key tile of 64 on one CU, a decode workgroup (8
+// wavefronts) kItemUs and kBlockUs per block of 32 keys; partial results are written and read once.
+constexpr double kItemUs = 4.0, kTileUs = 1.75, kBlockUs = 3.0, kMergeUs = 5.0, kPartBytesPerUs = 4.0e6;
+struct MixedRequest {
+    int64_t units;  // row tiles x head groups, or row blocks of decode-shaped work
+    int32_t extend; // new tokens
+    int32_t length; // key tiles of the last row tile, or key blocks of 32
+    float mean;     // key tiles or blocks of a unit on average
+    int32_t r;      // index in the batch
+    bool decode;
+};
+
+// Fills pl for at most seg_tiles key tiles per row-tiled item; returns the time.
+double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks, int kv_heads, int q_heads, Plan &pl)
+{
+    pl.mixed = true;
+    pl.seg_tiles = seg_tiles;
+    pl.dec_blocks = dec_blocks;
+    // One KV head on its share of the CUs, in the order of the list: the items of the first requests
+    // alone take their sum over the CUs and about half of the last one's length, and no less than the longest.
+    const double cus = (double)num_cus() / kv_heads;
+    double work = 0.0, most = 0.0;
+    for (int i = 0; i < n; ++i) {
+        const MixedRequest &m = req[i];
+        // as splits_of_request; a decode request has at most kMaxSplits ranges by the choice of dec_blocks
+        const int limit = m.decode ? dec_blocks : seg_tiles;
+        const int ns = std::min(kMaxSplits, (m.length + limit - 1) / limit);
+        const double step = m.decode ? kBlockUs : kTileUs;
+        const double us = (double)m.units * (ns * kItemUs + m.mean * step);
+        work += m.decode ? us / kWaves : us;
+        const double item = kItemUs + step * ((m.length + ns - 1) / ns);
+        most = std::max(most, std::max(item, work / cus + 0.5 * item));
+        (m.decode ? pl.dec_units : pl.row_items) += m.units * ns;
+        pl.nsplit = std::max(pl.nsplit, ns);
+        if (ns > 1) {
+            pl.merge_rows += m.extend;
+            pl.part_rows += (int64_t)ns * m.extend;
+        }
+    }
+    double us = most;
+    if (pl.part_rows > 0) us += kMergeUs + 2.0 * (double)part_bytes((size_t)pl.part_rows, q_heads) / kPartBytesPerUs;
+    return us;
+}
+
+// The best plan whose partial results fit into `room` bytes; false if there is none.
+bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order)
+{
+    const int G = s->num_q_heads / s->num_kv_heads;
+    MixedRequest req[kMixedMaxBatch];
+    int n = 0;
+    int32_t tiles = 1, blocks = 1;
+    int64_t decode_work = 0; // key blocks of all decode wavefronts
+    for (int r = 0; r < s->batch; ++r) {
+        const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
+        if (E == 0) continue;
+        MixedRequest &m = req[n++];
+        m.r = r;
+        m.extend = (int32_t)E;
+        m.decode = decode_shaped((int)E, G);
+        if (m.decode) {
+            m.units = (E * G + kDecRows - 1) / kDecRows;
+            m.length = (int32_t)((P + E + 31) / 32);
+            m.mean = (float)m.length;
+            blocks = std::max(blocks, m.length);
+            decode_work += m.units * m.length * s->num_kv_heads;
+        } else {
+            const int pack = heads_per_tile((int)E, G);
+            const int64_t nt = (E * pack + kBM - 1) / kBM;
+            const int32_t prefix = (int32_t)((P + kBN - 1) / kBN), own = (int32_t)((E + kBN - 1) / kBN);
+            m.units = units_of_request((int)E, G, pack);
+            m.length = prefix + own;
+            m.mean = (float)prefix + 0.5f * (float)own * (1.f + 1.f / (float)nt);
+        }
+        tiles = std::max(tiles, m.decode ? (m.length + 1) / 2 : m.length);
+    }
+    // row-tiled requests first, most keys first
+    std::sort(req, req + n, [](const MixedRequest &a, const MixedRequest &b) {
+        if (a.decode != b.decode) return b.decode;
+        return a.length != b.length ? a.length > b.length : a.r < b.r;
+    });
+    if (order) {
+        int at[kMixedMaxBatch / 64];
+        for (int g = 0; g < kMixedMaxBatch / 64; ++g) at[g] = 64 * g;
+        bool placed[kMixedMaxBatch] = {};
+        for (int i = 0; i < n; ++i) {
+            order[at[req[i].r / 64]++] = (uint8_t)(req[i].r % 64);
+            placed[req[i].r] = true;
+        }
+        for (int r = 0; r < (s->batch + 63) / 64 * 64; ++r) // no new tokens, or behind the batch's last request
+            if (!placed[r]) order[at[r / 64]++] = (uint8_t)(r % 64);
+    }
+    double best_us = -1.0;
+    int worse = 0;
+    for (int pieces = 1; pieces <= kMaxSplits && worse < 4; pieces += pieces < 8 ? 1 : pieces / 4) {
+        const int seg = (tiles + pieces - 1) / pieces;
+        if (pieces > 1 && seg < 2) break;
+        // A decode wavefront's chunk takes about as long as a row-tiled item, but is no shorter than
+        // twice its share of the decode work (8 wavefronts per CU), 4 to 16 blocks: finer chunks only
+        // give the merge more to read (21 requests, 218 MB of decode K/V: 16 blocks 49 us, 8: 52, 4: 57).
+        const int least = (int)std::min<int64_t>(16, std::max<int64_t>(4, 2 * decode_work / (8 * num_cus())));
+        const int dec = std::max(std::max(least, (int)(seg * (kTileUs / kBlockUs))), (blocks + kMaxSplits - 1) / kMaxSplits);
+        Plan pl{0, 0, 1, false, 1};
+        const double us = mixed_cost(req, n, seg, dec, s->num_kv_heads, s->num_q_heads, pl);
+        if (pl.part_rows > INT32_MAX / 2 || (pl.part_rows > 0 && part_bytes((size_t)pl.part_rows, s->num_q_heads) > room)) continue;
+        if ((pl.row_items + (pl.dec_units + kWaves - 1) / kWaves) * s->num_kv_heads > INT32_MAX / 2) continue;
+        worse = best_us >= 0.0 && us >= best_us ? worse + 1 : 0;
+        if (worse == 0) {
+            best_us = us;
+            best = pl;
+        }
+    }
+    return best_us >= 0.0;
+}
+
+// `room`: bytes that the caller has for partial results.  A batch of unequal lengths whose own plan
+// needs more takes the uniform one.
+// `order`: receives MixedParams::order of a mixed plan.
+Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullptr)
 {
     Plan pl{0, 0, 1, false, 1};
     const int G = s->num_q_heads / s->num_kv_heads;
@@ -1249,6 +1592,7 @@ Plan make_plan(const cp_shape *s)
         pl.decode = true;
         return pl;
     }
+    if (s->num_splits == 0 && s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, room, pl, order)) return pl;
     for (int r = 0; r < s->batch; ++r) {
         const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
         if (E == 0) continue;
@@ -1275,13 +1619,6 @@ Plan make_plan(const cp_shape *s)
     return pl;
 }
 
-bool equal_lengths(const cp_shape *s)
-{
-    for (int r = 1; r < s->batch; ++r)
-        if (s->h_prefix_lens[r] != s->h_prefix_lens[0] || s->h_extend_lens[r] != s->h_extend_lens[0]) return false;
-    return true;
-}
-
 // Launches the merge of nsplit partial results for n_rh (row, head) pairs.
 void launch_merge(const AttnParams &p, int nsplit, hipStream_t hs)
 {
@@ -1301,11 +1638,9 @@ void launch_merge(const AttnParams &p, int nsplit, hipStream_t hs)
 
 size_t workspace_for(const cp_shape *s, const Plan &pl)
 {
+    if (pl.mixed) return pl.part_rows > 0 ? part_bytes((size_t)pl.part_rows, s->num_q_heads) : 0;
     if (pl.nsplit <= 1) return 0;
-    const size_t rows = (size_t)pl.nsplit * (size_t)s->total_extend * (size_t)s->num_q_heads;
-    size_t o_bytes = rows * kD * sizeof(float);
-    size_t ml_bytes = rows * 2 * sizeof(float);
-    return ((o_bytes + 255) / 256) * 256 + ((ml_bytes + 255) / 256) * 256;
+    return part_bytes((size_t)pl.nsplit * (size_t)s->total_extend, s->num_q_heads);
 }
 
 
@@ -1489,19 +1824,19 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
                                      nullptr);
         if (chk != CP_OK) return chk;
     }
-    const Plan pl = make_plan(shape);
+    MixedParams p;
+    const Plan pl = make_plan(shape, workspace && aligned_to(workspace, 256) ? workspace_bytes : 0, p.order);
     const size_t need = workspace_for(shape, pl);
     if (need > 0) {
         if (!workspace || workspace_bytes < need) return CP_ERR_WORKSPACE;
-        if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return CP_ERR_WORKSPACE;
+        if (!aligned_to(workspace, 256)) return CP_ERR_WORKSPACE;
     }
-    const int64_t per_head = pl.q_tiles * pl.nsplit;
+    const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves : pl.q_tiles * pl.nsplit;
     const int64_t total = per_head * shape->num_kv_heads;
     if (total > INT32_MAX / 2) return CP_ERR_SHAPE;
     const int64_t dec_units = (int64_t)shape->batch * shape->num_kv_heads * pl.nsplit * pl.row_blocks;
     if (pl.decode && dec_units > INT32_MAX / 2) return CP_ERR_SHAPE;
 
-    AttnParams p;
     p.q = static_cast<const uint16_t *>(q);
     p.k_new = static_cast<const uint16_t *>(k_new);
     p.v_new = static_cast<const uint16_t *>(v_new);
@@ -1528,29 +1863,38 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
                                                     : (total + kXcds - 1) / kXcds);
     p.scale_log2 = shape->softmax_scale * 1.4426950408889634f;
 
+    p.seg_tiles = pl.seg_tiles;
+    p.dec_blocks = pl.dec_blocks;
+    p.row_items = (int32_t)pl.row_items;
+
     hipStream_t hs = static_cast<hipStream_t>(stream);
-    if (pl.decode) {
-        const size_t rows = (size_t)pl.nsplit * (size_t)p.T * (size_t)p.Hq;
-        const size_t o_bytes = ((rows * kD * sizeof(float) + 255) / 256) * 256;
+    if (need > 0) {
+        const size_t rows = (pl.mixed ? (size_t)pl.part_rows : (size_t)pl.nsplit * (size_t)p.T) * (size_t)p.Hq;
         p.part_o = static_cast<float *>(workspace);
-        p.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + o_bytes);
-        hipLaunchKernelGGL(decode_attn_kernel, dim3((unsigned)(dec_units / kDecWaves)), dim3(kDecWaves * 64), 0, hs, p);
+        p.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + ((rows * kD * sizeof(float) + 255) / 256) * 256);
+    }
+    if (pl.decode) {
+        hipLaunchKernelGGL(decode_attn_kernel, dim3((unsigned)(dec_units / kDecWaves)), dim3(kDecWaves * 64), 0, hs,
+                           static_cast<const AttnParams &>(p));
         if (hipGetLastError() != hipSuccess) return CP_ERR_LAUNCH;
         launch_merge(p, pl.nsplit, hs);
         return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_LAUNCH;
     }
     if (!allow_large_lds()) return CP_ERR_LAUNCH;
     const dim3 grid((unsigned)(p.items_per_xcd * kXcds)), block(kThreads);
-    if (pl.nsplit > 1) {
-        const size_t rows = (size_t)pl.nsplit * (size_t)p.T * (size_t)p.Hq;
-        const size_t o_bytes = ((rows * kD * sizeof(float) + 255) / 256) * 256;
-        p.part_o = static_cast<float *>(workspace);
-        p.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + o_bytes);
-        hipLaunchKernelGGL(extend_attn_kernel<true>, grid, block, kLdsBytes, hs, p);
+    if (pl.mixed) {
+        hipLaunchKernelGGL(extend_attn_kernel<kMixed>, grid, block, kMixedLdsBytes, hs, p);
+        if (pl.merge_rows > 0) {
+            if (hipGetLastError() != hipSuccess) return CP_ERR_LAUNCH;
+            const int64_t blocks = pl.merge_rows * ((p.Hq + kMergeHeads - 1) / kMergeHeads);
+            hipLaunchKernelGGL(merge_mixed_kernel, dim3((unsigned)blocks), dim3(32 * kMergeHeads), 0, hs, p);
+        }
+    } else if (pl.nsplit > 1) {
+        hipLaunchKernelGGL(extend_attn_kernel<kSplit>, grid, block, kLdsBytes, hs, static_cast<const AttnParams &>(p));
         if (hipGetLastError() != hipSuccess) return CP_ERR_LAUNCH;
         launch_merge(p, pl.nsplit, hs);
     } else {
-        hipLaunchKernelGGL(extend_attn_kernel<false>, grid, block, kLdsBytes, hs, p);
+        hipLaunchKernelGGL(extend_attn_kernel<kWhole>, grid, block, kLdsBytes, hs, static_cast<const AttnParams &>(p));
     }
     if (hipGetLastError() != hipSuccess) return CP_ERR_LAUNCH;
     return CP_OK;
@@ -1577,7 +1921,7 @@ int cp_extend_attention_noalloc(const void *q, const void *k_new, const void *v_
     const int st = validate(shape);
     if (st != CP_OK) return st;
     // sizes beyond the library's own array are refused here, before anything is looked up or launched
-    if (workspace_for(shape, make_plan(shape)) > CP_NOALLOC_SCRATCH_BYTES) return CP_ERR_WORKSPACE;
+    if (workspace_for(shape, make_plan(shape, CP_NOALLOC_SCRATCH_BYTES)) > CP_NOALLOC_SCRATCH_BYTES) return CP_ERR_WORKSPACE;
     void *ptr = scratch_address(); // the array's address on the current device, never the array's name
     if (!ptr) return CP_ERR_LAUNCH;
     return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, shape, ptr,

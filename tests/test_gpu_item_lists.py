@@ -26,3 +26,37 @@ def test_items_dealt_out_over_the_xcds(H, Hkv, P, E):
     want = oracle.attention_of(w)
     for splits in (1, 3):
         _check(H.gpu_attention(w, num_splits=splits), want, f"Hkv={Hkv} P={P} E={E} splits={splits}")
+
+
+@pytest.mark.parametrize("G,Hkv", [(4, 2), (8, 1), (1, 3), (4, 8)])
+@pytest.mark.parametrize("P,E", [
+    ([300, 40, 0, 1000], [1, 257, 16, 1]),                # decode-shaped requests next to a row tile and a bit
+    ([6000, 10, 3000, 0, 64], [1, 300, 4, 700, 65]),      # several key ranges for some requests, one for others
+    ([2000, 31, 32, 33, 0], [2, 1, 1, 1, 1]),             # blocks of 32 keys: remainders
+    ([4096, 50, 0], [0, 513, 1]),                         # a request without new tokens
+])
+def test_batches_of_unequal_lengths(H, G, Hkv, P, E):
+    import paper_2511_03475_amd as cp
+
+    w = W.make_uniform("mixed", 52, len(P), G * Hkv, Hkv, P, E)
+    want = oracle.attention_of(w)
+    case = H.DeviceCase(w)
+    _check(H.gpu_attention(w), want, f"G={G} Hkv={Hkv} P={P} E={E}")
+    # without room for the partial results of its own plan the batch takes a plan that needs none, or
+    # is refused if every plan of its shape needs some
+    st = cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
+                                case.extend_lens, case.out, None, case.shape, None, 0, check=False)
+    assert st in (cp.CP_OK, cp.CP_ERR_WORKSPACE)
+    if st == cp.CP_OK:
+        _check(case.out_bits(), want, f"no workspace G={G} Hkv={Hkv} P={P} E={E}")
+
+
+def test_more_requests_than_lanes(H):
+    """70 requests of both kinds: two groups of 64 in every search, equal lengths among the sorted ones."""
+    rng = np.random.default_rng(53)
+    P = [int(x) for x in rng.integers(0, 700, 70)]
+    E = [int(x) for x in np.where(rng.random(70) < 0.7, 1, rng.integers(20, 90, 70))]
+    P[3] = P[66] = 2500
+    P[5:9], E[5:9] = [128] * 4, [64] * 4
+    w = W.make_uniform("mixed70", 53, 70, 8, 2, P, E)
+    _check(H.gpu_attention(w), oracle.attention_of(w), "70 requests")
