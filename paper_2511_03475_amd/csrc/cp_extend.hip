@@ -1246,11 +1246,15 @@ __global__ __launch_bounds__(32 * kMergeHeads) void merge_mixed_kernel(const Mix
     *reinterpret_cast<bf16x4 *>(p.out + ((int64_t)(cu + row) * p.Hq + head) * kD + t * 4) = y;
 }
 
-// One workgroup copies 16 consecutive packed rows.  Its first wavefront finds the request, the
-// page and the slot of every row, 64 requests at a time (a prefix sum of extend_lens across the
-// lanes; a sequential scan costs one dependent load per request, which made a 32-row call take
-// 30 us); then thread (row, 16-byte chunk) copies the row's K and V for every KV head.
-constexpr int kWriteRows = 16;
+// A wavefront copies four consecutive packed rows of two KV heads; thread (row, 16-byte chunk).  It finds
+// the requests of its rows 64 at a time (a prefix sum of extend_lens across the lanes).  For a few rows
+// the time is the chain of dependent loads: lengths, then the block table, then the store.  The rows
+// themselves do not wait for it, they are requested first.  With all heads in one wavefront, two at a
+// time, the chain goes on: 32 rows, 8 KV heads 3.1 us a launch with two heads, 3.4 with four, 3.9 with eight
+// (5.8-6.5 with the rows requested after the table); 8000 rows 10.9, 11.4, 12.0; 18432 rows 23.9, 23.7, 24.2
+// (6.3 TB/s); 32768 rows 43.2, 45.0, 47.6.
+constexpr int kWriteRows = 16; // rows per workgroup
+constexpr int kWriteHeads = 2; // KV heads per workgroup
 __global__ __launch_bounds__(256) void write_kv_kernel(const uint16_t *__restrict__ k_new,
                                                        const uint16_t *__restrict__ v_new,
                                                        uint16_t *__restrict__ kv_pages,
@@ -1259,71 +1263,52 @@ __global__ __launch_bounds__(256) void write_kv_kernel(const uint16_t *__restric
                                                        const int32_t *__restrict__ extend_lens,
                                                        int batch, int Hkv, int max_pages, int T)
 {
-    __shared__ int64_t s_page[kWriteRows]; // physical page of the row's token, -1: no such row
-    __shared__ int s_slot[kWriteRows];     // its slot inside the page
-    const int row0 = blockIdx.x * kWriteRows;
     const int lane = threadIdx.x & 63;
-    if (threadIdx.x < 64) {
-        int req = -1, off = 0; // lane i < 16: owner of row row0 + i and the row's index inside it
-        int cu = 0;            // rows of the requests before `base`
-        for (int base = 0; base < batch; base += 64) {
-            const int rr = base + lane;
-            const int e = rr < batch ? extend_lens[rr] : 0;
-            const int incl = wave_inclusive_scan(e, lane);
-            const int total = __builtin_amdgcn_readlane(incl, 63);
+    const int groups = (Hkv + kWriteHeads - 1) / kWriteHeads; // workgroups that share the rows
+    const int row0 = (int)(blockIdx.x / groups) * kWriteRows + (int)(threadIdx.x >> 6) * 4;
+    const int head0 = (int)(blockIdx.x % groups) * kWriteHeads, head1 = min(head0 + 1, Hkv - 1);
+    if (row0 >= T) return;
+    const int row = row0 + (lane >> 4);
+    const int ch = lane & 15; // 16-byte chunk of a 256-byte head row
+    const int64_t src = (int64_t)min(row, T - 1) * Hkv * kD + ch * 8;
+    // the last of an odd number of heads is copied twice: the same bytes to the same place
+    const uint4 k0 = *reinterpret_cast<const uint4 *>(k_new + src + (int64_t)head0 * kD);
+    const uint4 v0 = *reinterpret_cast<const uint4 *>(v_new + src + (int64_t)head0 * kD);
+    const uint4 k1 = *reinterpret_cast<const uint4 *>(k_new + src + (int64_t)head1 * kD);
+    const uint4 v1 = *reinterpret_cast<const uint4 *>(v_new + src + (int64_t)head1 * kD);
+
+    int req = -1, tok = 0; // owner of this thread's row and the row's token inside it
+    int cu = 0;            // rows of the requests before `base`
+    for (int base = 0; base < batch; base += 64) {
+        const int rr = base + lane;
+        const int e = rr < batch ? extend_lens[rr] : 0;
+        const int pl = rr < batch ? prefix_lens[rr] : 0;
+        const int incl = wave_inclusive_scan(e, lane);
+        const int total = __builtin_amdgcn_readlane(incl, 63);
 #pragma unroll
-            for (int i = 0; i < kWriteRows; ++i) {
-                const int t = row0 + i - cu; // the row's index among the rows of this group of requests
-                if (t >= 0 && t < total) {
-                    const int first = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl > t));
-                    const int before = __builtin_amdgcn_readlane(incl - e, first);
-                    if (lane == i) {
-                        req = base + first;
-                        off = t - before;
-                    }
+        for (int i = 0; i < 4; ++i) {
+            const int t = row0 + i - cu; // the row's index among the rows of this group of requests
+            if (t >= 0 && t < total) {
+                const int first = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl > t));
+                const int at = __builtin_amdgcn_readlane(pl - incl + e, first) + t;
+                if ((lane >> 4) == i) {
+                    req = base + first;
+                    tok = at;
                 }
             }
-            if (row0 + kWriteRows - 1 - cu < total) break;
-            cu += total;
         }
-        if (lane < kWriteRows) {
-            int64_t page = -1;
-            int slot = 0;
-            if (req >= 0 && row0 + lane < T) {
-                const int tok = prefix_lens[req] + off;
-                page = block_table[(int64_t)req * max_pages + (tok >> 4)];
-                slot = tok & 15;
-            }
-            s_page[lane] = page;
-            s_slot[lane] = slot;
-        }
+        if (row0 + 3 - cu < total) break;
+        cu += total;
     }
-    __syncthreads();
-    const int lr = threadIdx.x >> 4; // row of the block
-    const int ch = threadIdx.x & 15; // 16-byte chunk of a 256-byte head row
-    const int64_t page = s_page[lr];
-    if (page < 0) return;
-    const int64_t row = row0 + lr;
-    const uint16_t *ksrc = k_new + row * Hkv * kD + ch * 8;
-    const uint16_t *vsrc = v_new + row * Hkv * kD + ch * 8;
-    uint16_t *kdst = kv_pages + ((page * 2 * Hkv) * kPS + s_slot[lr]) * (int64_t)kD + ch * 8;
+    if (req < 0 || row >= T) return;
+    const int64_t page = block_table[(int64_t)req * max_pages + (tok >> 4)];
+    uint16_t *kdst = kv_pages + ((page * 2 * Hkv) * kPS + (tok & 15)) * (int64_t)kD + ch * 8;
     uint16_t *vdst = kdst + (int64_t)Hkv * kPS * kD;
     const int64_t head_pitch = (int64_t)kPS * kD; // one KV head's slab inside a page
-    int g = 0;
-    for (; g + 2 <= Hkv; g += 2) { // four independent copies in flight
-        const uint4 k0 = *reinterpret_cast<const uint4 *>(ksrc + (int64_t)g * kD);
-        const uint4 k1 = *reinterpret_cast<const uint4 *>(ksrc + (int64_t)(g + 1) * kD);
-        const uint4 v0 = *reinterpret_cast<const uint4 *>(vsrc + (int64_t)g * kD);
-        const uint4 v1 = *reinterpret_cast<const uint4 *>(vsrc + (int64_t)(g + 1) * kD);
-        *reinterpret_cast<uint4 *>(kdst + g * head_pitch) = k0;
-        *reinterpret_cast<uint4 *>(kdst + (g + 1) * head_pitch) = k1;
-        *reinterpret_cast<uint4 *>(vdst + g * head_pitch) = v0;
-        *reinterpret_cast<uint4 *>(vdst + (g + 1) * head_pitch) = v1;
-    }
-    for (; g < Hkv; ++g) {
-        *reinterpret_cast<uint4 *>(kdst + g * head_pitch) = *reinterpret_cast<const uint4 *>(ksrc + (int64_t)g * kD);
-        *reinterpret_cast<uint4 *>(vdst + g * head_pitch) = *reinterpret_cast<const uint4 *>(vsrc + (int64_t)g * kD);
-    }
+    *reinterpret_cast<uint4 *>(kdst + head0 * head_pitch) = k0;
+    *reinterpret_cast<uint4 *>(vdst + head0 * head_pitch) = v0;
+    *reinterpret_cast<uint4 *>(kdst + head1 * head_pitch) = k1;
+    *reinterpret_cast<uint4 *>(vdst + head1 * head_pitch) = v1;
 }
 
 
@@ -1977,8 +1962,9 @@ int cp_write_kv(const void *k_new, const void *v_new, void *kv_pages, const int3
         if (chk != CP_OK) return chk;
     }
     const int T = shape->total_extend;
-    const dim3 grid((unsigned)((T + kWriteRows - 1) / kWriteRows)), block(256);
-    hipLaunchKernelGGL(write_kv_kernel, grid, block, 0, static_cast<hipStream_t>(stream),
+    const int64_t blocks = (int64_t)((T + kWriteRows - 1) / kWriteRows) * ((shape->num_kv_heads + kWriteHeads - 1) / kWriteHeads);
+    if (blocks > INT32_MAX) return CP_ERR_SHAPE;
+    hipLaunchKernelGGL(write_kv_kernel, dim3((unsigned)blocks), dim3(256), 0, static_cast<hipStream_t>(stream),
                        static_cast<const uint16_t *>(k_new), static_cast<const uint16_t *>(v_new),
                        static_cast<uint16_t *>(kv_pages), block_table, prefix_lens, extend_lens,
                        shape->batch, shape->num_kv_heads, shape->max_pages_per_req, T);

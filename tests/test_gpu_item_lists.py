@@ -75,3 +75,16 @@ def test_short_key_ranges(H, P, E):
     cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
                            case.extend_lens, case.out, None, case.shape, None, 0)
     _check(case.out_bits(), want, f"no workspace P={P} E={E}")
+
+
+@pytest.mark.parametrize("Hkv", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("E", [[1], [3, 0, 2], [1] * 70 + [37], [16, 1, 64, 5]])
+def test_cache_append_remainders(H, Hkv, E):
+    """Rows in numbers that no wavefront (4 rows) or workgroup (16) divides, odd numbers of KV heads, owners
+    in the second group of 64 requests: every byte of the pool as the oracle leaves it."""
+    P = [(7 * r) % 45 for r in range(len(E))]
+    w = W.make_uniform("append", 55, len(E), Hkv, Hkv, P, E)
+    case = H.DeviceCase(w)
+    case.write_kv()
+    want = oracle.write_kv(w.k_new, w.v_new, w.kv_pages, w.block_table, w.prefix_lens, w.extend_lens)
+    assert np.array_equal(case.kv_pages.cpu().numpy().view(np.uint16), want.view(np.uint16))
