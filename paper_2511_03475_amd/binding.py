@@ -367,7 +367,7 @@ class ContextIndex:
         buf = (ctypes.c_int32 * self.PATH_CAP)()
         n = ctypes.c_int32(0)
         _check_index(fn(self._h, *args, buf, self.PATH_CAP, ctypes.byref(n)), what)
-        return [int(buf[i]) for i in range(n.value)]
+        return buf[:n.value]
 
     def aligned(self, i: int):
         return self._list(self._lib.cp_index_aligned, "cp_index_aligned", int(i))

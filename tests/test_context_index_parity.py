@@ -178,3 +178,16 @@ def test_schedule_matches_oracle_on_random_paths():
         n = int(rng.integers(0, 40))
         paths = [list(map(int, rng.integers(0, 4, size=int(rng.integers(0, 5))))) for _ in range(n)]
         assert cp.cp_index_schedule(paths) == CI.schedule(paths)
+
+
+def test_many_equal_distances_and_rows_that_move_together():
+    """Few different ids, so that most distances are equal, and enough contexts that the clustering moves the
+    remaining rows together several times; alpha = 0 leaves 1 - shared / length alone."""
+    rng = np.random.default_rng(77)
+    for n, blocks, alpha in ((200, 9, ALPHA), (200, 14, 0.0), (131, 30, ALPHA)):
+        contexts = [[int(x) for x in rng.permutation(blocks)[:rng.integers(1, 7)]] for _ in range(n)]
+        C, L = _pack(contexts)
+        idx, ref = cp.ContextIndex(C, L, alpha), CI.ContextIndex.build(contexts, alpha)
+        _same_tree(idx, ref)
+        _same_contexts(idx, ref, n)
+        idx.close()
