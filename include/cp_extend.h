@@ -79,8 +79,9 @@ typedef struct cp_shape {
 
 /*
  * Bytes of device scratch with which cp_extend_attention takes its best plan for this shape (0 when
- * the keys are not split); see `workspace` below for calls with less.  A pure function of *shape, including the host length arrays.  Returns 0
- * for an invalid shape (cp_extend_attention then reports the error).
+ * the keys are not split); see `workspace` below for calls with less.  A pure function of *shape,
+ * including the host length arrays.  Returns 0 for an invalid shape (cp_extend_attention then reports
+ * the error).
  */
 size_t cp_workspace_bytes(const cp_shape *shape);
 
@@ -122,7 +123,9 @@ int32_t cp_plan_kind(const cp_shape *shape);
  *
  * workspace: DEVICE scratch of cp_workspace_bytes(shape) bytes, 256-byte aligned; may be NULL when
  * that size is 0.  With less, a call that is not decode-shaped and leaves num_splits at 0 takes a plan
- * that fits (not bit for bit the same result), any other call is refused.  Its contents are undefined afterwards.
+ * that fits (not bit for bit the same result), down to the partial results of key ranges of 8 tiles
+ * of 64 keys for two workgroups per compute unit; below that, and any other call, is refused.  Its
+ * contents are undefined afterwards.
  * Requests with E_r = 0 produce no rows.  Asynchronous on `stream`.
  */
 int cp_extend_attention(const void *q, const void *k_new, const void *v_new,

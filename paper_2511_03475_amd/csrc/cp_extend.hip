@@ -1548,6 +1548,18 @@ bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order)
     return best_us >= 0.0;
 }
 
+// Row-tiled work of a call: work units per KV head, key tiles of the longest request.
+void row_tiled_extent(const cp_shape *s, int64_t &q_tiles, int32_t &max_key_tiles)
+{
+    const int G = s->num_q_heads / s->num_kv_heads;
+    for (int r = 0; r < s->batch; ++r) {
+        const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
+        if (E == 0) continue;
+        q_tiles += units_of_request((int)E, G, heads_per_tile((int)E, G));
+        max_key_tiles = std::max(max_key_tiles, (int32_t)((P + kBN - 1) / kBN + (E + kBN - 1) / kBN));
+    }
+}
+
 // Key ranges for row-tiled requests of equal lengths: the least estimated time (see above).  A grid
 // of two workgroups per CU is not split: it gains nothing then.  Row tiles of one length run in whole
 // rounds over the CUs; if a request has several, of different lengths, the last round is about half empty.
@@ -1619,14 +1631,7 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
         return pl;
     }
     if (s->num_splits == 0 && s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, room, pl, order)) return pl;
-    for (int r = 0; r < s->batch; ++r) {
-        const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
-        if (E == 0) continue;
-        const int pack = heads_per_tile((int)E, s->num_q_heads / s->num_kv_heads);
-        pl.q_tiles += units_of_request((int)E, s->num_q_heads / s->num_kv_heads, pack);
-        const int64_t kt = (P + kBN - 1) / kBN + (E + kBN - 1) / kBN;
-        if (kt > pl.max_key_tiles) pl.max_key_tiles = (int32_t)kt;
-    }
+    row_tiled_extent(s, pl.q_tiles, pl.max_key_tiles);
     if (s->num_splits >= 1) {
         pl.nsplit = s->num_splits;
     } else {
@@ -1659,6 +1664,24 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
     return part_bytes((size_t)pl.nsplit * (size_t)s->total_extend, s->num_q_heads);
 }
 
+
+// Whether a call with `room` bytes of scratch and the plan pl made for them is refused: the plan needs more, or
+// the call is not decode-shaped, brings less than its best plan wants and also less than key ranges of
+// at least 8 tiles, for two workgroups per CU, take.  Plans without partial results exist for it, but
+// would run several times slower than the call can, without a word.
+bool too_little_scratch(const cp_shape *s, const Plan &pl, size_t room)
+{
+    if (workspace_for(s, pl) > room) return true;
+    if (pl.decode || s->num_splits >= 1) return false;
+    int64_t q_tiles = 0;
+    int32_t max_key_tiles = 0;
+    row_tiled_extent(s, q_tiles, max_key_tiles);
+    const int64_t items = q_tiles * s->num_kv_heads, want = 2LL * num_cus();
+    int64_t ns = items > 0 && items < want ? (want + items - 1) / items : 1;
+    ns = std::min<int64_t>({ns, max_key_tiles / 8, kMaxSplits});
+    if (ns <= 1 || part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) <= room) return false;
+    return workspace_for(s, make_plan(s)) > room;
+}
 
 inline bool aligned_to(const void *p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
 
@@ -1841,12 +1864,10 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
         if (chk != CP_OK) return chk;
     }
     MixedParams p;
-    const Plan pl = make_plan(shape, workspace && aligned_to(workspace, 256) ? workspace_bytes : 0, p.order);
+    const size_t room = workspace && aligned_to(workspace, 256) ? workspace_bytes : 0;
+    const Plan pl = make_plan(shape, room, p.order);
     const size_t need = workspace_for(shape, pl);
-    if (need > 0) {
-        if (!workspace || workspace_bytes < need) return CP_ERR_WORKSPACE;
-        if (!aligned_to(workspace, 256)) return CP_ERR_WORKSPACE;
-    }
+    if (too_little_scratch(shape, pl, room)) return CP_ERR_WORKSPACE;
     const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves : pl.q_tiles * pl.nsplit;
     const int64_t total = per_head * shape->num_kv_heads;
     if (total > INT32_MAX / 2) return CP_ERR_SHAPE;
@@ -1937,7 +1958,7 @@ int cp_extend_attention_noalloc(const void *q, const void *k_new, const void *v_
     const int st = validate(shape);
     if (st != CP_OK) return st;
     // sizes beyond the library's own array are refused here, before anything is looked up or launched
-    if (workspace_for(shape, make_plan(shape, CP_NOALLOC_SCRATCH_BYTES)) > CP_NOALLOC_SCRATCH_BYTES) return CP_ERR_WORKSPACE;
+    if (too_little_scratch(shape, make_plan(shape, CP_NOALLOC_SCRATCH_BYTES), CP_NOALLOC_SCRATCH_BYTES)) return CP_ERR_WORKSPACE;
     void *ptr = scratch_address(); // the array's address on the current device, never the array's name
     if (!ptr) return CP_ERR_LAUNCH;
     return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, shape, ptr,

@@ -62,19 +62,23 @@ def test_more_requests_than_lanes(H):
     _check(H.gpu_attention(w), oracle.attention_of(w), "70 requests")
 
 
-@pytest.mark.parametrize("P,E", [([512], [128]), ([0], [300]), ([130], [65]), ([900, 900], [33, 33]), ([64], [64])])
+@pytest.mark.parametrize("P,E", [([512], [128]), ([0], [300]), ([130], [65]), ([900, 900], [33, 33]), ([64], [64]),
+                                 ([3000], [128]), ([3000, 100], [100, 128])])
 def test_short_key_ranges(H, P, E):
-    """Few row tiles, so that the library splits the keys into ranges of two tiles; then without room for
-    partial results, where it has to do without."""
+    """Few row tiles: key ranges of a few tiles; then without room for partial
+    results, where a short call does without and a longer one is refused."""
     import paper_2511_03475_amd as cp
 
     w = W.make_uniform("ranges", 54, len(P), 8, 2, P, E)
     want = oracle.attention_of(w)
     case = H.DeviceCase(w)
     _check(H.gpu_attention(w), want, f"P={P} E={E}")
-    cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
-                           case.extend_lens, case.out, None, case.shape, None, 0)
-    _check(case.out_bits(), want, f"no workspace P={P} E={E}")
+    st = cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
+                                case.extend_lens, case.out, None, case.shape, None, 0, check=False)
+    # 16 key tiles make two ranges of 8, 49 six: too long to go without scratch
+    assert st == (cp.CP_ERR_WORKSPACE if P[0] >= 900 else cp.CP_OK)
+    if st == cp.CP_OK:
+        _check(case.out_bits(), want, f"no workspace P={P} E={E}")
 
 
 @pytest.mark.parametrize("Hkv", [1, 2, 3, 5, 8])
