@@ -217,17 +217,20 @@ __device__ __forceinline__ Owner find_owner(int at, const MixedParams &p, int la
 // ---- decode-shaped calls ------------------------------------------------------------------
 // When every request brings so few new tokens that all its rows for one KV head (G heads x E_r
 // tokens) fit a few 32-column MFMA tiles, the call is bound by reading the cached K/V once,
-// and the row-tiled kernel above wastes its wavefronts (most hold no valid row) and keeps too
-// little in flight.  This kernel turns the work around: a wavefront is the unit, owns 32 rows
-// of one (request, KV head) and a contiguous chunk of the keys, and runs alone - no barrier, no
-// shared tile.  Per block of 32 keys it loads the K and V rows with fully coalesced 16-byte
-// loads (one instruction = four whole rows), stages them in registers while the previous block
-// is computed, and passes them through a private LDS area from which the MFMA operands are read
-// (K rows as they are, V rows transposed).  Every wavefront writes an unnormalised partial
-// (m, l, O) and merge_splits_kernel combines them, exactly as for split-K.  Prefix and suffix
-// keys form one sequence of N = P + E keys; blocks inside the prefix take their two pages from
-// the block table with scalar loads, the last blocks resolve every row on its own.
-constexpr int kDecWaves = 4;            // wavefronts per workgroup (independent of each other)
+// and the row-tiled kernel below wastes its wavefronts (most hold no valid row) and keeps too
+// little in flight.  This kernel turns the work around: a wavefront is the unit, owns the one or two
+// blocks of 32 rows of one (request, KV head) and a share of its keys, in blocks of 32, and runs alone - no
+// barrier, no shared tile.  It loads the K and V rows of a block with fully coalesced 16-byte loads
+// (one instruction = four whole rows), stages them in registers while the previous block is
+// computed, and passes them through a private LDS area from which the MFMA operands are read (K rows
+// as they are, V rows transposed).  Prefix and suffix keys form one sequence of N = P + E keys;
+// blocks inside the prefix take their two pages from the block table with scalar loads, the last
+// blocks resolve every row on its own.  The results of a workgroup's wavefronts (m, l, O) are added up
+// through LDS; a merge launch is left only where several workgroups share the keys of a request.
+// Bound by reading the cache.  32 requests of 10240 tokens, 32/8 heads, with the merge: 217 -> 212 us for 1 new
+// token (6.3 TB/s), 254 -> 222 for 16 (two blocks of rows, each of which read the keys for itself before;
+// a pair of wavefronts that shares its keys behind barriers took 281); 64 of 100 tokens 11.6 -> 7.0; 20 of
+// 9000, 64/8 heads 141 -> 118.
 // LDS bytes per K row / V row: 256 + padding.  16 consecutive K rows at the same column fall into
 // 16 different 16-byte bank groups, the four consecutive V rows of a transposing read into four
 // different 64-byte bank groups, and every read address is a per-lane base plus an immediate.
@@ -235,6 +238,7 @@ constexpr int kDecPitchK = 272;
 constexpr int kDecPitchV = 320;
 constexpr int kDecLdsK = 32 * kDecPitchK;
 constexpr int kDecLdsPerWave = kDecLdsK + 32 * kDecPitchV;
+constexpr int kDecLeastWaves = 4;       // a call is planned in key chunks of wavefronts, a multiple of the smallest workgroup
 constexpr int kDecMaxChunks = 256;      // key chunks (= partial results) per (request, KV head)
 
 struct DecBlock { // one block of 32 keys as loaded: piece i is row (lane / 16) + 4 i, chunk lane % 16
@@ -242,40 +246,38 @@ struct DecBlock { // one block of 32 keys as loaded: piece i is row (lane / 16) 
     u32x4 v[8];
 };
 
-// One wavefront: row block rb of (request r, KV head kvh) against the key blocks b0 .. b1 - 1.  The
-// partial result of token e goes to row part_row + e of the partial results; part_row < 0 says that
-// these are all the keys and writes the finished rows instead.
-__device__ __forceinline__ void decode_chunk(const AttnParams &p, char *lds_k, int lane, int r, int kvh, int P, int E,
-                                             int cu, int rb, int b0, int b1, int64_t part_row)
+// What a wavefront has after its keys for a block of 32 rows: unnormalised, reference m (log2 domain), sum l
+// over this half-wave's keys; o[db][v] is O^T[d = db*32 + 8*(v/4) + 4*h + v%4][row j].
+struct DecResult {
+    f32x16 o[4];
+    float m, l;
+};
+
+// One wavefront: kRowBlocks blocks of 32 rows, from rb on, of (request r, KV head kvh) against the key blocks
+// b, b + step, ... below b1.
+template <int kRowBlocks>
+__device__ __forceinline__ void decode_keys(const AttnParams &p, char *lds_k, int lane, int r, int kvh, int P, int E,
+                                            int cu, int rb, int b, int b1, int step, DecResult (&res)[kRowBlocks])
 {
     char *const lds_v = lds_k + kDecLdsK;
     const int j = lane & 31; // (head, token) row of the accumulators; key row of the K operand
     const int h = lane >> 5;
-    // row 32 rb + j of the (request, KV head) is token e of head hg of the group; rows beyond
-    // G E are padding
-    if (rb * kDecRows >= p.G * E) return;
-    const int row = rb * kDecRows + j;
-    const bool row_valid = row < p.G * E;
-    const int hg = row_valid ? row / E : 0;
-    const int e = row_valid ? row - hg * E : 0;
-    const int head = kvh * p.G + hg;
-    const int64_t out_row = cu + e;
     const int N = P + E;
-    const int64_t prow = (part_row + e) * p.Hq + head;
-    if (b0 >= b1) { // nothing to do for this chunk: the merge skips entries whose sum is zero
-        if (row_valid && h == 0) {
-            p.part_ml[prow * 2] = -INFINITY;
-            p.part_ml[prow * 2 + 1] = 0.f;
-        }
-        return;
-    }
 
-    // Q fragments, B operand of S^T = K Q^T: lane (row j, h) holds q[row][16 kk + 8 h .. + 8)
-    u32x4 qf[8];
-    {
-        const uint16_t *qp = p.q + (out_row * p.Hq + head) * kD + 8 * h;
+    // Q fragments, B operand of S^T = K Q^T: lane (row j, h) holds q[row][16 kk + 8 h .. + 8).
+    // Row 32 rb + j of the (request, KV head) is token e of head hg of the group; rows beyond
+    // G E are padding.
+    u32x4 qf[kRowBlocks][8];
+    int e_row[kRowBlocks];
 #pragma unroll
-        for (int kk = 0; kk < 8; ++kk) qf[kk] = *(const __attribute__((address_space(1))) u32x4 *)(qp + 16 * kk);
+    for (int q = 0; q < kRowBlocks; ++q) {
+        const int row = (rb + q) * kDecRows + j;
+        const int hg = row < p.G * E ? row / E : 0;
+        const int e = row < p.G * E ? row - hg * E : 0;
+        e_row[q] = e;
+        const uint16_t *qp = p.q + ((int64_t)(cu + e) * p.Hq + kvh * p.G + hg) * kD + 8 * h;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk) qf[q][kk] = *(const __attribute__((address_space(1))) u32x4 *)(qp + 16 * kk);
     }
 
     // loads: lane covers rows ld_sub + 4 i (i = 0..7) of the block, 16-byte chunk ld_chunk
@@ -328,65 +330,79 @@ __device__ __forceinline__ void decode_chunk(const AttnParams &p, char *lds_k, i
     const int k_lane = j * kDecPitchK + h * 16;
     const int v_lane = (4 * h + ((lane & 15) >> 2)) * kDecPitchV + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
 
-    f32x16 o[4];
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
+    for (int q = 0; q < kRowBlocks; ++q) {
 #pragma unroll
-        for (int v = 0; v < 16; ++v) o[db][v] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f; // log2 domain; sum over this half-wave's keys
+        for (int db = 0; db < 4; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) res[q].o[db][v] = 0.f;
+        res[q].m = -INFINITY;
+        res[q].l = 0.f;
+    }
     const float c = p.scale_log2;
     const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
 
-    DecBlock blk;
-    load_block(b0, blk);
-    for (int b = b0; b < b1; ++b) {
-        // block b: registers -> private LDS (one wavefront's LDS operations are served in order,
-        // so these writes come after the reads of block b - 1), then block b + 1 into flight
-        store_block(blk);
-        if (b + 1 < b1) load_block(b + 1, blk);
-        f32x16 s;
+    // all rows against key block b, which is staged in LDS; the row blocks are chains of their own, so one
+    // computes while the other waits for its result
+    auto compute_block = [&](int b) {
+        f32x16 s[kRowBlocks];
+        u32x4 pb[kRowBlocks][2];
+        float alpha[kRowBlocks];
 #pragma unroll
-        for (int v = 0; v < 16; ++v) s[v] = 0.f;
+        for (int q = 0; q < kRowBlocks; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) s[q][v] = 0.f;
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
             const u32x4 a = *reinterpret_cast<const u32x4 *>(lds_k + k_lane + kk * 32);
-            s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                         __builtin_bit_cast(bf16x8, qf[kk]), s, 0, 0, 0);
+#pragma unroll
+            for (int q = 0; q < kRowBlocks; ++q)
+                s[q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
+                                                                __builtin_bit_cast(bf16x8, qf[q][kk]), s[q], 0, 0, 0);
         }
         // accumulator element v is key 32 b + 8 (v / 4) + 4 h + v % 4; row j sees keys <= P + e
         if (b * 32 + 31 > P) {
-            const int vis = P + e - b * 32 - 4 * h; // visible: 8 (v / 4) + v % 4 <= vis
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                if (8 * (v >> 2) + (v & 3) > vis) s[v] = -INFINITY;
-        }
-        float mx = s[0];
+            for (int q = 0; q < kRowBlocks; ++q) {
+                const int vis = P + e_row[q] - b * 32 - 4 * h; // visible: 8 (v / 4) + v % 4 <= vis
 #pragma unroll
-        for (int v = 1; v + 1 < 16; v += 2) mx = fmaxf(fmaxf(mx, s[v]), s[v + 1]);
-        mx = halfwave_max(fmaxf(mx, s[15]));
-        const float m_new = fmaxf(m_run, mx * c);
-        const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
-        const float alpha = fast_exp2(m_run - m_use);
-        u32x4 pb[2];
-        float psum = 0.f;
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                f32x2 x;
-                x[0] = fast_exp2(fmaf(s[8 * u + 2 * w], c, -m_use));
-                x[1] = fast_exp2(fmaf(s[8 * u + 2 * w + 1], c, -m_use));
-                const bf16x2 y = __builtin_convertvector(x, bf16x2);
-                psum = __builtin_amdgcn_fdot2_f32_bf16(y, ones, psum, false);
-                pb[u][w] = __builtin_bit_cast(unsigned, y);
+                for (int v = 0; v < 16; ++v)
+                    if (8 * (v >> 2) + (v & 3) > vis) s[q][v] = -INFINITY;
             }
-        l_run = l_run * alpha + psum;
-        m_run = m_new;
-        if (__builtin_amdgcn_ballot_w64(alpha != 1.f) != 0) {
+        }
+        bool moved = false;
 #pragma unroll
-            for (int db = 0; db < 4; ++db)
+        for (int q = 0; q < kRowBlocks; ++q) {
+            float mx = s[q][0];
 #pragma unroll
-                for (int v = 0; v < 16; ++v) o[db][v] *= alpha;
+            for (int v = 1; v + 1 < 16; v += 2) mx = fmaxf(fmaxf(mx, s[q][v]), s[q][v + 1]);
+            mx = halfwave_max(fmaxf(mx, s[q][15]));
+            const float m_new = fmaxf(res[q].m, mx * c);
+            const float m_use = (m_new == -INFINITY) ? 0.f : m_new;
+            alpha[q] = fast_exp2(res[q].m - m_use);
+            float psum = 0.f;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    f32x2 x;
+                    x[0] = fast_exp2(fmaf(s[q][8 * u + 2 * w], c, -m_use));
+                    x[1] = fast_exp2(fmaf(s[q][8 * u + 2 * w + 1], c, -m_use));
+                    const bf16x2 y = __builtin_convertvector(x, bf16x2);
+                    psum = __builtin_amdgcn_fdot2_f32_bf16(y, ones, psum, false);
+                    pb[q][u][w] = __builtin_bit_cast(unsigned, y);
+                }
+            res[q].l = res[q].l * alpha[q] + psum;
+            res[q].m = m_new;
+            moved |= alpha[q] != 1.f;
+        }
+        if (__builtin_amdgcn_ballot_w64(moved) != 0) {
+#pragma unroll
+            for (int q = 0; q < kRowBlocks; ++q)
+#pragma unroll
+                for (int db = 0; db < 4; ++db)
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) res[q].o[db][v] *= alpha[q];
         }
         // O^T += V^T P^T: 2 steps of 16 keys x 4 blocks of 32 d
 #pragma unroll
@@ -399,13 +415,30 @@ __device__ __forceinline__ void decode_chunk(const AttnParams &p, char *lds_k, i
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                     (__attribute__((address_space(3))) s16x4 *)(a + 8 * kDecPitchV));
                 const s16x8 vv = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-                o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv),
-                                                                 __builtin_bit_cast(bf16x8, pb[ks]), o[db], 0, 0, 0);
+#pragma unroll
+                for (int q = 0; q < kRowBlocks; ++q)
+                    res[q].o[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, vv),
+                                                                            __builtin_bit_cast(bf16x8, pb[q][ks]), res[q].o[db], 0, 0, 0);
             }
-    }
+    };
 
-    // partial result of this chunk; o[db][v] is O^T[d = db*32 + 8*(v/4) + 4*h + v%4][row j]
-    const float l_tot = halfwave_sum(l_run);
+    DecBlock blk;
+    if (b < b1) load_block(b, blk);
+    for (; b < b1; b += step) {
+        // block b: registers -> private LDS (one wavefront's LDS operations are served in order,
+        // so these writes come after the reads of the block before), then the next one into flight
+        store_block(blk);
+        if (b + step < b1) load_block(b + step, blk);
+        compute_block(b);
+    }
+}
+
+// Writes row `row` (token e of a head, -1: padding) of a finished wavefront: out, or its partial result.
+__device__ __forceinline__ void store_decode_row(const AttnParams &p, const DecResult &res, int lane, int64_t out_row, int64_t part_row,
+                                                 int head, bool row_valid)
+{
+    const int h = lane >> 5;
+    const float l_tot = halfwave_sum(res.l);
     if (!row_valid) return;
     if (part_row < 0) {
         const float inv = 1.f / l_tot;
@@ -416,43 +449,76 @@ __device__ __forceinline__ void decode_chunk(const AttnParams &p, char *lds_k, i
             for (int gq = 0; gq < 4; ++gq) {
                 bf16x4 x;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) x[i] = (__bf16)(o[db][4 * gq + i] * inv);
+                for (int i = 0; i < 4; ++i) x[i] = (__bf16)(res.o[db][4 * gq + i] * inv);
                 *reinterpret_cast<bf16x4 *>(po + db * 32 + 8 * gq + 4 * h) = x;
             }
         return;
     }
+    const int64_t prow = part_row * p.Hq + head;
     float *po = p.part_o + prow * kD;
 #pragma unroll
     for (int db = 0; db < 4; ++db)
 #pragma unroll
         for (int gq = 0; gq < 4; ++gq) {
-            f32x4 x = {o[db][4 * gq], o[db][4 * gq + 1], o[db][4 * gq + 2], o[db][4 * gq + 3]};
+            f32x4 x = {res.o[db][4 * gq], res.o[db][4 * gq + 1], res.o[db][4 * gq + 2], res.o[db][4 * gq + 3]};
             *reinterpret_cast<f32x4 *>(po + db * 32 + 8 * gq + 4 * h) = x;
         }
     if (h == 0) {
-        p.part_ml[prow * 2] = m_run;
+        p.part_ml[prow * 2] = res.m;
         p.part_ml[prow * 2 + 1] = l_tot;
     }
 }
 
-__global__ __launch_bounds__(kDecWaves * 64, 2) void decode_attn_kernel(const AttnParams p)
+// One wavefront on its own: row block rb against the key blocks b0 .. b1 - 1.  The partial result of token
+// e goes to row part_row + e of the partial results; part_row < 0 says that these are all the keys and
+// writes the finished rows instead.
+__device__ __forceinline__ void decode_chunk(const AttnParams &p, char *lds_k, int lane, int r, int kvh, int P, int E,
+                                             int cu, int rb, int b0, int b1, int64_t part_row)
+{
+    const int row = rb * kDecRows + (lane & 31);
+    const bool row_valid = row < p.G * E;
+    const int hg = row_valid ? row / E : 0;
+    const int e = row_valid ? row - hg * E : 0;
+    const int head = kvh * p.G + hg;
+    if (rb * kDecRows >= p.G * E) return;
+    if (b0 >= b1) { // nothing to do for this chunk: the merge skips entries whose sum is zero
+        if (row_valid && lane < 32) {
+            const int64_t prow = (part_row + e) * p.Hq + head;
+            p.part_ml[prow * 2] = -INFINITY;
+            p.part_ml[prow * 2 + 1] = 0.f;
+        }
+        return;
+    }
+    DecResult res[1];
+    decode_keys<1>(p, lds_k, lane, r, kvh, P, E, cu, rb, b0, b1, 1, res);
+    store_decode_row(p, res[0], lane, cu + e, part_row < 0 ? -1 : part_row + e, head, row_valid);
+}
+
+// A workgroup takes kRowBlocks blocks of 32 rows of one (request, KV head) and one of the nsplit chunks of
+// its keys; its wavefronts take the chunk's key blocks in turn.  With two row blocks a wavefront
+// needs twice the registers and a CU holds four of them instead of eight: enough, four read 61 GB/s with one
+// row block and 35 with two, and the memory gives every CU 25.
+constexpr int kDecPitchO = kD + 4; // floats between rows of O in LDS: rows in different banks
+static_assert((32 * kDecPitchO + 64) * 4 <= kDecLdsPerWave, "a wavefront's result fits where its keys were");
+template <int kDecWaves, int kRowBlocks>
+__global__ __launch_bounds__(kDecWaves * 64, kRowBlocks == 1 ? 2 : 1) void decode_attn_kernel(const AttnParams p)
 {
     __shared__ __attribute__((aligned(16))) char lds[kDecWaves * kDecLdsPerWave];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
 
-    // work unit: row block fastest (neighbouring wavefronts then read the same keys), then key
-    // chunk, KV head, request
-    const int64_t unit = (int64_t)blockIdx.x * kDecWaves + wave;
-    const int rb = (int)(unit % p.dec_row_blocks);
-    const int64_t uc = unit / p.dec_row_blocks;
-    const int chunk = (int)(uc % p.nsplit);
-    const int64_t rk = uc / p.nsplit;
-    const int kvh = (int)(rk % p.Hkv);
-    const int r = (int)(rk / p.Hkv);
+    // work unit: row blocks fastest (neighbours then read the same keys), then key chunk, KV head, request
+    const int row_groups = (p.dec_row_blocks + kRowBlocks - 1) / kRowBlocks;
+    const int rg = blockIdx.x % row_groups;
+    const int uc = blockIdx.x / row_groups;
+    const int chunk = uc % p.nsplit;
+    const int rk = uc / p.nsplit;
+    const int kvh = rk % p.Hkv;
+    const int r = rk / p.Hkv;
     if (r >= p.batch) return;
     const int E = p.extend_lens[r];
-    if (E <= 0) return;
+    const int rows = min(p.G * E - rg * kRowBlocks * kDecRows, kRowBlocks * kDecRows); // of this workgroup
+    if (rows <= 0) return;
     const int P = p.prefix_lens[r];
     // packed row of the request's first token: sum of the earlier extend lengths, 64 per step
     int cu = 0;
@@ -460,11 +526,74 @@ __global__ __launch_bounds__(kDecWaves * 64, 2) void decode_attn_kernel(const At
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) cu += __shfl_xor(cu, off, 64);
     cu = __builtin_amdgcn_readfirstlane(cu);
-    const int nblk = (P + E + 31) >> 5;
+    // no row of a block sees keys behind its last token
+    const int end_e = kRowBlocks > 1 ? E : min(rg * kDecRows % E + kDecRows, E);
+    const int nblk = (P + end_e + 31) >> 5;
     const int per = (nblk + p.nsplit - 1) / p.nsplit;
     const int b0 = chunk * per;
     const int b1 = min(nblk, b0 + per);
-    decode_chunk(p, lds + wave * kDecLdsPerWave, lane, r, kvh, P, E, cu, rb, b0, b1, (int64_t)chunk * p.T + cu);
+
+    DecResult res[kRowBlocks];
+    decode_keys<kRowBlocks>(p, lds + wave * kDecLdsPerWave, lane, r, kvh, P, E, cu, rg * kRowBlocks, b0 + wave, b1,
+                            kDecWaves, res);
+
+    // ---- the wavefronts' results through LDS, a block of rows at a time
+    const int d4 = (threadIdx.x & 31) * 4;
+#pragma unroll
+    for (int q = 0; q < kRowBlocks; ++q) {
+        if (q * kDecRows >= rows) return;
+        const float l_tot = halfwave_sum(res[q].l);
+        if (q > 0) __syncthreads(); // the block before has been read
+        {
+            float *const mine = reinterpret_cast<float *>(lds + wave * kDecLdsPerWave);
+            const int j = lane & 31, h = lane >> 5;
+#pragma unroll
+            for (int db = 0; db < 4; ++db)
+#pragma unroll
+                for (int gq = 0; gq < 4; ++gq) {
+                    const f32x4 x = {res[q].o[db][4 * gq], res[q].o[db][4 * gq + 1], res[q].o[db][4 * gq + 2], res[q].o[db][4 * gq + 3]};
+                    *reinterpret_cast<f32x4 *>(mine + j * kDecPitchO + db * 32 + 8 * gq + 4 * h) = x;
+                }
+            if (h == 0) *reinterpret_cast<f32x2 *>(mine + 32 * kDecPitchO + 2 * j) = f32x2{res[q].m, l_tot};
+        }
+        __syncthreads();
+        for (int i = threadIdx.x >> 5; i < min(kDecRows, rows - q * kDecRows); i += kDecWaves * 2) {
+            f32x2 ml[kDecWaves];
+            f32x4 x[kDecWaves];
+#pragma unroll
+            for (int w = 0; w < kDecWaves; ++w) {
+                const float *const part = reinterpret_cast<const float *>(lds + w * kDecLdsPerWave);
+                ml[w] = *reinterpret_cast<const f32x2 *>(part + 32 * kDecPitchO + 2 * i);
+                x[w] = *reinterpret_cast<const f32x4 *>(part + i * kDecPitchO + d4);
+            }
+            float m_star = -INFINITY;
+#pragma unroll
+            for (int w = 0; w < kDecWaves; ++w)
+                if (ml[w][1] != 0.f) m_star = fmaxf(m_star, ml[w][0]);
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            float denom = 0.f;
+#pragma unroll
+            for (int w = 0; w < kDecWaves; ++w)
+                if (ml[w][1] != 0.f) { // 0: no keys, or none that the row sees; NaN goes through
+                    const float f = fast_exp2(ml[w][0] - m_star);
+                    acc += x[w] * f;
+                    denom += ml[w][1] * f;
+                }
+            const int row = (rg * kRowBlocks + q) * kDecRows + i, hg = row / E, e = row - hg * E;
+            const int head = kvh * p.G + hg;
+            if (p.nsplit == 1) {
+                const float inv = 1.f / denom; // every row sees its own key
+                bf16x4 y;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) y[k] = (__bf16)(acc[k] * inv);
+                *reinterpret_cast<bf16x4 *>(p.out + ((int64_t)(cu + e) * p.Hq + head) * kD + d4) = y;
+            } else {
+                const int64_t prow = ((int64_t)chunk * p.T + cu + e) * p.Hq + head;
+                *reinterpret_cast<f32x4 *>(p.part_o + prow * kD + d4) = acc;
+                if (d4 == 0) *reinterpret_cast<f32x2 *>(p.part_ml + prow * 2) = f32x2{m_star, denom};
+            }
+        }
+    }
 }
 
 // LDS: four K buffers and five V buffers of one 64-key tile (16 KiB) each, K of tile t in buffer
@@ -1359,6 +1488,8 @@ struct Plan {
     int32_t nsplit;
     bool decode;       // few rows per (request, KV head): decode_attn_kernel
     int32_t row_blocks; // ... in this many blocks of 32 rows
+    int32_t dec_groups = 1; // ... by this many workgroups that share a request's keys
+    bool small = false; // few rows and keys: decode_attn_kernel with a workgroup per block of 32 rows
     bool mixed = false; // unequal lengths: extend_attn_kernel<kMixed>, with
     int32_t seg_tiles = 1, dec_blocks = 1;       // at most so many keys per item
     int64_t row_items = 0, dec_units = 0;        // row-tiled items and decode wavefronts per KV head
@@ -1566,8 +1697,9 @@ void row_tiled_extent(const cp_shape *s, int64_t &q_tiles, int32_t &max_key_tile
 // Against ranges of at least 8 tiles, two workgroups per CU: P = 512, E = 128, 8/2 heads (4 workgroups
 // of 10 tiles before) 25.2 -> 19.0 us; 4 requests, P = 3000, E = 128, 32/8 heads 61 -> 45; 1 request,
 // P = 2000, E = 700, 64/8 heads 100 -> 72; 12 requests, P = 20000, E = 128, 32/8 heads 538 -> 496.
-int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room)
+int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *estimate)
 {
+    *estimate = 0.0;
     const int64_t items = pl.q_tiles * s->num_kv_heads, cus = num_cus();
     if (items >= 2 * cus) return 1;
     const int G = s->num_q_heads / s->num_kv_heads;
@@ -1596,9 +1728,71 @@ int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room)
         if (ns == 1 || us < best_us) {
             best_us = ns == 1 ? 0.85 * us : us; // a split has to promise more than the estimate is off by
             best = ns;
+            *estimate = us;
         }
     }
     return best;
+}
+
+// Workgroups per (request, KV head) of a decode-shaped call: the least estimated time, returned in *estimate.  A
+// workgroup of four wavefronts reads up to kDecGroupBytesPerUs until all together reach kDecBytesPerUs,
+// and takes kDecStartUs to start and to end.  So some 160 workgroups read as fast as 2000 (1 request of
+// 131072 tokens, 8 KV heads: 16 per head 98 us, 24 88, 32 91, 64 93; 20 of 9000: 1 per head 117, 3 124, 4 126),
+// and every one more is a partial result to merge.  Of those with one block of rows a CU holds two; CUs
+// with one less than others cost bandwidth (45 of 7000: 1 per head, 360, 217 us; 2 205; 3 220; 4 210).
+// Of those with two blocks it holds one, and the next round begins when it ends (3 of 20000, 10
+// new tokens: 8 per head, 192, 55 us; 12, 288, 81; 20, 480, 61).
+constexpr double kDecGroupBytesPerUs = 4.0e4, kDecGroup2BytesPerUs = 3.3e4, kDecBytesPerUs = 6.5e6;
+constexpr double kDecStartUs = 4.0, kDecMergeUs = 5.0, kDecMergeManyUs = 1.5;
+int32_t choose_decode_groups(const cp_shape *s, int64_t max_n, const Plan &pl, double *estimate)
+{
+    const double units = (double)s->batch * s->num_kv_heads, cus = num_cus();
+    const double blocks = (double)((max_n + 31) / 32);
+    double best_us = 0.0;
+    int32_t best = 1;
+    for (int groups = 1; groups <= pl.nsplit && 4 * (groups - 1) < blocks; ++groups) {
+        const double launched = units * groups, rounds = std::ceil(launched / cus), fill = launched / (cus * rounds);
+        const double bytes = std::ceil(std::ceil(blocks / groups) / 4.0) * 4.0 * 16384.0; // of one workgroup
+        double us;
+        if (pl.row_blocks > 1) {
+            us = rounds * (kDecStartUs + std::max(bytes / kDecGroup2BytesPerUs, std::min(launched, cus) * bytes / kDecBytesPerUs));
+        } else {
+            us = kDecStartUs * std::max(1.0, 0.5 * launched / cus) +
+                 std::max(bytes / kDecGroupBytesPerUs, launched * bytes / kDecBytesPerUs * (rounds > 1.0 ? 1.3 - 0.3 * fill : 1.0));
+        }
+        if (groups > 1) us += kDecMergeUs + 2.0 * (double)part_bytes((size_t)groups * (size_t)s->total_extend, s->num_q_heads) / kPartBytesPerUs;
+        if (groups > kMergeFewSplits) us += kDecMergeManyUs;
+        if (groups == 1 || us < best_us) {
+            best_us = us;
+            best = groups;
+        }
+    }
+    *estimate = best_us;
+    return best;
+}
+
+// A call of few rows and few keys, none of it enough for the device: the decode kernel with a workgroup per 32
+// rows, whose eight wavefronts share the keys and need no merge launch.  One round over the CUs only,
+// because every workgroup reads all keys itself.  `us`: the estimate of the way it would go otherwise.
+// Against row tiles in key ranges and a merge: P = 512, E = 128, 8/2 heads 15.7 -> 11.0 us; P = 200, E = 128,
+// 32/8 heads 18.1 -> 9.5; 2 requests, P = 700, E = 60 21.6 -> 17.0; P = 3000, E = 128, 8/2 heads would take 27.4
+// instead of 25.9.  Four wavefronts instead of eight: 11.7, 9.7, 15.9 and 32.3.
+constexpr double kSmallStartUs = 5.0, kSmallBlockUs = 1.5; // a workgroup; a block of 32 keys per wavefront
+bool small_call(const cp_shape *s, int64_t max_n, double us, Plan &pl)
+{
+    const int G = s->num_q_heads / s->num_kv_heads;
+    int64_t blocks = 0; // of rows, the most of a request
+    for (int r = 0; r < s->batch; ++r) {
+        const int64_t rows = (int64_t)s->h_extend_lens[r] * G;
+        blocks = std::max(blocks, (rows + kDecRows - 1) / kDecRows);
+    }
+    if (blocks * s->batch * s->num_kv_heads > num_cus()) return false;
+    const double length = std::ceil((double)((max_n + 31) / 32) / 8.0) * kSmallBlockUs;
+    if (kSmallStartUs + length >= us) return false;
+    pl.small = true;
+    pl.dec_groups = 1;
+    pl.row_blocks = (int32_t)blocks;
+    return true;
 }
 
 // `room`: bytes that the caller has for partial results.  A batch of unequal lengths whose own plan
@@ -1623,11 +1817,14 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
         int64_t ns = (8LL * num_cus() + pairs - 1) / pairs;
         const int64_t cap = ((max_n + 31) / 32 + 1) / 2;
         if (ns > cap) ns = cap;
-        ns = (ns + kDecWaves - 1) / kDecWaves * kDecWaves;
+        ns = (ns + kDecLeastWaves - 1) / kDecLeastWaves * kDecLeastWaves;
         if (ns > kDecMaxChunks) ns = kDecMaxChunks;
-        if (ns < kDecWaves) ns = kDecWaves;
+        if (ns < kDecLeastWaves) ns = kDecLeastWaves;
         pl.nsplit = (int32_t)ns;
         pl.decode = true;
+        double us;
+        pl.dec_groups = choose_decode_groups(s, max_n, pl, &us);
+        if (pl.row_blocks > 1) small_call(s, max_n, us, pl);
         return pl;
     }
     if (s->num_splits == 0 && s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, room, pl, order)) return pl;
@@ -1635,7 +1832,9 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
     if (s->num_splits >= 1) {
         pl.nsplit = s->num_splits;
     } else {
-        pl.nsplit = choose_splits(s, pl, room);
+        double us;
+        pl.nsplit = choose_splits(s, pl, room, &us);
+        if (small_call(s, max_n, us, pl)) pl.nsplit = 1;
     }
     return pl;
 }
@@ -1910,11 +2109,16 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
         p.part_o = static_cast<float *>(workspace);
         p.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + ((rows * kD * sizeof(float) + 255) / 256) * 256);
     }
-    if (pl.decode) {
-        hipLaunchKernelGGL(decode_attn_kernel, dim3((unsigned)(dec_units / kDecWaves)), dim3(kDecWaves * 64), 0, hs,
-                           static_cast<const AttnParams &>(p));
+    if (pl.decode || pl.small) {
+        p.nsplit = pl.dec_groups;
+        const int share = !pl.small && pl.row_blocks > 1 ? 2 : 1; // blocks of rows per wavefront
+        const dim3 groups((unsigned)((int64_t)p.batch * p.Hkv * pl.dec_groups * ((pl.row_blocks + share - 1) / share)));
+        const AttnParams &a = p;
+        if (pl.small) hipLaunchKernelGGL((decode_attn_kernel<8, 1>), groups, dim3(512), 0, hs, a);
+        else if (share == 1) hipLaunchKernelGGL((decode_attn_kernel<4, 1>), groups, dim3(256), 0, hs, a);
+        else hipLaunchKernelGGL((decode_attn_kernel<4, 2>), groups, dim3(256), 0, hs, a);
         if (hipGetLastError() != hipSuccess) return CP_ERR_LAUNCH;
-        launch_merge(p, pl.nsplit, hs);
+        if (pl.dec_groups > 1) launch_merge(p, pl.dec_groups, hs);
         return hipGetLastError() == hipSuccess ? CP_OK : CP_ERR_LAUNCH;
     }
     if (!allow_large_lds()) return CP_ERR_LAUNCH;

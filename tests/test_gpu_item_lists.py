@@ -65,7 +65,7 @@ def test_more_requests_than_lanes(H):
 @pytest.mark.parametrize("P,E", [([512], [128]), ([0], [300]), ([130], [65]), ([900, 900], [33, 33]), ([64], [64]),
                                  ([3000], [128]), ([3000, 100], [100, 128])])
 def test_short_key_ranges(H, P, E):
-    """Few row tiles: key ranges of a few tiles; then without room for partial
+    """Few row tiles: a workgroup per 32 rows, or key ranges of a few tiles; then without room for partial
     results, where a short call does without and a longer one is refused."""
     import paper_2511_03475_amd as cp
 
@@ -75,8 +75,8 @@ def test_short_key_ranges(H, P, E):
     _check(H.gpu_attention(w), want, f"P={P} E={E}")
     st = cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
                                 case.extend_lens, case.out, None, case.shape, None, 0, check=False)
-    # 16 key tiles make two ranges of 8, 49 six: too long to go without scratch
-    assert st == (cp.CP_ERR_WORKSPACE if P[0] >= 900 else cp.CP_OK)
+    # 49 key tiles make six ranges of 8: too long to go without scratch
+    assert st == (cp.CP_ERR_WORKSPACE if P[0] == 3000 else cp.CP_OK)
     if st == cp.CP_OK:
         _check(case.out_bits(), want, f"no workspace P={P} E={E}")
 
@@ -92,3 +92,28 @@ def test_cache_append_remainders(H, Hkv, E):
     case.write_kv()
     want = oracle.write_kv(w.k_new, w.v_new, w.kv_pages, w.block_table, w.prefix_lens, w.extend_lens)
     assert np.array_equal(case.kv_pages.cpu().numpy().view(np.uint16), want.view(np.uint16))
+
+
+@pytest.mark.parametrize("G,Hkv", [(4, 2), (8, 1), (1, 3), (5, 1)])
+@pytest.mark.parametrize("P,E", [
+    ([3000, 5, 0, 700], [1, 3, 2, 1]),      # one block of 32 rows; several workgroups a request, some without keys
+    ([9000], [9]), ([2500, 31], [12, 7]),   # two blocks of 32 rows, the second one partly or wholly padding
+    ([300], [11]), ([0], [5]), ([31, 33], [8, 8]),    # and so few keys that each block is a workgroup
+    ([100], [65]), ([200, 200], [40, 40]), ([0, 64], [97, 97]),   # small row-tiled calls: a head's rows across two blocks
+])
+def test_decode_shaped_and_small_calls(H, G, Hkv, P, E):
+    w = W.make_uniform("few_rows", 56, len(P), G * Hkv, Hkv, P, E)
+    _check(H.gpu_attention(w), oracle.attention_of(w), f"G={G} Hkv={Hkv} P={P} E={E}")
+
+
+def test_small_call_lets_nan_through(H):
+    """A key that is not a number reaches every row that sees it, whichever wavefront read it."""
+    import torch
+
+    w = W.make_uniform("nan", 57, 1, 8, 2, [300], [100])
+    case = H.DeviceCase(w)
+    page = int(case.block_table[0, 9])                    # tokens 144 .. 159
+    case.kv_pages.view(-1)[(page * 2 * 2 + 1) * 16 * 128 + 5 * 128] = 0x7FC0      # K of KV head 1
+    case.attention()
+    out = case.out.view(torch.bfloat16).float()
+    assert out[:, 4:].isnan().all() and not out[:, :4].isnan().any()
