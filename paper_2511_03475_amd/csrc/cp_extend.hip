@@ -79,7 +79,7 @@ constexpr int kMixedMaxBatch = 512; // requests of a mixed batch; beyond, planni
 struct MixedParams : AttnParams {
     int32_t seg_tiles;  // key tiles per work item of a row-tiled request, at most
     int32_t dec_blocks; // key blocks of 32 per wavefront of a decode-shaped request, at most
-    int32_t row_items;  // row-tiled items per KV head; decode-shaped work follows them
+    uint64_t dec_share; // items of decode-shaped work among all, as a 32-bit fraction, see decode_items_before
     uint8_t order[kMixedMaxBatch]; // per group of 64 requests: which lane's request is first, second, ...
 };
 
@@ -151,6 +151,10 @@ __host__ __device__ inline int splits_of_request(int P, int E, int G, int seg_ti
     const int ns = (tiles + seg_tiles - 1) / seg_tiles;
     return ns < kMaxSplits ? ns : kMaxSplits;
 }
+// Mixed batches: how many of the first n items of a KV head are decode-shaped work.  They are spread evenly
+// over the list: side by side they wait for memory, of which row-tiled items need little.  dec_share is
+// rounded up, so that all of them are counted at the end.
+__device__ __forceinline__ int decode_items_before(int n, uint64_t dec_share) { return (int)((uint64_t)n * dec_share >> 32); }
 // Inclusive prefix sum over the 64 lanes of a wavefront.
 __device__ __forceinline__ int wave_inclusive_scan(int x, int lane)
 {
@@ -625,8 +629,9 @@ constexpr int kMixedLdsBytes = kWaves * kDecLdsPerWave > kLdsBytes ? kWaves * kD
 // One number of splits for all leaves the longest request to finish alone, and a token that is
 // decoded on a row tile of 256 rows occupies a CU for all its keys.  8 chunks of prompts next to 32
 // decoding requests, up to 12000 cached tokens, 32/8 heads: 246 -> 157 us; 5 and 43, 8/2 heads: 144 -> 69;
-// 21 prompts of 20 to 125 tokens, 64/8 heads: 87 -> 54.  Bound by the row-tiled items, which fill the CUs;
-// the decode work behind them on the list runs where CUs fall free.
+// 21 prompts of 20 to 125 tokens, 64/8 heads: 87 -> 54.  Bound by the row-tiled items, which fill the CUs.
+// The decode work is spread over the list: behind the row-tiled items it ran on all CUs at once and waited for
+// memory (the first of these 157 us so, 146 spread out; 22 decoding beside 4 chunks 59.2 and 58.9).
 enum Mode { kWhole, kSplit, kMixed };
 template <Mode kMode>
 __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::conditional_t<kMode == kMixed, MixedParams, AttnParams> p)
@@ -646,8 +651,9 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
     if (rem < 0) return;
     int r, cu, E, P, unit, split, nsplit, parts = 0;
     if constexpr (kMode == kMixed) {
-        if (rem >= p.row_items) { // eight wavefronts of decode-shaped work, each on its own
-            const Owner w = find_owner<true>((rem - p.row_items) * kWaves + wave, p, lane);
+        const int decode_before = decode_items_before(rem, p.dec_share);
+        if (decode_items_before(rem + 1, p.dec_share) > decode_before) { // eight wavefronts of decode-shaped work, each on its own
+            const Owner w = find_owner<true>(decode_before * kWaves + wave, p, lane);
             if (w.r >= p.batch) return;
             const int row_blocks = (w.E * p.G + kDecRows - 1) / kDecRows;
             const int rb = w.unit % row_blocks, chunk = w.unit / row_blocks; // row blocks of the same keys side by side
@@ -656,7 +662,7 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
                          min(nblk, chunk * per + per), w.splits > 1 ? w.parts + (int64_t)chunk * w.E : -1);
             return;
         }
-        const Owner w = find_owner<false>(rem, p, lane);
+        const Owner w = find_owner<false>(rem - decode_before, p, lane);
         r = w.r;
         cu = w.cu;
         E = w.E;
@@ -2101,7 +2107,7 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
 
     p.seg_tiles = pl.seg_tiles;
     p.dec_blocks = pl.dec_blocks;
-    p.row_items = (int32_t)pl.row_items;
+    if (pl.mixed) p.dec_share = (((uint64_t)(per_head - pl.row_items) << 32) + (uint64_t)per_head - 1) / (uint64_t)per_head;
 
     hipStream_t hs = static_cast<hipStream_t>(stream);
     if (need > 0) {
