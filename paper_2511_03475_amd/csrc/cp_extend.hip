@@ -1201,7 +1201,12 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
 // partial sums of the groups are added in group order.
 constexpr int kMergeGroups = 32;
 constexpr int kMergePerGroup = 8; // splits per group: up to 256 partial results in all
-constexpr int kMergeFewSplits = 8; // up to this many splits the second form is used
+// Up to kMergeFewSplits splits the second form is used, and for as many (row, head) pairs as fill the device up to
+// kMergeSomeSplits: the first form then runs many workgroups of 1024 threads after each other.
+// Attention and merge of 12 ranges, first and second form: 64 rows x 32 heads 36.4 and 26.7 us; 128 x 32 50.0 and 31.0;
+// 256 x 32 162 and 125; of 32 ranges 32 and 25 for 1600 pairs, 191 and 150 for 8192.  One decoded row of 32
+// heads, 24 to 64 ranges, is better off with the first form, whose threads share the ranges.
+constexpr int kMergeFewSplits = 8, kMergeSomeSplits = 32, kMergeSomeRows = 1024;
 __global__ __launch_bounds__(32 * kMergeGroups) void merge_splits_kernel(const float *__restrict__ part_o,
                                                                           const float *__restrict__ part_ml,
                                                                           uint16_t *__restrict__ out,
@@ -1780,9 +1785,9 @@ int32_t choose_decode_groups(const cp_shape *s, int64_t max_n, const Plan &pl, d
 // A call of few rows and few keys, none of it enough for the device: the decode kernel with a workgroup per 32
 // rows, whose eight wavefronts share the keys and need no merge launch.  One round over the CUs only,
 // because every workgroup reads all keys itself.  `us`: the estimate of the way it would go otherwise.
-// Against row tiles in key ranges and a merge: P = 512, E = 128, 8/2 heads 15.7 -> 11.0 us; P = 200, E = 128,
-// 32/8 heads 18.1 -> 9.5; 2 requests, P = 700, E = 60 21.6 -> 17.0; P = 3000, E = 128, 8/2 heads would take 27.4
-// instead of 25.9.  Four wavefronts instead of eight: 11.7, 9.7, 15.9 and 32.3.
+// Against row tiles in the best number of key ranges and a merge: P = 512, E = 128, 8/2 heads 15.7 -> 11.0 us;
+// P = 1500, E = 256, 32/8 heads 29.8 -> 22.2; 4 requests, P = 400, E = 64 21.3 -> 15.9; P = 3000, E = 128, 8/2 heads
+// would take 27.4 instead of 25.9.  Four wavefronts instead of eight: 11.7 us for the first, 32.3 for the last.
 constexpr double kSmallStartUs = 5.0, kSmallBlockUs = 1.5; // a workgroup; a block of 32 keys per wavefront
 bool small_call(const cp_shape *s, int64_t max_n, double us, Plan &pl)
 {
@@ -1849,10 +1854,15 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
 void launch_merge(const AttnParams &p, int nsplit, hipStream_t hs)
 {
     const int64_t n_rh = (int64_t)p.T * p.Hq;
-    if (nsplit <= kMergeFewSplits) {
+    if (nsplit <= kMergeFewSplits || (nsplit <= kMergeSomeSplits && n_rh >= kMergeSomeRows)) {
         const dim3 grid((unsigned)((n_rh + 7) / 8));
         if (nsplit <= 4)
             hipLaunchKernelGGL(merge_few_splits_kernel<4>, grid, dim3(256), 0, hs, p.part_o, p.part_ml, p.out, n_rh, nsplit);
+        else if (nsplit > 16)
+            hipLaunchKernelGGL(merge_few_splits_kernel<kMergeSomeSplits>, grid, dim3(256), 0, hs, p.part_o, p.part_ml,
+                               p.out, n_rh, nsplit);
+        else if (nsplit > kMergeFewSplits)
+            hipLaunchKernelGGL(merge_few_splits_kernel<16>, grid, dim3(256), 0, hs, p.part_o, p.part_ml, p.out, n_rh, nsplit);
         else
             hipLaunchKernelGGL(merge_few_splits_kernel<kMergeFewSplits>, grid, dim3(256), 0, hs, p.part_o, p.part_ml,
                                p.out, n_rh, nsplit);

@@ -117,3 +117,12 @@ def test_small_call_lets_nan_through(H):
     case.attention()
     out = case.out.view(torch.bfloat16).float()
     assert out[:, 4:].isnan().all() and not out[:, :4].isnan().any()
+
+
+@pytest.mark.parametrize("splits", [8, 9, 16, 17, 32, 33])
+@pytest.mark.parametrize("E", [31, 32])
+def test_merge_forms(H, splits, E):
+    """Both forms of the merge around the limits of their numbers of ranges, with 1024 (row, head) pairs and
+    fewer; some ranges are empty."""
+    w = W.make_uniform("merge", 58, 1, 32, 8, [1500], [E])
+    _check(H.gpu_attention(w, num_splits=splits), oracle.attention_of(w), f"E={E} splits={splits}")
