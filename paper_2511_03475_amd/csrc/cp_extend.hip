@@ -511,10 +511,15 @@ __global__ __launch_bounds__(kDecWaves * 64, kRowBlocks == 1 ? 2 : 1) void decod
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int lane = threadIdx.x & 63;
 
-    // work unit: row blocks fastest (neighbours then read the same keys), then key chunk, KV head, request
+    // work unit: row blocks fastest, then key chunk, KV head, request.  Row blocks of the same keys stay on one
+    // XCD where the number of units allows it, so that its L2 fetches the keys once.
     const int row_groups = (p.dec_row_blocks + kRowBlocks - 1) / kRowBlocks;
-    const int rg = blockIdx.x % row_groups;
-    const int uc = blockIdx.x / row_groups;
+    int rg = blockIdx.x % row_groups, uc = blockIdx.x / row_groups;
+    if (row_groups > 1 && gridDim.x / row_groups % kXcds == 0) {
+        const int at = blockIdx.x / kXcds;
+        rg = at % row_groups;
+        uc = at / row_groups * kXcds + blockIdx.x % kXcds;
+    }
     const int chunk = uc % p.nsplit;
     const int rk = uc / p.nsplit;
     const int kvh = rk % p.Hkv;
@@ -1786,9 +1791,9 @@ int32_t choose_decode_groups(const cp_shape *s, int64_t max_n, const Plan &pl, d
 // rows, whose eight wavefronts share the keys and need no merge launch.  One round over the CUs only,
 // because every workgroup reads all keys itself.  `us`: the estimate of the way it would go otherwise.
 // Against row tiles in the best number of key ranges and a merge: P = 512, E = 128, 8/2 heads 15.7 -> 11.0 us;
-// P = 1500, E = 256, 32/8 heads 29.8 -> 22.2; 4 requests, P = 400, E = 64 21.3 -> 15.9; P = 3000, E = 128, 8/2 heads
+// P = 1500, E = 256, 32/8 heads 29.8 -> 21.1; 4 requests, P = 1000, E = 64 25.8 -> 15.3; P = 3000, E = 128, 8/2 heads
 // would take 27.4 instead of 25.9.  Four wavefronts instead of eight: 11.7 us for the first, 32.3 for the last.
-constexpr double kSmallStartUs = 5.0, kSmallBlockUs = 1.5; // a workgroup; a block of 32 keys per wavefront
+constexpr double kSmallStartUs = 5.0, kSmallBlockUs = 2.0; // a workgroup; a block of 32 keys per wavefront
 bool small_call(const cp_shape *s, int64_t max_n, double us, Plan &pl)
 {
     const int G = s->num_q_heads / s->num_kv_heads;
