@@ -87,7 +87,8 @@ size_t cp_workspace_bytes(const cp_shape *shape);
 
 /* The number of key ranges whose partial results cp_extend_attention will merge for this shape
  * (1 = no split; up to 64 when forced, up to 256 when chosen by the library; 0 if invalid).  For a
- * batch of unequal lengths, whose requests are split one by one: the largest. */
+ * batch of unequal lengths, whose requests are split one by one: the largest.  For a decode-shaped
+ * call: the most wavefronts that may share a request's keys, most of whose results meet in LDS. */
 int32_t cp_num_splits(const cp_shape *shape);
 
 /*
@@ -97,10 +98,12 @@ int32_t cp_num_splits(const cp_shape *shape);
  */
 enum {
     CP_PLAN_INVALID = 0,
-    CP_PLAN_ROW_TILED = 1,       /* extend_attn_kernel, keys not split */
+    CP_PLAN_ROW_TILED = 1,       /* extend_attn_kernel, keys not split; calls too small for the device:
+                                    decode_attn_kernel over blocks of 32 rows */
     CP_PLAN_ROW_TILED_SPLIT = 2, /* extend_attn_kernel over key ranges + a merge; in a batch of unequal
                                     lengths decode-shaped requests take decode_attn_kernel's form inside it */
-    CP_PLAN_DECODE = 3           /* decode_attn_kernel (a wavefront per key chunk) + merge_splits_kernel */
+    CP_PLAN_DECODE = 3           /* decode_attn_kernel (wavefronts share the keys) + a merge where several
+                                    workgroups do */
 };
 int32_t cp_plan_kind(const cp_shape *shape);
 

@@ -93,9 +93,9 @@ struct Merge {
 // miss per row.  Three things keep them few and short, and none changes a value or a choice: the
 // nearest neighbour of a row whose neighbour was merged away is looked for only when the row comes up as
 // the smallest (until then its old key is a lower bound: the other entries are what they were, and
-// the new cluster's is compared at every merge); a scan finds the smallest distance of
-// every block first and compares ids only in the blocks where it occurs; and when half of the rows are gone the rest move together, so that the
-// later merges work in cache.  2000 contexts of 15 ids: 190 -> 82 ms on one host, the whole pass from ids to
+// the new cluster's is compared at every merge); a scan finds the smallest distance of every block
+// first and compares ids only in the blocks where it occurs; and when half of the rows are gone the
+// rest move together, so that the later merges work in cache.  2000 contexts of 15 ids: 190 -> 82 ms on one host, the whole pass from ids to
 // execution order 56 -> 31 ms on another; what is left is half the column writes (45 of 82 ms).
 std::vector<Merge> linkage(double *D, int32_t m)
 {
