@@ -1198,8 +1198,10 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
 }
 
 // out[row, head, :] = sum_s w_s O_s / sum_s w_s l_s with w_s = 2^(m_s - max_s m_s).
-// Entries with l_s = 0 (empty splits) are skipped.  Two forms, chosen by the number of splits; in
-// both every sum runs in a fixed order, so the result is reproducible.
+// Entries with l_s = 0 (empty splits) are skipped, and nothing else is: a sum that is not a number, or a value
+// behind a weight of 0 that is not, reaches the result as it does without a split.  A row whose scores are
+// all minus infinity is 0 / 0 in either case.  Two forms, chosen by the number of splits; in both every
+// sum runs in a fixed order, so the result is reproducible.
 //
 // Many splits: one workgroup per (row, head).  kMergeGroups groups of 32 threads take the splits
 // s = g, g + kMergeGroups, ... (at most kMergePerGroup each; 4 consecutive d per thread), then the
@@ -1240,7 +1242,7 @@ __global__ __launch_bounds__(32 * kMergeGroups) void merge_splits_kernel(const f
     float m = -INFINITY;
 #pragma unroll
     for (int i = 0; i < kMergePerGroup; ++i)
-        if (ls[i] > 0.f) m = fmaxf(m, ms[i]);
+        if (ls[i] != 0.f) m = fmaxf(m, ms[i]);
     if (t == 0) s_max[g] = m;
     __syncthreads();
     float m_star = s_max[0];
@@ -1251,7 +1253,7 @@ __global__ __launch_bounds__(32 * kMergeGroups) void merge_splits_kernel(const f
     float denom = 0.f;
 #pragma unroll
     for (int i = 0; i < kMergePerGroup; ++i)
-        if (ls[i] > 0.f) {
+        if (ls[i] != 0.f) {
             const float w = fast_exp2(ms[i] - m_star);
             acc += x[i] * w;
             denom += ls[i] * w;
@@ -1265,7 +1267,7 @@ __global__ __launch_bounds__(32 * kMergeGroups) void merge_splits_kernel(const f
         acc += s_acc[i][t];
         denom += s_den[i];
     }
-    const float inv = denom > 0.f ? 1.f / denom : 0.f;
+    const float inv = 1.f / denom;
     bf16x4 y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[e] * inv);
@@ -1295,17 +1297,17 @@ __global__ __launch_bounds__(256) void merge_few_splits_kernel(const float *__re
     float m_star = -INFINITY;
 #pragma unroll
     for (int s = 0; s < kSplits; ++s)
-        if (ls[s] > 0.f) m_star = fmaxf(m_star, ms[s]);
+        if (ls[s] != 0.f) m_star = fmaxf(m_star, ms[s]);
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
     float denom = 0.f;
 #pragma unroll
     for (int s = 0; s < kSplits; ++s)
-        if (ls[s] > 0.f) {
+        if (ls[s] != 0.f) {
             const float w = fast_exp2(ms[s] - m_star);
             acc += x[s] * w;
             denom += ls[s] * w;
         }
-    const float inv = denom > 0.f ? 1.f / denom : 0.f;
+    const float inv = 1.f / denom;
     bf16x4 y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[e] * inv);
@@ -1356,12 +1358,12 @@ __global__ __launch_bounds__(32 * kMergeHeads) void merge_mixed_kernel(const Mix
 #pragma unroll
     for (int i = 0; i < 2; ++i)
         ml[i] = t + 32 * i < ns ? *reinterpret_cast<const f32x2 *>(p.part_ml + (first + (t + 32 * i) * step) * 2) : f32x2{0.f, 0.f};
-    float m_star = fmaxf(ml[0][1] > 0.f ? ml[0][0] : -INFINITY, ml[1][1] > 0.f ? ml[1][0] : -INFINITY);
+    float m_star = fmaxf(ml[0][1] != 0.f ? ml[0][0] : -INFINITY, ml[1][1] != 0.f ? ml[1][0] : -INFINITY);
 #pragma unroll
     for (int off = 16; off > 0; off >>= 1) m_star = fmaxf(m_star, __shfl_xor(m_star, off, 32));
-    float w[2];
+    float w[2]; // -1: an empty range, which left no values
 #pragma unroll
-    for (int i = 0; i < 2; ++i) w[i] = ml[i][1] > 0.f ? fast_exp2(ml[i][0] - m_star) : 0.f;
+    for (int i = 0; i < 2; ++i) w[i] = ml[i][1] != 0.f ? fast_exp2(ml[i][0] - m_star) : -1.f;
     float denom = ml[0][1] * w[0] + ml[1][1] * w[1];
 #pragma unroll
     for (int off = 16; off > 0; off >>= 1) denom += __shfl_xor(denom, off, 32);
@@ -1378,13 +1380,13 @@ __global__ __launch_bounds__(32 * kMergeHeads) void merge_mixed_kernel(const Mix
 #pragma unroll
             for (int i = 0; i < kMany; ++i) {
                 const float ws = __shfl(s0 < 32 ? w[0] : w[1], (s0 + i) & 31, 32);
-                if (ws > 0.f) acc += x[i] * ws; // an empty range left no values
+                if (!(ws < 0.f)) acc += x[i] * ws; // a weight that is not a number counts
             }
         }
     };
     if (ns <= 4) add_up(std::integral_constant<int, 4>{});
     else add_up(std::integral_constant<int, 16>{});
-    const float inv = denom > 0.f ? 1.f / denom : 0.f;
+    const float inv = 1.f / denom;
     bf16x4 y;
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[e] * inv);

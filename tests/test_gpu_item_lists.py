@@ -126,3 +126,46 @@ def test_merge_forms(H, splits, E):
     fewer; some ranges are empty."""
     w = W.make_uniform("merge", 58, 1, 32, 8, [1500], [E])
     _check(H.gpu_attention(w, num_splits=splits), oracle.attention_of(w), f"E={E} splits={splits}")
+
+
+@pytest.mark.parametrize("P,E,splits", [
+    ([3000, 10], [130, 1], 0),                            # a mixed batch: its own merge
+    ([3000, 40], [1, 300], 0),                            # ... whose decode-shaped request is the bad one
+    ([1500], [100], 3), ([1500], [100], 7),               # the merge of few ranges, at each of its sizes
+    ([1500], [130], 12), ([1500], [130], 23),
+    ([1500], [130], 40), ([1500], [9], 23),               # the merge of many
+    ([3000], [1], 0), ([40000], [9], 0),                  # decode-shaped: LDS sum, then a merge
+    ([1500], [130], 1),                                   # and none at all
+])
+def test_bad_keys_come_through_every_merge(H, P, E, splits):
+    """A key or a value that is not a number makes every row that sees it not a number, also where another
+    range of the row's keys outweighs it by far; so do scores that are all minus infinity (0 / 0, as in the
+    oracle).  Heads of the other KV head stay finite."""
+    import torch
+
+    w = W.make_uniform("bad", 59, len(P), 8, 2, P, E)
+    token = P[0] // 2
+    page, rows = int(w.block_table[0, token // 16]), E[0]
+    for what in (0, 1):                                   # K, V
+        case = H.DeviceCase(w, splits)
+        assert splits == 1 or case.ws_bytes > 0
+        case.kv_pages.view(-1, 2, 2, 16, 128)[page, what, 1, token % 16, 5] = 0x7FC0
+        case.attention()
+        out = case.out.view(torch.bfloat16).float()
+        bad = slice(None) if what == 0 else slice(5, 6)
+        assert out[:rows, 4:, bad].isnan().all() and out[:, :4].isfinite().all(), f"what={what} P={P} E={E} splits={splits}"
+    case = H.DeviceCase(w, splits)                        # key 3 outweighs all others, the bad value has weight 0
+    pool = case.kv_pages.view(-1, 2, 2, 16, 128)
+    case.q[:rows, 4:] = 0x4140                            # 12
+    pool[int(w.block_table[0, 0]), 0, 1, 3] = 0x4140
+    pool[page, 1, 1, token % 16, 5] = 0x7FC0
+    case.attention()
+    out = case.out.view(torch.bfloat16).float()
+    assert out[:rows, 4:, 5].isnan().all() and out[:, :4].isfinite().all(), f"outweighed P={P} E={E} splits={splits}"
+    case = H.DeviceCase(w, splits)
+    case.q[:rows, 4:, 0] = 0x3F80                         # 1 times minus infinity
+    case.kv_pages.view(-1, 2, 2, 16, 128)[:, 0, 1, :, 0] = -128        # 0xFF80
+    case.k_new.view(-1, 2, 128)[:, 1, 0] = -128
+    case.attention()
+    out = case.out.view(torch.bfloat16).float()
+    assert out[:rows, 4:].isnan().all() and out[:, :4].isfinite().all(), f"minus infinity P={P} E={E} splits={splits}"
