@@ -79,16 +79,17 @@ typedef struct cp_shape {
 
 /*
  * Bytes of device scratch with which cp_extend_attention takes its best plan for this shape (0 when
- * the keys are not split); see `workspace` below for calls with less.  A pure function of *shape,
- * including the host length arrays.  Returns 0 for an invalid shape (cp_extend_attention then reports
- * the error).
+ * the keys are not split; for a decode-shaped call an upper bound, room for a partial result per
+ * cp_num_splits); see `workspace` below for calls with less.  A pure function of *shape, including the
+ * host length arrays.  Returns 0 for an invalid shape (cp_extend_attention then reports the error).
  */
 size_t cp_workspace_bytes(const cp_shape *shape);
 
 /* The number of key ranges whose partial results cp_extend_attention will merge for this shape
  * (1 = no split; up to 64 when forced, up to 256 when chosen by the library; 0 if invalid).  For a
  * batch of unequal lengths, whose requests are split one by one: the largest.  For a decode-shaped
- * call: the most wavefronts that may share a request's keys, most of whose results meet in LDS. */
+ * call: an upper bound; a row has as many partial results as workgroups share its request's keys, and
+ * none to merge where one workgroup has them all. */
 int32_t cp_num_splits(const cp_shape *shape);
 
 /*
@@ -127,8 +128,9 @@ int32_t cp_plan_kind(const cp_shape *shape);
  * workspace: DEVICE scratch of cp_workspace_bytes(shape) bytes, 256-byte aligned; may be NULL when
  * that size is 0.  With less, a call that is not decode-shaped and leaves num_splits at 0 takes a plan
  * that fits (not bit for bit the same result), down to the partial results of key ranges of 8 tiles
- * of 64 keys for two workgroups per compute unit; below that, and any other call, is refused.  Its
- * contents are undefined afterwards.
+ * of 64 keys for two workgroups per compute unit; a decode-shaped call runs the same with what its
+ * workgroups leave behind, nothing where one has all keys of a request; below that, and any other call,
+ * is refused.  Its contents are undefined afterwards.
  * Requests with E_r = 0 produce no rows.  Asynchronous on `stream`.
  */
 int cp_extend_attention(const void *q, const void *k_new, const void *v_new,
@@ -143,8 +145,8 @@ int cp_extend_attention(const void *q, const void *k_new, const void *v_new,
  * arguments, result and checks as cp_extend_attention without the last two; the split-K /
  * decode partial results go to an array of cp_noalloc_scratch_bytes() bytes (64 MiB) that lives
  * inside the library, once per device, from the moment the library is loaded until the process
- * ends.  A shape for which every plan needs more is refused with CP_ERR_WORKSPACE
- * and nothing is launched.  The call allocates nothing and frees nothing (the array's device
+ * ends.  A shape that cp_extend_attention would refuse with a workspace of that size is refused with
+ * CP_ERR_WORKSPACE and nothing is launched.  The call allocates nothing and frees nothing (the array's device
  * address is looked up on the first call on each device).  All calls on one device share the
  * array: two such calls that overlap in time (different streams, different host threads) race
  * on it and must be serialised by the caller; calls on one stream are ordered and safe.

@@ -1885,7 +1885,13 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
     if (pl.nsplit <= 1) return 0;
     return part_bytes((size_t)pl.nsplit * (size_t)s->total_extend, s->num_q_heads);
 }
-
+// What the launches touch of it: of a decode-shaped call the partial results of the workgroups that share a
+// request's keys, at most nsplit, none where one workgroup has them all.
+size_t scratch_used(const cp_shape *s, const Plan &pl)
+{
+    if (!pl.decode) return workspace_for(s, pl);
+    return pl.dec_groups > 1 ? part_bytes((size_t)pl.dec_groups * (size_t)s->total_extend, s->num_q_heads) : 0;
+}
 
 // Whether a call with `room` bytes of scratch and the plan pl made for them is refused: the plan needs more, or
 // the call is not decode-shaped, brings less than its best plan wants and also less than key ranges of
@@ -1893,7 +1899,7 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
 // would run several times slower than the call can, without a word.
 bool too_little_scratch(const cp_shape *s, const Plan &pl, size_t room)
 {
-    if (workspace_for(s, pl) > room) return true;
+    if (scratch_used(s, pl) > room) return true;
     if (pl.decode || s->num_splits >= 1) return false;
     int64_t q_tiles = 0;
     int32_t max_key_tiles = 0;
@@ -2088,7 +2094,7 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     MixedParams p;
     const size_t room = workspace && aligned_to(workspace, 256) ? workspace_bytes : 0;
     const Plan pl = make_plan(shape, room, p.order);
-    const size_t need = workspace_for(shape, pl);
+    const size_t need = scratch_used(shape, pl);
     if (too_little_scratch(shape, pl, room)) return CP_ERR_WORKSPACE;
     const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves : pl.q_tiles * pl.nsplit;
     const int64_t total = per_head * shape->num_kv_heads;
@@ -2128,7 +2134,8 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
 
     hipStream_t hs = static_cast<hipStream_t>(stream);
     if (need > 0) {
-        const size_t rows = (pl.mixed ? (size_t)pl.part_rows : (size_t)pl.nsplit * (size_t)p.T) * (size_t)p.Hq;
+        const size_t parts = pl.mixed ? (size_t)pl.part_rows : (size_t)(pl.decode ? pl.dec_groups : pl.nsplit) * (size_t)p.T;
+        const size_t rows = parts * (size_t)p.Hq;
         p.part_o = static_cast<float *>(workspace);
         p.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + ((rows * kD * sizeof(float) + 255) / 256) * 256);
     }

@@ -88,3 +88,34 @@ def test_the_call_can_be_recorded_into_a_hip_graph_and_replayed():
         torch.cuda.synchronize()
         graph.replay()
         assert (c.out_bits() == want).all()
+
+
+@pytest.mark.parametrize("B,Hq,Hkv,P,E", [(64, 64, 8, 100, 8), (40, 8, 8, 33, 7), (3, 8, 2, 40, 16)])
+def test_a_decode_call_needs_only_the_scratch_that_it_uses(B, Hq, Hkv, P, E):
+    """One workgroup has all keys of a request here, so nothing is left to merge: the call runs without a
+    workspace, and through the library's own array also where cp_workspace_bytes is beyond its size."""
+    w = W.make_uniform("noalloc_decode", 783, B, Hq, Hkv, P, E)
+    c = DeviceCase(w)
+    if B == 64:
+        assert c.ws_bytes > cp.cp_noalloc_scratch_bytes()
+    c.attention()
+    want = c.out_bits().copy()
+    c.out.fill_(0x7FC1)
+    cp.cp_extend_attention(c.q, c.k_new, c.v_new, c.kv_pages, c.block_table, c.prefix_lens, c.extend_lens, c.out,
+                           torch.cuda.current_stream(), c.shape, None, 0)
+    assert (c.out_bits() == want).all()
+    c.out.fill_(0x7FC1)
+    cp.cp_extend_attention_noalloc(c.q, c.k_new, c.v_new, c.kv_pages, c.block_table, c.prefix_lens,
+                                   c.extend_lens, c.out, torch.cuda.current_stream(), c.shape)
+    assert (c.out_bits() == want).all()
+
+
+def test_a_decode_call_whose_workgroups_share_keys_still_needs_scratch():
+    w = W.make_uniform("noalloc_decode_long", 784, 2, 8, 2, 9000, 3)
+    c = DeviceCase(w)
+    c.out.fill_(0x1234)
+    st = cp.cp_extend_attention(c.q, c.k_new, c.v_new, c.kv_pages, c.block_table, c.prefix_lens, c.extend_lens, c.out,
+                                torch.cuda.current_stream(), c.shape, None, 0, check=False)
+    assert st == cp.CP_ERR_WORKSPACE and (c.out_bits() == 0x1234).all()
+    got, want = _both(w)
+    assert (got == want).all()
