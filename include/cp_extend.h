@@ -130,7 +130,7 @@ int32_t cp_plan_kind(const cp_shape *shape);
  * that fits (not bit for bit the same result), down to the partial results of key ranges of 8 tiles
  * of 64 keys for two workgroups per compute unit; a decode-shaped call runs the same with what its
  * workgroups leave behind, nothing where one has all keys of a request; below that, and any other call,
- * is refused.  Its contents are undefined afterwards.
+ * is refused, and so is a buffer that the plan for its size uses and that is not aligned.  Its contents are undefined afterwards.
  * Requests with E_r = 0 produce no rows.  Asynchronous on `stream`.
  */
 int cp_extend_attention(const void *q, const void *k_new, const void *v_new,

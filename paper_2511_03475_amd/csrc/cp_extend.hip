@@ -2092,10 +2092,10 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
         if (chk != CP_OK) return chk;
     }
     MixedParams p;
-    const size_t room = workspace && aligned_to(workspace, 256) ? workspace_bytes : 0;
+    const size_t room = workspace ? workspace_bytes : 0;
     const Plan pl = make_plan(shape, room, p.order);
     const size_t need = scratch_used(shape, pl);
-    if (too_little_scratch(shape, pl, room)) return CP_ERR_WORKSPACE;
+    if (too_little_scratch(shape, pl, room) || (need > 0 && !aligned_to(workspace, 256))) return CP_ERR_WORKSPACE;
     const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves : pl.q_tiles * pl.nsplit;
     const int64_t total = per_head * shape->num_kv_heads;
     if (total > INT32_MAX / 2) return CP_ERR_SHAPE;

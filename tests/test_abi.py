@@ -126,6 +126,24 @@ def test_null_pointers_and_missing_workspace_are_rejected_before_any_launch(lib)
         cp.cp_write_kv(None, 1, 1, 1, 1, 1, None, ok)
 
 
+@pytest.mark.parametrize("P,E,Hq,Hkv", [
+    ([782, 64], [1, 254], 64, 8),                 # unequal lengths: calls that also run without scratch
+    ([399, 443, 622, 780, 785, 2], [357, 1, 1, 1, 1, 1], 8, 2),
+    ([3000, 10, 700], [130, 1, 64], 8, 2),        # ... and that do not
+    ([10240], [128], 32, 8),
+    ([131072], [1], 32, 8),                       # decode-shaped, several workgroups on the keys
+])
+def test_a_misaligned_workspace_is_rejected_wherever_the_plan_uses_it(lib, P, E, Hq, Hkv):
+    """A buffer that is large enough but not 256-byte aligned is an error of the caller; it is not taken for a
+    missing one, without which some of these calls run, slower and not bit for bit the same."""
+    sh = _shape(P, E, Hq=Hq, Hkv=Hkv)
+    need = cp.cp_workspace_bytes(sh)
+    assert need > 0
+    for off in (16, 128):
+        assert cp.cp_extend_attention(256, 256, 256, 256, 256, 256, 256, 256, None, sh, 4096 + off, need,
+                                      check=False) == cp.CP_ERR_WORKSPACE
+
+
 def test_misaligned_device_pointers_are_rejected_before_any_launch(lib):
     """q, k_new, v_new, kv_pages and out are moved in 16-byte pieces, the int32 arrays in 4-byte
     ones: every pointer is checked on the host, one at a time here."""
