@@ -99,12 +99,12 @@ int32_t cp_num_splits(const cp_shape *shape);
  */
 enum {
     CP_PLAN_INVALID = 0,
-    CP_PLAN_ROW_TILED = 1,       /* extend_attn_kernel, keys not split; calls too small for the device:
-                                    decode_attn_kernel over blocks of 32 rows */
+    CP_PLAN_ROW_TILED = 1,       /* extend_attn_kernel, keys not split */
     CP_PLAN_ROW_TILED_SPLIT = 2, /* extend_attn_kernel over key ranges + a merge; in a batch of unequal
                                     lengths decode-shaped requests take decode_attn_kernel's form inside it */
     CP_PLAN_DECODE = 3           /* decode_attn_kernel (wavefronts share the keys) + a merge where several
-                                    workgroups do */
+                                    workgroups do; also calls too small for the device, a workgroup per
+                                    32 rows of a KV head and no merge */
 };
 int32_t cp_plan_kind(const cp_shape *shape);
 

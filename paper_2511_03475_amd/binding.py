@@ -200,8 +200,9 @@ def cp_num_splits(shape: Shape) -> int:
     return int(load_library().cp_num_splits(shape.ref()))
 
 
-PLAN_KERNELS = {1: "extend_attn_kernel", 2: "extend_attn_kernel + merge_splits_kernel",
-                3: "decode_attn_kernel + merge_splits_kernel"}
+# which merge runs, and for decode_attn_kernel whether one does, depends on the lengths
+PLAN_KERNELS = {1: "extend_attn_kernel", 2: "extend_attn_kernel + a merge kernel",
+                3: "decode_attn_kernel (+ a merge kernel where workgroups share keys)"}
 
 
 def cp_plan_kind(shape: Shape) -> int:

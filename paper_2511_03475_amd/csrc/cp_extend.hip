@@ -2058,7 +2058,7 @@ int32_t cp_plan_kind(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return CP_PLAN_INVALID;
     const Plan pl = make_plan(shape);
-    if (pl.decode) return CP_PLAN_DECODE;
+    if (pl.decode || pl.small) return CP_PLAN_DECODE;
     return pl.nsplit > 1 ? CP_PLAN_ROW_TILED_SPLIT : CP_PLAN_ROW_TILED;
 }
 

@@ -87,7 +87,12 @@ def test_plan_kind_names_the_kernels_that_will_run(lib):
     assert cp.cp_plan_kind(_shape([10240], [128])) == 2                           # few workgroups: split
     assert cp.cp_plan_kind(_shape([10240] * 32, [1] * 32)) == 3                   # decode-shaped
     assert cp.cp_plan_kind(_shape([10240] * 32, [1] * 32, splits=1)) == 1
+    assert cp.cp_plan_kind(_shape([512], [128], Hq=8, Hkv=2)) == 3                # small: decode_attn_kernel, no merge
+    assert cp.cp_num_splits(_shape([512], [128], Hq=8, Hkv=2)) == 1
+    assert cp.cp_plan_kind(_shape([3000, 40], [130, 1], Hq=8, Hkv=2)) == 2        # unequal lengths, split
     assert cp.cp_plan_kind(_shape([32], [32], D=64)) == 0
+    # the extend kernel takes one of three merges, the decode kernel one or none: neither is named
+    assert all("merge_" not in names for names in cp.PLAN_KERNELS.values())
     assert set(cp.PLAN_KERNELS) == {1, 2, 3}
 
 
