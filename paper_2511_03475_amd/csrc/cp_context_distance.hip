@@ -146,7 +146,7 @@ __global__ __launch_bounds__(kThreads, 4) void context_distance_kernel(const int
     for (int t = 0; t < over; ++t) {
         const uint32_t h = s_over_hash[t], entry = s_over_entry[t], pos = entry % kMax;
         uint32_t gap = 0, hit = 0;
-        for (int b = 0; b < len_j; ++b)
+        for (int b = 0; b < min(len_j, stride); ++b) // the length comes from the device, unchecked
             if ((uint32_t)contexts[(int64_t)jc * stride + b] * kHash == h) {
                 gap = (uint32_t)abs(b - (int)pos);
                 hit = 1;

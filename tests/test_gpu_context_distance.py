@@ -78,3 +78,23 @@ def test_tile_edges_and_crowded_dictionary_buckets(n, stride):
     C = np.stack([rng.permutation(ids)[:stride] for _ in range(n)]).astype(np.int32)
     L = rng.integers(0, stride + 1, size=n).astype(np.int32)
     _check(C, L, 0.001)
+
+
+def test_a_length_beyond_the_row_reads_no_other_row():
+    """Lengths live on the device and are not validated: one beyond the stride counts as a length, but the ids
+    behind the row belong to the next one (and behind the last row to nobody), also in the search for ids that
+    found no place in the kernel's dictionary."""
+    rng = np.random.default_rng(3)
+    back = pow(0x9E3779B1, -1, 1 << 32)
+    crowd = [(h * back) % (1 << 32) for h in (0x12400000 + np.arange(64)).tolist()]
+    ids = np.array([i for i in crowd if i < 1 << 31][:20], dtype=np.int64)
+    n, stride = 64, 8
+    C = np.stack([rng.permutation(ids)[:stride] for _ in range(n)]).astype(np.int32)
+    L = np.full(n, stride, np.int32)
+    L[:n - 1:3] = stride + 4
+    want = np.zeros((n, n))
+    for i in range(n):
+        for j in range(n):
+            gaps = [abs(a - C[j].tolist().index(x)) for a, x in enumerate(C[i].tolist()) if x in C[j]]
+            want[i, j] = 1.0 - len(gaps) / max(L[i], L[j]) + 0.001 * sum(gaps) / max(len(gaps), 1)
+    assert np.abs(_gpu(C, L, 0.001) - want).max() <= TOL
