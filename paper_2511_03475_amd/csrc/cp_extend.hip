@@ -2072,10 +2072,12 @@ size_t cp_workspace_bytes(const cp_shape *shape)
 
 namespace {
 // Everything behind cp_extend_attention: argument checks, plan, launches.  `workspace` is
-// whatever scratch the entry point brings: the caller's buffer or the library's own array.
+// whatever scratch the entry point brings: the caller's buffer or the library's own array.  `planned`: the
+// plan for it where the entry point has made and checked one, with its order in p.
 int run_attention(const void *q, const void *k_new, const void *v_new, const void *kv_pages,
                   const int32_t *block_table, const int32_t *prefix_lens, const int32_t *extend_lens, void *out,
-                  void *stream, const cp_shape *shape, void *workspace, size_t workspace_bytes)
+                  void *stream, const cp_shape *shape, void *workspace, size_t workspace_bytes, MixedParams &p,
+                  const Plan *planned)
 {
     const int st = validate(shape);
     if (st != CP_OK) return st;
@@ -2091,11 +2093,11 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
                                      nullptr);
         if (chk != CP_OK) return chk;
     }
-    MixedParams p;
     const size_t room = workspace ? workspace_bytes : 0;
-    const Plan pl = make_plan(shape, room, p.order);
+    const Plan pl = planned ? *planned : make_plan(shape, room, p.order);
     const size_t need = scratch_used(shape, pl);
-    if (too_little_scratch(shape, pl, room) || (need > 0 && !aligned_to(workspace, 256))) return CP_ERR_WORKSPACE;
+    if (!planned && too_little_scratch(shape, pl, room)) return CP_ERR_WORKSPACE;
+    if (need > 0 && !aligned_to(workspace, 256)) return CP_ERR_WORKSPACE;
     const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves : pl.q_tiles * pl.nsplit;
     const int64_t total = per_head * shape->num_kv_heads;
     if (total > INT32_MAX / 2) return CP_ERR_SHAPE;
@@ -2179,8 +2181,9 @@ int cp_extend_attention(const void *q, const void *k_new, const void *v_new, con
                         const int32_t *extend_lens, void *out, void *stream, const cp_shape *shape,
                         void *workspace, size_t workspace_bytes)
 {
+    MixedParams p;
     return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, shape,
-                         workspace, workspace_bytes);
+                         workspace, workspace_bytes, p, nullptr);
 }
 
 size_t cp_noalloc_scratch_bytes(void) { return CP_NOALLOC_SCRATCH_BYTES; }
@@ -2192,11 +2195,13 @@ int cp_extend_attention_noalloc(const void *q, const void *k_new, const void *v_
     const int st = validate(shape);
     if (st != CP_OK) return st;
     // sizes beyond the library's own array are refused here, before anything is looked up or launched
-    if (too_little_scratch(shape, make_plan(shape, CP_NOALLOC_SCRATCH_BYTES), CP_NOALLOC_SCRATCH_BYTES)) return CP_ERR_WORKSPACE;
+    MixedParams p;
+    const Plan pl = make_plan(shape, CP_NOALLOC_SCRATCH_BYTES, p.order);
+    if (too_little_scratch(shape, pl, CP_NOALLOC_SCRATCH_BYTES)) return CP_ERR_WORKSPACE;
     void *ptr = scratch_address(); // the array's address on the current device, never the array's name
     if (!ptr) return CP_ERR_LAUNCH;
     return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, shape, ptr,
-                         CP_NOALLOC_SCRATCH_BYTES);
+                         CP_NOALLOC_SCRATCH_BYTES, p, &pl);
 }
 
 int cp_write_kv(const void *k_new, const void *v_new, void *kv_pages, const int32_t *block_table,

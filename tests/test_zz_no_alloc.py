@@ -119,3 +119,11 @@ def test_a_decode_call_whose_workgroups_share_keys_still_needs_scratch():
     assert st == cp.CP_ERR_WORKSPACE and (c.out_bits() == 0x1234).all()
     got, want = _both(w)
     assert (got == want).all()
+
+
+def test_a_batch_split_request_by_request_keeps_its_order():
+    """Unequal lengths, decode-shaped requests next to prompts: the plan is made once, with the order in which
+    the requests are taken, before the library's own array is looked up."""
+    w = W.make_uniform("noalloc_mixed", 785, 5, 8, 2, [6000, 10, 3000, 0, 64], [1, 300, 4, 700, 65])
+    got, want = _both(w)
+    assert (got == want).all()
