@@ -1627,8 +1627,8 @@ double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks,
     return us;
 }
 
-// The best plan whose partial results fit into `room` bytes; false if there is none.
-bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order)
+// The best plan whose partial results fit into `room` bytes, and its time; false if there is none.
+bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order, double *estimate)
 {
     const int G = s->num_q_heads / s->num_kv_heads;
     MixedRequest req[kMixedMaxBatch];
@@ -1694,6 +1694,7 @@ bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order)
             best = pl;
         }
     }
+    *estimate = best_us;
     return best_us >= 0.0;
 }
 
@@ -1709,17 +1710,21 @@ void row_tiled_extent(const cp_shape *s, int64_t &q_tiles, int32_t &max_key_tile
     }
 }
 
-// Key ranges for row-tiled requests of equal lengths: the least estimated time (see above).  A grid
+// One number of key ranges for all requests: the least estimated time (see above).  A grid
 // of two workgroups per CU is not split: it gains nothing then.  Row tiles of one length run in whole
 // rounds over the CUs; if a request has several, of different lengths, the last round is about half empty.
+// In a batch of unequal lengths the longest item may be among the last to begin, and more ranges than the cheaper merge
+// takes are for the plan that splits only the requests which need it (10 requests, 39 ranges 36 us, 25).
 // Against ranges of at least 8 tiles, two workgroups per CU: P = 512, E = 128, 8/2 heads (4 workgroups
 // of 10 tiles before) 25.2 -> 19.0 us; 4 requests, P = 3000, E = 128, 32/8 heads 61 -> 45; 1 request,
 // P = 2000, E = 700, 64/8 heads 100 -> 72; 12 requests, P = 20000, E = 128, 32/8 heads 538 -> 496.
+constexpr double kLastItem = 0.75; // of its length, behind the others
 int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *estimate)
 {
-    *estimate = 0.0;
     const int64_t items = pl.q_tiles * s->num_kv_heads, cus = num_cus();
-    if (items >= 2 * cus) return 1;
+    const bool equal = equal_lengths(s);
+    *estimate = 0.0;
+    if (items >= 2 * cus && (equal || s->batch > kMixedMaxBatch)) return 1; // nothing to compare it with
     const int G = s->num_q_heads / s->num_kv_heads;
     double tiles = 0.0; // key tiles of all items
     bool alike = true;
@@ -1734,13 +1739,16 @@ int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *es
     }
     int32_t best = 1;
     double best_us = 0.0;
-    for (int32_t ns = 1; ns <= std::min(kMaxSplits, std::max(1, pl.max_key_tiles / 2)); ++ns) {
+    const int32_t most = items >= 2 * cus ? 1 : std::min(equal ? kMaxSplits : kMergeSomeSplits, std::max(1, pl.max_key_tiles / 2));
+    for (int32_t ns = 1; ns <= most; ++ns) {
         const size_t bytes = ns > 1 ? part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) : 0;
         if (bytes > room) break;
         const double longest = kItemUs + kTileUs * ((pl.max_key_tiles + ns - 1) / ns);
         const double mean = kItemUs + kTileUs * tiles / ((double)items * ns);
         double us = longest;
-        if (items * ns > cus)
+        if (items * ns > cus && !equal)
+            us = std::max(us, mean * ((double)(items * ns) / (double)cus) + kLastItem * longest);
+        else if (items * ns > cus)
             us = std::max(us, alike ? (double)((items * ns + cus - 1) / cus) * mean : mean * ((double)(items * ns) / (double)cus + 0.5));
         if (ns > 1) us += kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
         if (ns == 1 || us < best_us) {
@@ -1813,8 +1821,14 @@ bool small_call(const cp_shape *s, int64_t max_n, double us, Plan &pl)
     return true;
 }
 
-// `room`: bytes that the caller has for partial results.  A batch of unequal lengths whose own plan
-// needs more takes the uniform one.
+// A batch of unequal lengths is split request by request where that promises kMixedUs less than one number of
+// key ranges for all, whose kernel finds the owner of an item about 1 us faster; a small one (see above) needs
+// neither.  12 requests, P up to 190, E up to 59, 8/2 heads: split request by request 20.8 us, one range each 15.6,
+// small 8.9; 12, P up to 14891, E up to 2805, 64/8 heads 91, with one number of ranges 126.  Of 300 random
+// batches of 2 to 64 requests 92 were more than 6 % slower than with one number of ranges of at least 8 tiles as long as
+// all were split request by request; 10 are.
+constexpr double kMixedUs = 2.0;
+// `room`: bytes that the caller has for partial results.
 // `order`: receives MixedParams::order of a mixed plan.
 Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullptr)
 {
@@ -1845,14 +1859,21 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
         if (pl.row_blocks > 1) small_call(s, max_n, us, pl);
         return pl;
     }
-    if (s->num_splits == 0 && s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, room, pl, order)) return pl;
     row_tiled_extent(s, pl.q_tiles, pl.max_key_tiles);
     if (s->num_splits >= 1) {
         pl.nsplit = s->num_splits;
-    } else {
-        double us;
-        pl.nsplit = choose_splits(s, pl, room, &us);
-        if (small_call(s, max_n, us, pl)) pl.nsplit = 1;
+        return pl;
+    }
+    double us;
+    pl.nsplit = choose_splits(s, pl, room, &us);
+    if (small_call(s, max_n, us, pl)) {
+        pl.nsplit = 1;
+        return pl;
+    }
+    if (s->batch <= kMixedMaxBatch && max_e > 0 && !equal_lengths(s)) {
+        Plan mixed{0, 0, 1, false, 1};
+        double mixed_us;
+        if (plan_mixed(s, room, mixed, order, &mixed_us) && mixed_us + kMixedUs < us) return mixed;
     }
     return pl;
 }

@@ -96,6 +96,24 @@ def test_plan_kind_names_the_kernels_that_will_run(lib):
     assert set(cp.PLAN_KERNELS) == {1, 2, 3}
 
 
+@pytest.mark.parametrize("P,E,Hq,Hkv,kind,splits", [
+    ([190, 40, 7], [1, 59, 1], 8, 2, 3, 1),                   # small calls, whatever the lengths
+    ([416, 100], [1, 354], 8, 2, 3, 1),
+    ([263, 30, 111, 9, 80], [1, 1, 23, 1, 1], 64, 8, 3, 1),
+    ([50, 300, 120, 77, 190] * 5, [1, 1, 1, 1, 60] * 5, 8, 2, 1, 1),   # a merge would cost more than it saves
+])
+def test_small_batches_of_unequal_lengths_are_not_split(lib, P, E, Hq, Hkv, kind, splits):
+    """Requests split one by one and merged took 1.2 to 1.35 times as long as one launch."""
+    sh = _shape(P, E, Hq=Hq, Hkv=Hkv)
+    assert cp.cp_plan_kind(sh) == kind and cp.cp_num_splits(sh) == splits and cp.cp_workspace_bytes(sh) == 0
+
+
+def test_long_batches_of_unequal_lengths_are_split_request_by_request(lib):
+    sh = _shape([12000] + [300] * 30, [130] + [1] * 30)
+    rows = cp.cp_workspace_bytes(sh) // (32 * 130 * 4)        # partial results of the long request alone
+    assert cp.cp_plan_kind(sh) == 2 and 130 < rows < cp.cp_num_splits(sh) * 160
+
+
 def test_invalid_shapes_are_rejected_on_the_host(lib):
     bad = [
         _shape([32], [32], Hq=4, Hkv=3),           # Hq % Hkv != 0

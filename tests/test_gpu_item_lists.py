@@ -34,6 +34,9 @@ def test_items_dealt_out_over_the_xcds(H, Hkv, P, E):
     ([6000, 10, 3000, 0, 64], [1, 300, 4, 700, 65]),      # several key ranges for some requests, one for others
     ([2000, 31, 32, 33, 0], [2, 1, 1, 1, 1]),             # blocks of 32 keys: remainders
     ([4096, 50, 0], [0, 513, 1]),                         # a request without new tokens
+    ([190, 40, 7], [1, 59, 1]),                           # small: no key ranges at all, rows of some requests missing
+    ([50, 300, 120, 77, 190] * 5, [1, 1, 1, 1, 60] * 5),  # one range each is faster than ranges of their own
+    ([12000, 300, 500], [130, 130, 1]),                   # one long request in many ranges
 ])
 def test_batches_of_unequal_lengths(H, G, Hkv, P, E):
     import paper_2511_03475_amd as cp
@@ -129,7 +132,7 @@ def test_merge_forms(H, splits, E):
 
 
 @pytest.mark.parametrize("P,E,splits", [
-    ([3000, 10], [130, 1], 0),                            # a mixed batch: its own merge
+    ([3000, 6000, 10, 0], [130, 1, 300, 700], 0),         # a mixed batch: its own merge
     ([3000, 40], [1, 300], 0),                            # ... whose decode-shaped request is the bad one
     ([1500], [100], 3), ([1500], [100], 7),               # the merge of few ranges, at each of its sizes
     ([1500], [130], 12), ([1500], [130], 23),
