@@ -1507,6 +1507,7 @@ struct Plan {
     bool decode;       // few rows per (request, KV head): decode_attn_kernel
     int32_t row_blocks; // ... in this many blocks of 32 rows
     int32_t dec_groups = 1; // ... by this many workgroups that share a request's keys
+    int32_t dec_share = 1;  // ... with this many blocks of rows per wavefront
     bool small = false; // few rows and keys: decode_attn_kernel with a workgroup per block of 32 rows
     bool mixed = false; // unequal lengths: extend_attn_kernel<kMixed>, with
     int32_t seg_tiles = 1, dec_blocks = 1;       // at most so many keys per item
@@ -1766,35 +1767,49 @@ int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *es
 // 131072 tokens, 8 KV heads: 16 per head 98 us, 24 88, 32 91, 64 93; 20 of 9000: 1 per head 117, 3 124, 4 126),
 // and every one more is a partial result to merge.  Of those with one block of rows a CU holds two; CUs
 // with one less than others cost bandwidth (45 of 7000: 1 per head, 360, 217 us; 2 205; 3 220; 4 210).
-// Of those with two blocks it holds one, and the next round begins when it ends (3 of 20000, 10
-// new tokens: 8 per head, 192, 55 us; 12, 288, 81; 20, 480, 61).
-constexpr double kDecGroupBytesPerUs = 4.0e4, kDecGroup2BytesPerUs = 3.3e4, kDecBytesPerUs = 6.5e6;
+constexpr double kDecGroupBytesPerUs = 4.0e4, kDecBytesPerUs = 6.5e6;
 constexpr double kDecStartUs = 4.0, kDecMergeUs = 5.0, kDecMergeManyUs = 1.5;
-int32_t choose_decode_groups(const cp_shape *s, int64_t max_n, const Plan &pl, double *estimate)
+// Two blocks of rows.  Together in a wavefront they read the keys once, but a CU holds one such workgroup, its start
+// and end take twice as long, and the next round begins when it ends (3 of 20000, 10 new tokens: 8 per
+// head, 192, 55 us; 12, 288, 81; 20, 480, 61).  Apart, a CU holds two, and the L2 serves the second if both are on one
+// XCD, for which their number has to be a multiple of the XCDs.  Together is better where the memory bounds the call (32 requests of 10240, 16
+// new: 222 us, apart 234; 25 of 9173, 7 new, 64/8 heads 174, 182), apart where the chain of blocks does
+// (1 of 46, 14 new, 8/2 heads 10.8, 7.5; 33 of 1544, 10 new 72, 60; 2 of 23880, 12 new 50, 37).
+constexpr double kDec2ApartBytesPerUs = 5.8e4, kDec2ApartStartUs = 4.4, kDec2ApartRoundUs = 2.0, kDec2ApartTwice = 1.6;
+constexpr double kDec2BytesPerUs = 3.1e4, kDec2MemoryBytesPerUs = 7.0e6, kDec2StartUs = 4.2, kDec2RoundUs = 4.6, kDec2MergeUs = 2.0;
+void choose_decode_groups(const cp_shape *s, int64_t max_n, Plan &pl, double *estimate)
 {
     const double units = (double)s->batch * s->num_kv_heads, cus = num_cus();
     const double blocks = (double)((max_n + 31) / 32);
-    double best_us = 0.0;
-    int32_t best = 1;
+    double best_us = -1.0;
     for (int groups = 1; groups <= pl.nsplit && 4 * (groups - 1) < blocks; ++groups) {
-        const double launched = units * groups, rounds = std::ceil(launched / cus), fill = launched / (cus * rounds);
+        const double launched = units * groups;
         const double bytes = std::ceil(std::ceil(blocks / groups) / 4.0) * 4.0 * 16384.0; // of one workgroup
-        double us;
-        if (pl.row_blocks > 1) {
-            us = rounds * (kDecStartUs + std::max(bytes / kDecGroup2BytesPerUs, std::min(launched, cus) * bytes / kDecBytesPerUs));
-        } else {
-            us = kDecStartUs * std::max(1.0, 0.5 * launched / cus) +
-                 std::max(bytes / kDecGroupBytesPerUs, launched * bytes / kDecBytesPerUs * (rounds > 1.0 ? 1.3 - 0.3 * fill : 1.0));
-        }
-        if (groups > 1) us += kDecMergeUs + 2.0 * (double)part_bytes((size_t)groups * (size_t)s->total_extend, s->num_q_heads) / kPartBytesPerUs;
-        if (groups > kMergeFewSplits) us += kDecMergeManyUs;
-        if (groups == 1 || us < best_us) {
-            best_us = us;
-            best = groups;
+        const double traffic = 2.0 * (double)part_bytes((size_t)groups * (size_t)s->total_extend, s->num_q_heads) / kPartBytesPerUs;
+        for (int share = 1; share <= pl.row_blocks; ++share) {
+            const double workgroups = launched * pl.row_blocks / share, rounds = std::ceil(workgroups / cus);
+            const double empty = rounds > 1.0 ? 1.0 - workgroups / (cus * rounds) : 0.0; // of the last round
+            double us;
+            if (pl.row_blocks == 1) {
+                us = kDecStartUs * std::max(1.0, 0.5 * launched / cus) +
+                     std::max(bytes / kDecGroupBytesPerUs, launched * bytes / kDecBytesPerUs * (1.0 + 0.3 * empty));
+            } else if (share == 1) {
+                const double twice = (int64_t)launched % kXcds == 0 ? 1.0 : kDec2ApartTwice;
+                us = kDec2ApartStartUs + kDec2ApartRoundUs * std::max(1.0, launched / cus) +
+                     std::max(bytes / kDec2ApartBytesPerUs, launched * bytes / kDecBytesPerUs * twice * (1.0 + 0.6 * empty));
+            } else {
+                us = kDec2StartUs + rounds * (kDec2RoundUs + std::max(bytes / kDec2BytesPerUs, std::min(launched, cus) * bytes / kDec2MemoryBytesPerUs));
+            }
+            if (groups > 1) us += (pl.row_blocks == 1 ? kDecMergeUs : kDec2MergeUs) + traffic;
+            if (groups > kMergeFewSplits) us += kDecMergeManyUs;
+            if (best_us < 0.0 || us < best_us) {
+                best_us = us;
+                pl.dec_groups = groups;
+                pl.dec_share = share;
+            }
         }
     }
     *estimate = best_us;
-    return best;
 }
 
 // A call of few rows and few keys, none of it enough for the device: the decode kernel with a workgroup per 32
@@ -1804,6 +1819,9 @@ int32_t choose_decode_groups(const cp_shape *s, int64_t max_n, const Plan &pl, d
 // P = 1500, E = 256, 32/8 heads 29.8 -> 21.1; 4 requests, P = 1000, E = 64 25.8 -> 15.3; P = 3000, E = 128, 8/2 heads
 // would take 27.4 instead of 25.9.  Four wavefronts instead of eight: 11.7 us for the first, 32.3 for the last.
 constexpr double kSmallStartUs = 5.0, kSmallBlockUs = 2.0; // a workgroup; a block of 32 keys per wavefront
+// Of decode-shaped calls those with two row blocks and at most this many keys: 12 requests, 16 new tokens, 32/8
+// heads, P = 3546 34.7 us, 39.6 otherwise; 57, 9 new, 8/2 heads, P = 15646 250, which is more than estimated, and 171.
+constexpr int64_t kSmallDecodeKeys = 4096;
 bool small_call(const cp_shape *s, int64_t max_n, double us, Plan &pl)
 {
     const int G = s->num_q_heads / s->num_kv_heads;
@@ -1855,8 +1873,8 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
         pl.nsplit = (int32_t)ns;
         pl.decode = true;
         double us;
-        pl.dec_groups = choose_decode_groups(s, max_n, pl, &us);
-        if (pl.row_blocks > 1) small_call(s, max_n, us, pl);
+        choose_decode_groups(s, max_n, pl, &us);
+        if (pl.row_blocks > 1 && max_n <= kSmallDecodeKeys) small_call(s, max_n, us, pl);
         return pl;
     }
     row_tiled_extent(s, pl.q_tiles, pl.max_key_tiles);
@@ -2164,7 +2182,7 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     }
     if (pl.decode || pl.small) {
         p.nsplit = pl.dec_groups;
-        const int share = !pl.small && pl.row_blocks > 1 ? 2 : 1; // blocks of rows per wavefront
+        const int share = pl.small ? 1 : pl.dec_share;
         const dim3 groups((unsigned)((int64_t)p.batch * p.Hkv * pl.dec_groups * ((pl.row_blocks + share - 1) / share)));
         const AttnParams &a = p;
         if (pl.small) hipLaunchKernelGGL((decode_attn_kernel<8, 1>), groups, dim3(512), 0, hs, a);

@@ -172,3 +172,16 @@ def test_bad_keys_come_through_every_merge(H, P, E, splits):
     case.attention()
     out = case.out.view(torch.bfloat16).float()
     assert out[:rows, 4:].isnan().all() and out[:, :4].isfinite().all(), f"minus infinity P={P} E={E} splits={splits}"
+
+
+@pytest.mark.parametrize("B,Hkv,P,E", [
+    (7, 32, 1000, 9), (3, 3, 16000, 9),       # both blocks of rows in a wavefront; one workgroup on the keys, several
+    (1, 2, 2513, 14), (3, 2, 1500, 11),       # apart, several workgroups: their number a multiple of the XCDs, and not
+    (40, 8, 150, 13),                         # apart, one workgroup each
+])
+def test_two_blocks_of_rows_together_and_apart(H, B, Hkv, P, E):
+    """Lengths that differ a little and requests without new tokens, so that blocks are partly or wholly padding."""
+    Ps = [max(P - 37 * (r % 5), 0) for r in range(B)]
+    Es = [E - r % 4 if r % 6 != 5 else 0 for r in range(B)]
+    w = W.make_uniform("two_blocks", 60, B, 4 * Hkv, Hkv, Ps, Es)
+    _check(H.gpu_attention(w), oracle.attention_of(w), f"B={B} Hkv={Hkv} P={P} E={E}")
