@@ -100,10 +100,9 @@ __device__ __forceinline__ float halfwave_sum(float x)
 // The item list of a call is KV head by KV head, items_per_head each.  Consecutive workgroup ids go
 // round the XCDs, and an XCD works on one KV head at a time, so that the workgroups resident on it
 // stream the same K/V through its L2.  With 8 KV heads or more an XCD gets a contiguous range of the
-// list.  With 1, 2 or 4 several XCDs share a head: a contiguous range each is right when that is the
-// same number of equal requests for all of them (4 requests, P = 4000, E = 3000, 8/2 heads: 288 us,
-// 299 dealt out), otherwise it leaves unequal shares, because the longest row tiles of a request
-// come first, and the head's items are dealt out one at a time (one prompt of 32768 tokens, 8/2
+// list.  With 1, 2 or 4 several XCDs share a head: a contiguous range each is right when that is about
+// the same work for all of them (contiguous_ranges), otherwise, because the longest row tiles of a
+// request come first, the head's items are dealt out one at a time (one prompt of 32768 tokens, 8/2
 // heads: 2.81 -> 1.85 ms; of 8192: 211 -> 151 us).
 // Position of this workgroup's item in the list, or -1.
 __device__ __forceinline__ int work_item(int bid, const AttnParams &p, int &kvh)
@@ -1896,6 +1895,38 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
     return pl;
 }
 
+// Whether XCDs that share a KV head take a contiguous range of its items each (see work_item): for equal requests, if
+// no range takes more than 6 % longer than the mean.  Then the XCDs stream different keys; dealt out, all the same
+// ones.  9 requests, P = 5548, E = 817, 8/2 heads 234 us, dealt out 293; 20, P = 0, E = 1511 122 and 137; but with a
+// range 15 % over the mean (3 requests, P = 0, E = 5067, 16/4 heads) 342, dealt out 303.
+constexpr double kContiguousExcess = 1.06;
+bool contiguous_ranges(const cp_shape *s, const Plan &pl, int64_t items, int xcds)
+{
+    if (items <= 0 || pl.mixed || !equal_lengths(s)) return false;
+    const int G = s->num_q_heads / s->num_kv_heads, E = s->h_extend_lens[0], pack = heads_per_tile(E, G);
+    const int64_t rows = kBM / pack, nt = (E + rows - 1) / rows, per = (items + xcds - 1) / xcds;
+    const double prefix = (double)((s->h_prefix_lens[0] + kBN - 1) / kBN);
+    double load = 0.0, most = 0.0, all = 0.0;
+    int64_t left = per;
+    for (int r = 0; r < s->batch; ++r)
+        for (int64_t t = nt - 1; t >= 0; --t) {
+            const double tiles = prefix + (double)((std::min<int64_t>(E, (t + 1) * rows) + kBN - 1) / kBN);
+            const double us = kItemUs + kTileUs * tiles / pl.nsplit;
+            for (int64_t n = G / pack * pl.nsplit; n > 0;) {
+                const int64_t take = std::min(n, left);
+                load += (double)take * us;
+                n -= take;
+                left -= take;
+                if (left > 0) continue;
+                most = std::max(most, load);
+                all += load;
+                load = 0.0;
+                left = per;
+            }
+        }
+    return std::max(most, load) * xcds <= kContiguousExcess * (all + load);
+}
+
 // Launches the merge of nsplit partial results for n_rh (row, head) pairs.
 void launch_merge(const AttnParams &p, int nsplit, hipStream_t hs)
 {
@@ -2164,7 +2195,7 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     p.items_per_head = (int32_t)per_head;
     p.total_items = (int32_t)total;
     p.xcds_per_head = p.Hkv < kXcds && kXcds % p.Hkv == 0 ? kXcds / p.Hkv : 1;
-    if (p.batch % p.xcds_per_head == 0 && equal_lengths(shape)) p.xcds_per_head = 1;
+    if (p.xcds_per_head > 1 && contiguous_ranges(shape, pl, per_head, p.xcds_per_head)) p.xcds_per_head = 1;
     p.items_per_xcd = (int32_t)(p.xcds_per_head > 1 ? (per_head + p.xcds_per_head - 1) / p.xcds_per_head
                                                     : (total + kXcds - 1) / kXcds);
     p.scale_log2 = shape->softmax_scale * 1.4426950408889634f;

@@ -19,9 +19,11 @@ def H():
 
 
 @pytest.mark.parametrize("Hkv", [1, 2, 4, 8, 3])
-@pytest.mark.parametrize("P,E", [([40], [257]), ([0, 100, 7], [513, 1, 300]), ([64, 64], [300, 300])])
+@pytest.mark.parametrize("P,E", [([40], [257]), ([0, 100, 7], [513, 1, 300]), ([64, 64], [300, 300]),
+                                 ([64] * 9, [300] * 9), ([0] * 3, [1100] * 3)])
 def test_items_dealt_out_over_the_xcds(H, Hkv, P, E):
-    """Numbers of items that no number of XCDs divides, with several XCDs to a KV head and with one."""
+    """Numbers of items that no number of XCDs divides, with several XCDs to a KV head and with one; equal
+    requests in contiguous ranges and, where these would differ too much, dealt out."""
     w = W.make_uniform("items", 51, len(P), 3 * Hkv, Hkv, P, E)
     want = oracle.attention_of(w)
     for splits in (1, 3):
