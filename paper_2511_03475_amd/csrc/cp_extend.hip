@@ -1813,7 +1813,7 @@ void choose_decode_groups(const cp_shape *s, int64_t max_n, Plan &pl, double *es
 
 // A call of few rows and few keys, none of it enough for the device: the decode kernel with a workgroup per 32
 // rows, whose eight wavefronts share the keys and need no merge launch.  One round over the CUs only,
-// because every workgroup reads all keys itself.  `us`: the estimate of the way it would go otherwise.
+// because every workgroup reads all keys itself.  `us`: the estimate of the way it would go otherwise, then of this one.
 // Against row tiles in the best number of key ranges and a merge: P = 512, E = 128, 8/2 heads 15.7 -> 11.0 us;
 // P = 1500, E = 256, 32/8 heads 29.8 -> 21.1; 4 requests, P = 1000, E = 64 25.8 -> 15.3; P = 3000, E = 128, 8/2 heads
 // would take 27.4 instead of 25.9.  Four wavefronts instead of eight: 11.7 us for the first, 32.3 for the last.
@@ -1821,7 +1821,7 @@ constexpr double kSmallStartUs = 5.0, kSmallBlockUs = 2.0; // a workgroup; a blo
 // Of decode-shaped calls those with two row blocks and at most this many keys: 12 requests, 16 new tokens, 32/8
 // heads, P = 3546 34.7 us, 39.6 otherwise; 57, 9 new, 8/2 heads, P = 15646 250, which is more than estimated, and 171.
 constexpr int64_t kSmallDecodeKeys = 4096;
-bool small_call(const cp_shape *s, int64_t max_n, double us, Plan &pl)
+bool small_call(const cp_shape *s, int64_t max_n, double &us, Plan &pl)
 {
     const int G = s->num_q_heads / s->num_kv_heads;
     int64_t blocks = 0; // of rows, the most of a request
@@ -1832,6 +1832,7 @@ bool small_call(const cp_shape *s, int64_t max_n, double us, Plan &pl)
     if (blocks * s->batch * s->num_kv_heads > num_cus()) return false;
     const double length = std::ceil((double)((max_n + 31) / 32) / 8.0) * kSmallBlockUs;
     if (kSmallStartUs + length >= us) return false;
+    us = kSmallStartUs + length;
     pl.small = true;
     pl.dec_groups = 1;
     pl.row_blocks = (int32_t)blocks;
@@ -1883,10 +1884,7 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
     }
     double us;
     pl.nsplit = choose_splits(s, pl, room, &us);
-    if (small_call(s, max_n, us, pl)) {
-        pl.nsplit = 1;
-        return pl;
-    }
+    if (small_call(s, max_n, us, pl)) pl.nsplit = 1;
     if (s->batch <= kMixedMaxBatch && max_e > 0 && !equal_lengths(s)) {
         Plan mixed{0, 0, 1, false, 1};
         double mixed_us;

@@ -187,3 +187,28 @@ def test_two_blocks_of_rows_together_and_apart(H, B, Hkv, P, E):
     Es = [E - r % 4 if r % 6 != 5 else 0 for r in range(B)]
     w = W.make_uniform("two_blocks", 60, B, 4 * Hkv, Hkv, Ps, Es)
     _check(H.gpu_attention(w), oracle.attention_of(w), f"B={B} Hkv={Hkv} P={P} E={E}")
+
+
+@pytest.mark.parametrize("Hq,Hkv,P,E", [
+    (8, 2, [1806, 191, 1026, 2831, 250, 6836, 113], [21, 21, 24, 23, 22, 26, 20]),     # split request by request
+    (32, 8, [181, 99, 607, 1950, 821, 157, 4821, 6124], [1, 24, 23, 1, 1, 1, 1, 1]),
+    (8, 2, [4000, 10, 3000], [130, 1, 300]), (32, 8, [10240], [128]),                  # one number of ranges for all
+    (8, 2, [9000], [9]), (8, 2, [3000, 5, 0, 700], [1, 3, 2, 1]),                      # decode-shaped
+])
+def test_more_scratch_than_asked_for_changes_nothing(H, Hq, Hkv, P, E):
+    """cp_workspace_bytes is what the best plan takes: with exactly that much the same plan is made as with any
+    amount, bit for bit the same result."""
+    import torch
+
+    import paper_2511_03475_amd as cp
+
+    w = W.make_uniform("room", 61, len(P), Hq, Hkv, P, E)
+    case = H.DeviceCase(w)
+    assert case.ws_bytes > 0
+    case.attention()
+    want = case.out_bits().copy()
+    case.out.fill_(0x7FC1)
+    space = torch.empty(256 << 20, dtype=torch.uint8, device="cuda:0")
+    cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
+                           case.extend_lens, case.out, torch.cuda.current_stream(), case.shape, space, space.numel())
+    assert (case.out_bits() == want).all()
