@@ -182,7 +182,7 @@ def test_schedule_matches_oracle_on_random_paths():
 
 def test_many_equal_distances_and_rows_that_move_together():
     """Few different ids, so that most distances are equal, and enough contexts that the clustering moves the
-    remaining rows together several times; alpha = 0 leaves 1 - shared / length alone."""
+    remaining rows together once; alpha = 0 leaves 1 - shared / length alone."""
     rng = np.random.default_rng(77)
     for n, blocks, alpha in ((200, 9, ALPHA), (200, 14, 0.0), (131, 30, ALPHA)):
         contexts = [[int(x) for x in rng.permutation(blocks)[:rng.integers(1, 7)]] for _ in range(n)]
@@ -191,3 +191,44 @@ def test_many_equal_distances_and_rows_that_move_together():
         _same_tree(idx, ref)
         _same_contexts(idx, ref, n)
         idx.close()
+
+
+def _numpy_linkage(D):
+    """The oracle's clustering with whole rows at a time: active clusters in the order of their ids, so that the
+    first of equal smallest entries above the diagonal is the pair that the tie rule names."""
+    D = np.array(D, dtype=np.float64)
+    n = len(D)
+    D[np.tril_indices(n)] = np.inf
+    ids, sizes, merges = list(range(n)), [1] * n, []
+    for step in range(n - 1):
+        x, y = np.unravel_index(np.argmin(D), D.shape)
+        full = np.minimum(D, D.T)                          # infinite on the diagonal
+        row = (sizes[x] * full[x] + sizes[y] * full[y]) / (sizes[x] + sizes[y])
+        merges.append((ids[x], ids[y], float(D[x, y]), sizes[x] + sizes[y]))
+        keep = [k for k in range(len(ids)) if k not in (x, y)]
+        grown = np.full((len(keep) + 1, len(keep) + 1), np.inf)
+        grown[:-1, :-1] = D[np.ix_(keep, keep)]
+        grown[:-1, -1] = row[keep]
+        D = grown
+        sizes = [sizes[k] for k in keep] + [sizes[x] + sizes[y]]
+        ids = [ids[k] for k in keep] + [n + step]
+    return merges
+
+
+def test_large_index_with_many_equal_distances(monkeypatch):
+    """600 distinct contexts: a matrix on large pages, rows that move together three times (at 300, 150 and 75
+    clusters), distances of which most occur many times.  The oracle's clustering is replaced by the same with
+    numpy, after a check against it."""
+    rng = np.random.default_rng(78)
+    small = [[int(x) for x in rng.permutation(12)[:rng.integers(1, 6)]] for _ in range(50)]
+    D = CI.distance_matrix(small, ALPHA)
+    assert _numpy_linkage(D) == CI.linkage(D)
+    contexts = list({tuple(int(x) for x in rng.permutation(20)[:rng.integers(2, 7)]) for _ in range(640)})[:600]
+    contexts = [list(c) for c in contexts]
+    assert len(contexts) == 600
+    monkeypatch.setattr(CI, "linkage", _numpy_linkage)
+    C, L = _pack(contexts)
+    idx, ref = cp.ContextIndex(C, L, ALPHA), CI.ContextIndex.build(contexts, ALPHA)
+    _same_tree(idx, ref)
+    _same_contexts(idx, ref, len(contexts))
+    idx.close()
