@@ -31,29 +31,62 @@ def test_items_dealt_out_over_the_xcds(H, Hkv, P, E):
 
 
 @pytest.mark.parametrize("G,Hkv", [(4, 2), (8, 1), (1, 3), (4, 8)])
-@pytest.mark.parametrize("P,E", [
-    ([300, 40, 0, 1000], [1, 257, 16, 1]),                # decode-shaped requests next to a row tile and a bit
-    ([6000, 10, 3000, 0, 64], [1, 300, 4, 700, 65]),      # several key ranges for some requests, one for others
-    ([2000, 31, 32, 33, 0], [2, 1, 1, 1, 1]),             # blocks of 32 keys: remainders
-    ([4096, 50, 0], [0, 513, 1]),                         # a request without new tokens
-    ([190, 40, 7], [1, 59, 1]),                           # small: no key ranges at all, rows of some requests missing
-    ([50, 300, 120, 77, 190] * 5, [1, 1, 1, 1, 60] * 5),  # one range each is faster than ranges of their own
-    ([12000, 300, 500], [130, 130, 1]),                   # one long request in many ranges
+@pytest.mark.parametrize("P,E,without", [                 # without: the groups of heads that also run without scratch
+    ([300, 40, 0, 1000], [1, 257, 16, 1], (1,)),          # decode-shaped requests next to a row tile and a bit
+    ([6000, 10, 3000, 0, 64], [1, 300, 4, 700, 65], ()),  # several key ranges for some requests, one for others
+    ([2000, 31, 32, 33, 0], [2, 1, 1, 1, 1], ()),         # blocks of 32 keys: remainders
+    ([4096, 50, 0], [0, 513, 1], (1, 4, 8)),              # a request without new tokens
+    ([190, 40, 7], [1, 59, 1], (1, 4, 8)),                # small: no key ranges at all, rows of some requests missing
+    ([50, 300, 120, 77, 190] * 5, [1, 1, 1, 1, 60] * 5, (1, 4, 8)),   # one range each is faster than ranges of their own
+    ([12000, 300, 500], [130, 130, 1], ()),               # one long request in many ranges
 ])
-def test_batches_of_unequal_lengths(H, G, Hkv, P, E):
+def test_batches_of_unequal_lengths(H, G, Hkv, P, E, without):
     import paper_2511_03475_amd as cp
 
     w = W.make_uniform("mixed", 52, len(P), G * Hkv, Hkv, P, E)
     want = oracle.attention_of(w)
     case = H.DeviceCase(w)
     _check(H.gpu_attention(w), want, f"G={G} Hkv={Hkv} P={P} E={E}")
-    # without room for the partial results of its own plan the batch takes a plan that needs none, or
-    # is refused if every plan of its shape needs some
+    # without room for partial results a batch takes a plan that needs none, unless ranges of 8 key tiles would
+    # have to do without them: those calls are refused
     st = cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
                                 case.extend_lens, case.out, None, case.shape, None, 0, check=False)
-    assert st in (cp.CP_OK, cp.CP_ERR_WORKSPACE)
+    assert st == (cp.CP_OK if G in without else cp.CP_ERR_WORKSPACE)
     if st == cp.CP_OK:
         _check(case.out_bits(), want, f"no workspace G={G} Hkv={Hkv} P={P} E={E}")
+
+
+@pytest.mark.parametrize("P,E,Hq,Hkv,part,ok", [
+    ([3000], [128], 8, 2, 0.75, True), ([3000], [128], 8, 2, 0.5, True), ([3000], [128], 8, 2, 0.25, False),
+    ([1500] * 3, [40] * 3, 8, 2, 0.5, True), ([500] * 2, [600] * 2, 8, 2, 0.75, True),     # one number of ranges for all
+    ([500] * 2, [600] * 2, 8, 2, 0.5, False),
+    ([700, 1000, 1400, 900], [300, 1, 1, 300], 8, 2, 0.5, True),                           # unequal lengths
+    ([782, 64], [1, 254], 64, 8, 0.75, True), ([782, 64], [1, 254], 64, 8, 0.1, True),
+    ([12000, 300, 500], [130, 130, 1], 8, 2, 0.75, False),
+    ([9000], [9], 8, 2, 0.25, True), ([9000], [9], 8, 2, 0.1, False),                      # decode-shaped
+])
+def test_less_scratch_than_asked_for(H, P, E, Hq, Hkv, part, ok):
+    """A part of cp_workspace_bytes: the call takes a plan that fits and leaves what lies behind alone, or is
+    refused and leaves everything alone."""
+    import torch
+
+    import paper_2511_03475_amd as cp
+
+    w = W.make_uniform("part", 62, len(P), Hq, Hkv, P, E)
+    case = H.DeviceCase(w)
+    size = int(case.ws_bytes * part) // 256 * 256
+    assert 0 < size < case.ws_bytes
+    space = torch.full((case.ws_bytes + 4096,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    case.out.fill_(0x1234)
+    st = cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
+                                case.extend_lens, case.out, torch.cuda.current_stream(), case.shape, space, size, check=False)
+    assert st == (cp.CP_OK if ok else cp.CP_ERR_WORKSPACE)
+    got = case.out_bits()
+    assert (space[size if ok else 0:] == 0x5A).all()
+    if ok:
+        _check(got, oracle.attention_of(w), f"P={P} E={E} {part} of the scratch")
+    else:
+        assert (got == 0x1234).all()
 
 
 def test_more_requests_than_lanes(H):
