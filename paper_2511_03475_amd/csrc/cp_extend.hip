@@ -1763,11 +1763,12 @@ int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *es
 // Workgroups per (request, KV head) of a decode-shaped call: the least estimated time, returned in *estimate.  A
 // workgroup of four wavefronts reads up to kDecGroupBytesPerUs until all together reach kDecBytesPerUs,
 // and takes kDecStartUs to start and to end.  So some 160 workgroups read as fast as 2000 (1 request of
-// 131072 tokens, 8 KV heads: 16 per head 98 us, 24 88, 32 91, 64 93; 20 of 9000: 1 per head 117, 3 124, 4 126),
+// 131072 tokens, 8 KV heads: 17 per head 95 us, 22 88, 29 90, 50 95, 67 106; 20 of 9000: 1 per head 117, 3 124, 4 126),
 // and every one more is a partial result to merge.  Of those with one block of rows a CU holds two; CUs
 // with one less than others cost bandwidth (45 of 7000: 1 per head, 360, 217 us; 2 205; 3 220; 4 210).
 constexpr double kDecGroupBytesPerUs = 4.0e4, kDecBytesPerUs = 6.5e6;
 constexpr double kDecStartUs = 4.0, kDecMergeUs = 5.0, kDecMergeManyUs = 1.5;
+constexpr double kDecResolution = 0.995; // less of a gain than this the estimate cannot tell: fewer workgroups then
 // Two blocks of rows.  Together in a wavefront they read the keys once, but a CU holds one such workgroup, its start
 // and end take twice as long, and the next round begins when it ends (3 of 20000, 10 new tokens: 8 per
 // head, 192, 55 us; 12, 288, 81; 20, 480, 61).  Apart, a CU holds two, and the L2 serves the second if both are on one
@@ -1801,7 +1802,7 @@ void choose_decode_groups(const cp_shape *s, int64_t max_n, Plan &pl, double *es
             }
             if (groups > 1) us += (pl.row_blocks == 1 ? kDecMergeUs : kDec2MergeUs) + traffic;
             if (groups > kMergeFewSplits) us += kDecMergeManyUs;
-            if (best_us < 0.0 || us < best_us) {
+            if (best_us < 0.0 || us < kDecResolution * best_us) {
                 best_us = us;
                 pl.dec_groups = groups;
                 pl.dec_share = share;
