@@ -21,7 +21,7 @@ HIPCC_FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # the attention kernel's loop over key tiles (2.7 KB) begins where an instruction cache line does: 8 requests,
     # P = 6144, E = 2304, 32/8 heads 1943 -> 1930 us; without it that depends on the code in front
-    "-falign-loops=64",
+    "-Xarch_device", "-falign-loops=64",
 ]
 
 

@@ -5,7 +5,7 @@
 //   extend_attn_kernel    suffix rows attend to cached prefix pages + their own K/V
 //                         (paper, Section 1 / Section 2.1: prefill over a prefix cache); in batches of
 //                         unequal lengths also the decode-shaped requests, next to the others
-//   decode_attn_kernel    the same for calls with few rows per KV head (a wavefront per key chunk)
+//   decode_attn_kernel    the same for calls with few rows per KV head or few keys (wavefronts share the keys)
 //   merge_splits_kernel, merge_few_splits_kernel, merge_mixed_kernel   combine partial results over key ranges
 //   check_tables_kernel   optional check of block_table against the pool size
 //
@@ -241,8 +241,8 @@ constexpr int kDecPitchK = 272;
 constexpr int kDecPitchV = 320;
 constexpr int kDecLdsK = 32 * kDecPitchK;
 constexpr int kDecLdsPerWave = kDecLdsK + 32 * kDecPitchV;
-constexpr int kDecLeastWaves = 4;       // a call is planned in key chunks of wavefronts, a multiple of the smallest workgroup
-constexpr int kDecMaxChunks = 256;      // key chunks (= partial results) per (request, KV head)
+constexpr int kDecLeastWaves = 4;       // wavefronts of the smallest workgroup
+constexpr int kDecMaxChunks = 256;      // partial results per (request, KV head), at most
 
 struct DecBlock { // one block of 32 keys as loaded: piece i is row (lane / 16) + 4 i, chunk lane % 16
     u32x4 k[8];
@@ -329,7 +329,7 @@ __device__ __forceinline__ void decode_keys(const AttnParams &p, char *lds_k, in
             *reinterpret_cast<u32x4 *>(lds_v + st_v + 4 * i * kDecPitchV) = blk.v[i];
         }
     };
-    // operand reads, as in the kernel above
+    // operand reads, as in the row-tiled kernel below, with padded rows instead of swizzled ones
     const int k_lane = j * kDecPitchK + h * 16;
     const int v_lane = (4 * h + ((lane & 15) >> 2)) * kDecPitchV + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
 
@@ -681,30 +681,30 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
         unit = rem / nsplit;
         r = p.batch;
         cu = E = P = 0;
-    // Units of a KV head: requests in order; within a request the last (longest) row tile
-    // first, and for each row tile the groups of q heads that are packed into one workgroup.
-    // The request that owns the unit is found 64 requests at a time: every lane takes one
-    // request, a prefix sum over the wavefront gives the first unit of each (a sequential scan
-    // costs a dependent scalar load and several integer divisions per request, ~1.5 us each).
-    for (int base = 0; base < p.batch; base += 64) {
-        const int rr = base + lane;
-        const int e_l = rr < p.batch ? p.extend_lens[rr] : 0;
-        const int units_l = units_of_request(e_l, p.G, heads_per_tile(e_l, p.G));
-        const int incl_u = wave_inclusive_scan(units_l, lane);
-        const int incl_e = wave_inclusive_scan(e_l, lane);
-        const int total_u = __builtin_amdgcn_readlane(incl_u, 63);
-        if (unit < total_u) {
-            const int first = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl_u > unit));
-            r = base + first;
-            unit -= __builtin_amdgcn_readlane(incl_u - units_l, first);
-            cu += __builtin_amdgcn_readlane(incl_e - e_l, first);
-            E = __builtin_amdgcn_readlane(e_l, first);
-            break;
+        // Units of a KV head: requests in order; within a request the last (longest) row tile
+        // first, and for each row tile the groups of q heads that are packed into one workgroup.
+        // The request that owns the unit is found 64 requests at a time: every lane takes one
+        // request, a prefix sum over the wavefront gives the first unit of each (a sequential scan
+        // costs a dependent scalar load and several integer divisions per request, ~1.5 us each).
+        for (int base = 0; base < p.batch; base += 64) {
+            const int rr = base + lane;
+            const int e_l = rr < p.batch ? p.extend_lens[rr] : 0;
+            const int units_l = units_of_request(e_l, p.G, heads_per_tile(e_l, p.G));
+            const int incl_u = wave_inclusive_scan(units_l, lane);
+            const int incl_e = wave_inclusive_scan(e_l, lane);
+            const int total_u = __builtin_amdgcn_readlane(incl_u, 63);
+            if (unit < total_u) {
+                const int first = __builtin_ctzll(__builtin_amdgcn_ballot_w64(incl_u > unit));
+                r = base + first;
+                unit -= __builtin_amdgcn_readlane(incl_u - units_l, first);
+                cu += __builtin_amdgcn_readlane(incl_e - e_l, first);
+                E = __builtin_amdgcn_readlane(e_l, first);
+                break;
+            }
+            unit -= total_u;
+            cu += __builtin_amdgcn_readlane(incl_e, 63);
         }
-        unit -= total_u;
-        cu += __builtin_amdgcn_readlane(incl_e, 63);
-    }
-    if (r < p.batch) P = p.prefix_lens[r];
+        if (r < p.batch) P = p.prefix_lens[r];
     }
     if (r >= p.batch) return;
     const int pack = heads_per_tile(E, p.G);
@@ -1860,9 +1860,9 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
         max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
     }
     if (s->num_splits == 0 && max_e > 0 && max_e * G <= kDecRows * kDecMaxRowBlocks) {
-        // Decode-shaped: one wavefront per (request, KV head, 32 rows, key chunk).  Enough chunks
-        // for 8 wavefronts per CU, at least 2 blocks of 32 keys each, a multiple of the workgroup
-        // size.
+        // Decode-shaped.  nsplit bounds the workgroups that may share a request's keys, and is what the
+        // queries report: key chunks for 8 wavefronts per CU, at least 2 blocks of 32 keys each, a
+        // multiple of the wavefronts of a workgroup.
         pl.row_blocks = (int32_t)((max_e * G + kDecRows - 1) / kDecRows);
         const int64_t pairs = (int64_t)s->batch * s->num_kv_heads * pl.row_blocks;
         int64_t ns = (8LL * num_cus() + pairs - 1) / pairs;
