@@ -1772,9 +1772,9 @@ constexpr double kDecResolution = 0.995; // less of a gain than this the estimat
 // Two blocks of rows.  Together in a wavefront they read the keys once, but a CU holds one such workgroup, its start
 // and end take twice as long, and the next round begins when it ends (3 of 20000, 10 new tokens: 8 per
 // head, 192, 55 us; 12, 288, 81; 20, 480, 61).  Apart, a CU holds two, and the L2 serves the second if both are on one
-// XCD, for which their number has to be a multiple of the XCDs.  Together is better where the memory bounds the call (32 requests of 10240, 16
-// new: 222 us, apart 234; 25 of 9173, 7 new, 64/8 heads 174, 182), apart where the chain of blocks does
-// (1 of 46, 14 new, 8/2 heads 10.8, 7.5; 33 of 1544, 10 new 72, 60; 2 of 23880, 12 new 50, 37).
+// XCD, for which their number has to be a multiple of the XCDs.  Together is better where the memory bounds the call (28 requests of 6494, 15
+// new, 32/8 heads 136 us, apart 142; 25 of 9173, 7 new, 64/8 heads 174 and 182), apart where the chain of blocks
+// does (32/8 heads: 3 of 48, 14 new 11.2 and 7.5; 48 of 1906, 14 new 94 and 76; 2 of 23880, 12 new 50 and 37).
 constexpr double kDec2ApartBytesPerUs = 5.8e4, kDec2ApartStartUs = 4.4, kDec2ApartRoundUs = 2.0, kDec2ApartTwice = 1.6;
 constexpr double kDec2BytesPerUs = 3.1e4, kDec2MemoryBytesPerUs = 7.0e6, kDec2StartUs = 4.2, kDec2RoundUs = 4.6, kDec2MergeUs = 2.0;
 void choose_decode_groups(const cp_shape *s, int64_t max_n, Plan &pl, double *estimate)
@@ -1896,7 +1896,7 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
 
 // Whether XCDs that share a KV head take a contiguous range of its items each (see work_item): for equal requests, if
 // no range takes more than 6 % longer than the mean.  Then the XCDs stream different keys; dealt out, all the same
-// ones.  9 requests, P = 5548, E = 817, 8/2 heads 234 us, dealt out 293; 20, P = 0, E = 1511 122 and 137; but with a
+// ones.  9 requests, P = 5548, E = 817, 8/2 heads 260 us, dealt out 301; 20, P = 0, E = 1511 122 and 137; but with a
 // range 15 % over the mean (3 requests, P = 0, E = 5067, 16/4 heads) 342, dealt out 303.
 constexpr double kContiguousExcess = 1.06;
 bool contiguous_ranges(const cp_shape *s, const Plan &pl, int64_t items, int xcds)
