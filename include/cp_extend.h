@@ -128,7 +128,8 @@ int32_t cp_plan_kind(const cp_shape *shape);
  * workspace: DEVICE scratch of cp_workspace_bytes(shape) bytes, 256-byte aligned; may be NULL when
  * that size is 0.  With less, a call that is not decode-shaped and leaves num_splits at 0 takes a plan
  * that fits (not bit for bit the same result), down to the partial results of key ranges of 8 tiles
- * of 64 keys for two workgroups per compute unit; a decode-shaped call runs the same with what its
+ * of 64 keys for two workgroups per compute unit (in a batch of unequal lengths, if that is less, of every
+ * request split by its own length); a decode-shaped call runs the same with what its
  * workgroups leave behind, nothing where one has all keys of a request; below that, and any other call,
  * is refused, and so is a buffer that the plan for its size uses and that is not aligned.  Its contents are undefined afterwards.
  * Requests with E_r = 0 produce no rows.  Asynchronous on `stream`.

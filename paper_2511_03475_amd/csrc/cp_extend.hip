@@ -1722,9 +1722,9 @@ constexpr double kLastItem = 0.75; // of its length, behind the others
 int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *estimate)
 {
     const int64_t items = pl.q_tiles * s->num_kv_heads, cus = num_cus();
-    const bool equal = equal_lengths(s);
+    const bool mixed = s->batch <= kMixedMaxBatch && !equal_lengths(s); // a plan to compare this one with
     *estimate = 0.0;
-    if (items >= 2 * cus && (equal || s->batch > kMixedMaxBatch)) return 1; // nothing to compare it with
+    if (items >= 2 * cus && !mixed) return 1;
     const int G = s->num_q_heads / s->num_kv_heads;
     double tiles = 0.0; // key tiles of all items
     bool alike = true;
@@ -1739,14 +1739,14 @@ int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *es
     }
     int32_t best = 1;
     double best_us = 0.0;
-    const int32_t most = items >= 2 * cus ? 1 : std::min(equal ? kMaxSplits : kMergeSomeSplits, std::max(1, pl.max_key_tiles / 2));
+    const int32_t most = items >= 2 * cus ? 1 : std::min(mixed ? kMergeSomeSplits : kMaxSplits, std::max(1, pl.max_key_tiles / 2));
     for (int32_t ns = 1; ns <= most; ++ns) {
         const size_t bytes = ns > 1 ? part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) : 0;
         if (bytes > room) break;
         const double longest = kItemUs + kTileUs * ((pl.max_key_tiles + ns - 1) / ns);
         const double mean = kItemUs + kTileUs * tiles / ((double)items * ns);
         double us = longest;
-        if (items * ns > cus && !equal)
+        if (items * ns > cus && mixed)
             us = std::max(us, mean * ((double)(items * ns) / (double)cus) + kLastItem * longest);
         else if (items * ns > cus)
             us = std::max(us, alike ? (double)((items * ns + cus - 1) / cus) * mean : mean * ((double)(items * ns) / (double)cus + 0.5));
@@ -1964,8 +1964,8 @@ size_t scratch_used(const cp_shape *s, const Plan &pl)
 
 // Whether a call with `room` bytes of scratch and the plan pl made for them is refused: the plan needs more, or
 // the call is not decode-shaped, brings less than its best plan wants and also less than key ranges of
-// at least 8 tiles, for two workgroups per CU, take.  Plans without partial results exist for it, but
-// would run several times slower than the call can, without a word.
+// at least 8 tiles, for two workgroups per CU, take, or than a split request by request does.  Plans
+// without partial results exist for it, but would run several times slower than the call can, without a word.
 bool too_little_scratch(const cp_shape *s, const Plan &pl, size_t room)
 {
     if (scratch_used(s, pl) > room) return true;
@@ -1977,7 +1977,10 @@ bool too_little_scratch(const cp_shape *s, const Plan &pl, size_t room)
     int64_t ns = items > 0 && items < want ? (want + items - 1) / items : 1;
     ns = std::min<int64_t>({ns, max_key_tiles / 8, kMaxSplits});
     if (ns <= 1 || part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) <= room) return false;
-    return workspace_for(s, make_plan(s)) > room;
+    if (workspace_for(s, make_plan(s)) <= room) return false;
+    Plan mixed{0, 0, 1, false, 1};
+    double us;
+    return s->batch > kMixedMaxBatch || equal_lengths(s) || !plan_mixed(s, SIZE_MAX, mixed, nullptr, &us) || workspace_for(s, mixed) > room;
 }
 
 inline bool aligned_to(const void *p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }

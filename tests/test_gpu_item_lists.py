@@ -63,6 +63,7 @@ def test_batches_of_unequal_lengths(H, G, Hkv, P, E, without):
     ([700, 1000, 1400, 900], [300, 1, 1, 300], 8, 2, 0.5, True),                           # unequal lengths
     ([782, 64], [1, 254], 64, 8, 0.75, True), ([782, 64], [1, 254], 64, 8, 0.1, True),
     ([12000, 300, 500], [130, 130, 1], 8, 2, 0.75, False),
+    ([3763, 1178], [1, 47], 10, 2, 0.379, True),          # a split request by request, which takes less than the best plan
     ([9000], [9], 8, 2, 0.25, True), ([9000], [9], 8, 2, 0.1, False),                      # decode-shaped
 ])
 def test_less_scratch_than_asked_for(H, P, E, Hq, Hkv, part, ok):
