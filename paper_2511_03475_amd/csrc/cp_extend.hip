@@ -9,8 +9,8 @@
 //   merge_splits_kernel, merge_few_splits_kernel, merge_mixed_kernel   combine partial results over key ranges
 //   check_tables_kernel   optional check of block_table against the pool size
 //
-// Attention kernel layout.  One workgroup = 8 wavefronts = 256 query rows of one q head; each
-// wavefront owns 32 rows.  Keys are streamed in tiles of 64 through LDS.  Scores are computed
+// Attention kernel layout.  One workgroup = 8 wavefronts = 256 (token, q head) rows of one KV
+// head; each wavefront owns 32 rows.  Keys are streamed in tiles of 64 through LDS.  Scores are computed
 // transposed, S^T = K Q^T, with v_mfma_f32_32x32x16_bf16 so that the accumulator lane
 // (lane % 32) is a query row: the softmax row reductions are then in-lane plus one exchange
 // between the two half-waves, the bf16 probabilities already sit in the B-operand layout of the
@@ -35,7 +35,8 @@ namespace {
 
 constexpr int kD = 128;       // head dim
 constexpr int kPS = 16;       // tokens per page
-constexpr int kBM = 256;      // query rows per workgroup
+constexpr int kBM = 256;      // query rows per workgroup, at most
+constexpr int kTileShift = 8; // its logarithm
 constexpr int kBN = 64;       // keys per tile
 constexpr int kThreads = 512; // 8 wavefronts
 constexpr int kXcds = 8;      // accelerator complex dies; workgroup ids round-robin over them
@@ -43,7 +44,7 @@ constexpr int kMaxSplits = 64;
 constexpr int kWaves = kThreads / 64;
 constexpr int kNKB = kBN / 32;            // 32-key blocks per tile
 constexpr int kLoadRows = kWaves * 4;     // key rows one load step of the workgroup covers
-static_assert(kBM == kWaves * 32 && kBN == 2 * kLoadRows, "tile shape");
+static_assert(kBM == kWaves * 32 && kBM == 1 << kTileShift && kBN == 2 * kLoadRows, "tile shape");
 
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) __bf16 bf16x4;
@@ -64,16 +65,22 @@ struct AttnParams {
     const int32_t *prefix_lens;
     const int32_t *extend_lens;
     uint16_t *out;
-    float *part_o;  // [nsplit][T][Hq][D]   unnormalised partial outputs (mixed: [part_rows][Hq][D])
+    float *part_o;  // [nsplit][T][Hq][D]   unnormalised partial outputs (mixed: [part_rows][Hq][D];
+                    // tail: [Hkv][tail_units][nsplit][kBM][D])
     float *part_ml; // [nsplit][T][Hq][2]   running max (log2 domain) and sum
     int32_t batch, Hq, Hkv, G, max_pages, T;
     int32_t nsplit;
+    int32_t whole_units;    // row tiles of a KV head in front of those that are split (all requests equal), else 0
+    int32_t tail_units;     // ... and those that are, 0: all or none
+    int32_t alternate;      // see row_tile_of
+    int32_t tile_shift;     // rows of a tile: 1 << tile_shift
     int32_t dec_row_blocks; // decode kernel: blocks of 32 (head, token) rows per (request, KV head)
-    int32_t items_per_head; // work units per KV head * nsplit
+    int32_t items_per_head; // work items per KV head
     int32_t total_items;    // items_per_head * Hkv
     int32_t items_per_xcd;  // list positions of each XCD, see work_item
     int32_t xcds_per_head;  // XCDs that share the items of one KV head
     float scale_log2;       // softmax_scale * log2(e)
+    uint32_t g_magic;       // see over_heads, 0: plain division
 };
 constexpr int kMixedMaxBatch = 512; // requests of a mixed batch; beyond, planning costs the host more than the call takes
 struct MixedParams : AttnParams {
@@ -120,22 +127,31 @@ __device__ __forceinline__ int work_item(int bid, const AttnParams &p, int &kvh)
     return item - kvh * p.items_per_head;
 }
 
-// Number of q heads of one KV head that share a workgroup (GQA head sharing): short extends
-// leave most of a 256-row tile empty, so the rows of up to 8 heads are packed into it.  The
-// largest power of two that divides G and still gives every head enough rows for E.
-__host__ __device__ inline int heads_per_tile(int E, int G)
+// n / G: a multiplication where the host says that it is exact for every row of the call, (n + 1) G <= 2^32 with
+// g_magic = floor((2^32 - 1) / G).  A division by a number that the compiler does not know takes some 40
+// instructions, and an item starts with four of them.
+__device__ __forceinline__ int over_heads(int n, const AttnParams &p)
 {
-    int pack = 1;
-    while (pack < 8 && (G & (2 * pack - 1)) == 0 && E * (pack * 2) <= kBM) pack *= 2;
-    return pack;
+    return p.g_magic ? (int)__umulhi((uint32_t)n + 1u, p.g_magic) : n / p.G;
 }
-// Work units (row tiles x head groups) of one request for one KV head; pack = heads_per_tile.
-__host__ __device__ inline int units_of_request(int E, int G, int pack)
+// Row tiles of one request for one KV head: its E x G (token, q head) rows, token by token and within a token
+// head by head, are cut into tiles of 1 << shift.  So only a request's last tile can hold padding, whatever E and G are,
+// all rows of a tile end at about the same key, and the rows of a token lie side by side in q and out.  Before, a tile
+// took rows of 1, 2, 4 or 8 whole heads: 9 requests, P = 190, E = 190, 32/8 heads (36 tiles, now 27) 33.5 -> 21.6 us; 40
+// requests of which 8 bring 34 to 582 tokens 141 -> 135.
+__host__ __device__ inline int64_t row_tiles(int E, int G, int shift)
 {
-    if (E <= 0) return 0;
-    int shift = 0;
-    while ((1 << shift) < pack) ++shift;
-    return ((E * pack + kBM - 1) / kBM) * (G >> shift);
+    return E <= 0 ? 0 : ((int64_t)E * G + (1 << shift) - 1) >> shift;
+}
+constexpr int kAlternateRounds = 16;
+// Row tile of a request for its unit-th work unit.  The longest first, so that the last items of the list are
+// short.  In a batch of equal requests every second one takes the shortest first: a CU that has had longer items
+// of one request than others has shorter ones of the next, while the list stays request by request, which the
+// L2 wants.  8 requests, P = 6144, E = 2304, 32/8 heads (36 items a CU group of 32, 97 to 132 key tiles): 1982
+// -> 1906 us; calls of more than kAlternateRounds items a CU gain nothing and stay as they are.
+__device__ __forceinline__ int row_tile_of(int unit, int nt, int r, int batch, int alternate)
+{
+    return alternate && ((batch - r) & 1) == 0 ? unit : nt - 1 - unit;
 }
 // Few new tokens: the rows of a KV head (G heads x E tokens) fit into kDecMaxRowBlocks blocks.
 constexpr int kDecRows = 32;        // (head, token) rows per wavefront
@@ -175,7 +191,7 @@ struct Owner {
     int splits; // its key ranges
 };
 // The request that owns position `at` of a list of units.  kDecode: the decode-shaped requests, row
-// blocks x key chunks each.  Otherwise the row-tiled requests, row tiles x head groups x key ranges
+// blocks x key chunks each.  Otherwise the row-tiled requests, row tiles x key ranges
 // each.  The list takes the requests of a group of 64 in the order that the host gives (most keys
 // first, so that the items that start last are short).  Every lane takes one request; the first unit
 // of each is a sum over the lanes.
@@ -191,7 +207,7 @@ __device__ __forceinline__ Owner find_owner(int at, const MixedParams &p, int la
         const int ns = splits_of_request(pl, e, p.G, p.seg_tiles, p.dec_blocks);
         int units = 0;
         if (e > 0 && decode_shaped(e, p.G) == kDecode)
-            units = (kDecode ? (e * p.G + kDecRows - 1) / kDecRows : units_of_request(e, p.G, heads_per_tile(e, p.G))) * ns;
+            units = (kDecode ? (e * p.G + kDecRows - 1) / kDecRows : (int)row_tiles(e, p.G, p.tile_shift)) * ns;
         const int sorted = __shfl(units, from, 64);
         const int incl = wave_inclusive_scan(sorted, lane);
         const int parts = ns > 1 ? ns * e : 0;
@@ -676,20 +692,26 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
         split = w.unit % nsplit;
         unit = w.unit / nsplit;
     } else {
-        nsplit = p.nsplit;
-        split = rem % nsplit;
-        unit = rem / nsplit;
+        nsplit = 1;
+        split = 0;
+        unit = rem;
+        if (kMode == kSplit && rem >= p.whole_units) {
+            nsplit = p.nsplit;
+            const int piece = rem - p.whole_units;
+            unit = p.whole_units + piece / nsplit;
+            split = piece % nsplit;
+        }
+        const int tail_unit = unit - p.whole_units;
         r = p.batch;
         cu = E = P = 0;
-        // Units of a KV head: requests in order; within a request the last (longest) row tile
-        // first, and for each row tile the groups of q heads that are packed into one workgroup.
+        // Units of a KV head: requests in order; within a request the last (longest) row tile first.
         // The request that owns the unit is found 64 requests at a time: every lane takes one
         // request, a prefix sum over the wavefront gives the first unit of each (a sequential scan
         // costs a dependent scalar load and several integer divisions per request, ~1.5 us each).
         for (int base = 0; base < p.batch; base += 64) {
             const int rr = base + lane;
             const int e_l = rr < p.batch ? p.extend_lens[rr] : 0;
-            const int units_l = units_of_request(e_l, p.G, heads_per_tile(e_l, p.G));
+            const int units_l = (int)row_tiles(e_l, p.G, p.tile_shift);
             const int incl_u = wave_inclusive_scan(units_l, lane);
             const int incl_e = wave_inclusive_scan(e_l, lane);
             const int total_u = __builtin_amdgcn_readlane(incl_u, 63);
@@ -705,24 +727,22 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
             cu += __builtin_amdgcn_readlane(incl_e, 63);
         }
         if (r < p.batch) P = p.prefix_lens[r];
+        if (p.tail_units > 0) parts = ((kvh * p.tail_units + tail_unit) * nsplit + split) * kBM + wave * 32;
     }
     if (r >= p.batch) return;
-    const int pack = heads_per_tile(E, p.G);
-    int shift = 0;
-    while ((1 << shift) < pack) ++shift;
-    const int groups = p.G >> shift;
-    const int nt = (E * pack + kBM - 1) / kBM; // row tiles of kBM / pack rows
-    const int hgroup = unit % groups;
-    const int t = nt - 1 - unit / groups;
+    const int t = row_tile_of(unit, (int)row_tiles(E, p.G, p.tile_shift), r, p.batch, kMode != kMixed && p.alternate);
 
-    // GQA head sharing: `pack` q heads of the KV head share the workgroup's K/V tiles, each
-    // with kBM / pack query rows; a wavefront belongs to exactly one of them.
-    const int rows_per_head = kBM / pack;
-    const int head = kvh * p.G + hgroup * pack + (wave * 32) / rows_per_head;
-    const int q0 = t * rows_per_head;                          // first extend row of the tile
-    const int wave_row0 = q0 + (wave * 32) % rows_per_head;    // first row of this wavefront
-    const int row_i = wave_row0 + j;                           // this lane's extend row (may be >= E)
-    const int rows_end = min(E, q0 + rows_per_head);           // one past the last valid row
+    // Row i of the (request, KV head) is token i / G for q head i % G of the group; the q heads of the KV
+    // head thus share the workgroup's K/V tiles.
+    const int rows = E * p.G;
+    const int tile_end = min(rows, (t + 1) << p.tile_shift);   // one past the tile's last row
+    const int wave_row0 = (t << p.tile_shift) + wave * 32;     // first row of this wavefront
+    const int wave_tok0 = over_heads(wave_row0, p);            // its token
+    const int wave_tok1 = over_heads(wave_row0 + 31, p);       // token of the last row (may be >= E)
+    const bool row_valid = wave_row0 + j < tile_end;
+    const int row_tok = over_heads(min(wave_row0 + j, rows - 1), p); // this lane's token
+    const int head = kvh * p.G + min(wave_row0 + j, rows - 1) - row_tok * p.G;
+    const int rows_end = over_heads(tile_end - 1, p) + 1; // one past the tile's last token
     const int np_tiles = (P + kBN - 1) / kBN;        // prefix key tiles
     const int ns_tiles = (rows_end + kBN - 1) / kBN; // suffix key tiles up to the diagonal
     const int n_tiles = np_tiles + ns_tiles;
@@ -734,15 +754,18 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
     const int kt_end = min(n_tiles, kt_begin + per_split);
     const int n_it = kt_end - kt_begin;              // key tiles of this work item
 
-    const int64_t out_row = (int64_t)(cu + min(row_i, E - 1));
-    const bool row_valid = row_i < E;
-    const bool partial = kMode == kMixed ? nsplit > 1 : kMode == kSplit;
-    auto part_row = [&] { return kMode == kMixed ? parts + (int64_t)split * E + row_i : (int64_t)split * p.T + out_row; };
+    const int64_t out_row = (int64_t)(cu + row_tok);
+    const bool partial = kMode != kWhole && nsplit > 1;
+    // row of the partial results
+    auto part_row = [&]() -> int64_t {
+        if (kMode == kSplit && p.tail_units > 0) return parts + j;
+        return (kMode == kMixed ? parts + (int64_t)split * E + row_tok : (int64_t)split * p.T + out_row) * p.Hq + head;
+    };
 
     if (n_it <= 0) {
         // empty split: the merge skips entries whose sum is zero
         if (partial && row_valid && h == 0) {
-            float *ml = p.part_ml + (part_row() * p.Hq + head) * 2;
+            float *ml = p.part_ml + part_row() * 2;
             ml[0] = -INFINITY;
             ml[1] = 0.f;
         }
@@ -869,18 +892,18 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
 
     // ---- per-lane LDS read offsets (bytes inside a tile buffer)
     // K, A operand of S^T: lane (j, h) reads 16 bytes of key row kb*32 + j at chunk 2 kk + h,
-    // which the swizzle puts at slot (2 kk + h) ^ (j & 15): one offset per kk.
-    int k_lane[8];
-#pragma unroll
-    for (int kk = 0; kk < 8; ++kk) k_lane[kk] = j * kPitchK + (((2 * kk + h) ^ (j & 15)) << 4);
+    // which the swizzle puts at slot (2 kk + h) ^ (j & 15): the offset for kk = 0 with bits 5 to 7
+    // exchanged.  Eight offsets kept in registers cost no fewer instructions (the buffer is added to each)
+    // and leave the loop short of registers.
+    const int k_lane = j * kPitchK + ((h ^ (j & 15)) << 4);
     // V^T, A operand of O^T = V^T P^T, through the transposing read: within a group of 16
     // lanes, lane i supplies the address of 4 consecutive d of key row k0 + i / 4 and receives
     // V[k0 .. k0+3][d0 + i].  Here k0 = 4 h (+ 8 for the second read), d0 = 32 db + 16 (lane/16 % 2);
-    // the swizzle exchanges the 64-byte column blocks: block db of row r sits at db ^ (r & 3).
-    int v_lane[4];
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-        v_lane[db] = (4 * h + ((lane & 15) >> 2)) * kPitchV + ((db ^ ((lane >> 2) & 3)) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    // the swizzle exchanges the 64-byte column blocks: block db of row r sits at db ^ (r & 3), the
+    // offset for db = 0 with bits 6 and 7 exchanged.
+    const int v_lane = (4 * h + ((lane & 15) >> 2)) * kPitchV + (((lane >> 2) & 3) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
+    typedef __attribute__((address_space(3))) const char *lptr;
+    const uint32_t lds_k0 = (uint32_t)(uintptr_t)(lptr)lds_k, lds_v0 = (uint32_t)(uintptr_t)(lptr)lds_v; // multiples of 256
 
     f32x16 o[4];
 #pragma unroll
@@ -896,15 +919,16 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
 
     // S^T = K Q^T for the tile in K buffer kbuf.
     auto qk_tile = [&](int kbuf, STile &s) {
-        const char *kb = lds_k + kbuf * kTileBytesK;
+        const uint32_t kb = lds_k0 + kbuf * kTileBytesK + k_lane;
         const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int b = 0; b < kNKB; ++b) s[b] = zero;
 #pragma unroll
         for (int kk = 0; kk < 8; ++kk) {
 #pragma unroll
-            for (int b = 0; b < kNKB; ++b) {
-                const u32x4 a = *reinterpret_cast<const u32x4 *>(kb + k_lane[kk] + b * 32 * kPitchK);
+            for (int bb = 0; bb < kNKB; ++bb) {
+                const int b = kk >= 4 ? kNKB - 1 - bb : bb;
+                const u32x4 a = *reinterpret_cast<__attribute__((address_space(3))) const u32x4 *>((lptr)(uintptr_t)(kb ^ (kk << 5)) + b * 32 * kPitchK);
                 s[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), qf[kk], s[b], 0, 0, 0);
             }
         }
@@ -922,12 +946,12 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
     };
     // O^T += V^T P^T for the tile in V buffer vbuf: 4 d blocks x steps of 16 keys.
     auto pv_tile = [&](int vbuf, const PTile &pb) {
-        const char *vb = lds_v + vbuf * kTileBytesV;
+        const uint32_t vb = lds_v0 + vbuf * kTileBytesV + v_lane;
 #pragma unroll
         for (int ks = 0; ks < 2 * kNKB; ++ks) { // keys ks*16 .. ks*16+15
 #pragma unroll
             for (int db = 0; db < 4; ++db) {
-                const char *a = vb + v_lane[db] + ks * 16 * kPitchV;
+                const lptr a = (lptr)(uintptr_t)(vb ^ (db << 6)) + ks * 16 * kPitchV;
                 const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
                     (__attribute__((address_space(3))) s16x4 *)(a));
                 const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -975,10 +999,21 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
                 x[0] = fast_exp2(kPlain ? s0 : s0 - m_use);
                 x[1] = fast_exp2(kPlain ? s1 : s1 - m_use);
                 const bf16x2 y = __builtin_convertvector(x, bf16x2);
-                psum = __builtin_amdgcn_fdot2_f32_bf16(y, ones, psum, false);
                 pb[t][e] = y[0];
                 pb[t][e + 1] = y[1];
             }
+        // The row sums come after all conversions (the empty statement says so): mixed with them by the scheduler they
+        // wait for each other between the last MFMAs of P V (4 requests, P = 24576, E = 8192, 64/8 heads 25.5 -> 25.2 ms).
+        u32x4 w[2 * kNKB];
+#pragma unroll
+        for (int t = 0; t < 2 * kNKB; ++t) w[t] = __builtin_bit_cast(u32x4, pb[t]);
+        asm("" : "+v"(w[0]), "+v"(w[1]), "+v"(w[2]), "+v"(w[3]));
+#pragma unroll
+        for (int t = 0; t < 2 * kNKB; ++t) pb[t] = __builtin_bit_cast(bf16x8, w[t]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < 2 * kNKB; ++t) psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, (unsigned)w[t][e]), ones, psum, false);
         return psum;
     };
     auto row_max = [&](const STile &s) -> float {
@@ -1036,14 +1071,14 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
         const bool suffix = kt >= np_tiles;
         const int key0 = tile_key0(kt);
         qk_tile(buf, s);
-        const bool need_mask = suffix ? (key0 + kBN - 1 > wave_row0) : (key0 + kBN > P);
-        if (need_mask) mask_tile(suffix ? (row_i - key0 + 1) : (P - key0), s);
+        const bool need_mask = suffix ? (key0 + kBN - 1 > wave_tok0) : (key0 + kBN > P);
+        if (need_mask) mask_tile(suffix ? (row_tok - key0 + 1) : (P - key0), s);
     };
     // a suffix tile entirely above this wavefront's rows shows it nothing, and neither does
     // any later tile; a wavefront whose 32 rows all lie past the end of the request (short
     // extends, decode) computes nothing at all and only takes part in the cooperative loads
-    const bool no_rows = wave_row0 >= E;
-    auto skipped = [&](int kt) { return no_rows || (kt >= np_tiles && tile_key0(kt) > wave_row0 + 31); };
+    const bool no_rows = wave_row0 >= tile_end;
+    auto skipped = [&](int kt) { return no_rows || (kt >= np_tiles && tile_key0(kt) > wave_tok1); };
 
     PTile pb_a, pb_b; // probabilities of the previous / the current tile
 
@@ -1092,65 +1127,66 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
         // case distinctions, and the block-table entries of a tile are fetched one iteration
         // before its loads are issued (the general step spends ~500 of ~4200 cycles per tile
         // between the barrier and its first MFMA on tile kinds, table lookups and addresses,
-        // with the matrix pipe idle).
-        int fast_end;
-        if (P % kBN == 0) {
-            const int last_unmasked = np_tiles + (wave_row0 >= kBN - 1 ? (wave_row0 - (kBN - 1)) / kBN : -1);
+        // with the matrix pipe idle).  A prefix that ends inside a tile leaves two such stretches, with the
+        // general step between them (P = 777, E = 16000, 32/8 heads: 2038 -> 1927 us with the second one).
+        for (;;) {
+            const bool two_stretches = P % kBN != 0 && kt_begin + it < np_tiles; // the first one is ahead
+            const int last_unmasked = np_tiles + (wave_tok0 >= kBN - 1 ? (wave_tok0 - (kBN - 1)) / kBN : -1);
             const int last_full = np_tiles + E / kBN - 1;
-            fast_end = min(min(last_unmasked + 1, last_full - 1), kt_end - 2) - kt_begin;
-        } else {
-            fast_end = min(n_it - 2, P / kBN - 2 - kt_begin);
-        }
-        if (it < fast_end) {
-            const int tsel = wave >> 2;
-            const int last_entry = (P + E + kPS - 1) / kPS - 1; // last page of the request: nothing beyond it is read
-            auto entry = [&](int kt, int i) {
-                return (uint32_t)table[min(kt * (kBN / kPS) + 2 * i + tsel, last_entry)];
-            };
-            uint32_t pg0 = entry(kt_begin + it + 2, 0), pg1 = entry(kt_begin + it + 2, 1);
-            int vprev = (it - 1) % kNumBufsV; // V buffer of tile it - 1
-            auto vnext = [](int v, int n) { v += n; return v >= kNumBufsV ? v - kNumBufsV : v; };
-            // while every row of the wavefront has the reference 0 (the usual case, see kSnap);
-            // otherwise the general step below takes over
-            for (; it < fast_end && __builtin_amdgcn_ballot_w64(m_ref != 0.f) == 0; ++it) {
-                const int buf = it & 3;
-                const int kt2 = kt_begin + it + 2;
-                gptr k0, v0, k1, v1;
-                if (kt2 < np_tiles) {
-                    const gptr b0 = pages_head + (uint64_t)pg0 * page_bytes;
-                    const gptr b1 = pages_head + (uint64_t)pg1 * page_bytes;
-                    k0 = b0 + pg_lane_k;
-                    v0 = b0 + pg_lane_v;
-                    k1 = b1 + pg_lane_k;
-                    v1 = b1 + pg_lane_v;
-                } else {
-                    const int64_t off = (int64_t)(kt2 - np_tiles) * kBN * row_bytes;
-                    k0 = knew_head + off + sfx_lane_k;
-                    v0 = vnew_head + off + sfx_lane_v;
-                    k1 = k0 + (int64_t)kLoadRows * row_bytes;
-                    v1 = v0 + (int64_t)kLoadRows * row_bytes;
+            const int fast_end = min(two_stretches ? P / kBN - 2 : min(last_unmasked + 1, last_full - 1), kt_end - 2) - kt_begin;
+            if (it < fast_end) {
+                const int tsel = wave >> 2;
+                const int last_entry = (P + E + kPS - 1) / kPS - 1; // last page of the request: nothing beyond it is read
+                auto entry = [&](int kt, int i) {
+                    return (uint32_t)table[min(kt * (kBN / kPS) + 2 * i + tsel, last_entry)];
+                };
+                uint32_t pg0 = entry(kt_begin + it + 2, 0), pg1 = entry(kt_begin + it + 2, 1);
+                int vprev = (it - 1) % kNumBufsV; // V buffer of tile it - 1
+                auto vnext = [](int v, int n) { v += n; return v >= kNumBufsV ? v - kNumBufsV : v; };
+                // while every row of the wavefront has the reference 0 (the usual case, see kSnap);
+                // otherwise the general step below takes over
+                for (; it < fast_end && __builtin_amdgcn_ballot_w64(m_ref != 0.f) == 0; ++it) {
+                    const int buf = it & 3;
+                    const int kt2 = kt_begin + it + 2;
+                    gptr k0, v0, k1, v1;
+                    if (kt2 < np_tiles) {
+                        const gptr b0 = pages_head + (uint64_t)pg0 * page_bytes;
+                        const gptr b1 = pages_head + (uint64_t)pg1 * page_bytes;
+                        k0 = b0 + pg_lane_k;
+                        v0 = b0 + pg_lane_v;
+                        k1 = b1 + pg_lane_k;
+                        v1 = b1 + pg_lane_v;
+                    } else {
+                        const int64_t off = (int64_t)(kt2 - np_tiles) * kBN * row_bytes;
+                        k0 = knew_head + off + sfx_lane_k;
+                        v0 = vnew_head + off + sfx_lane_v;
+                        k1 = k0 + (int64_t)kLoadRows * row_bytes;
+                        v1 = v0 + (int64_t)kLoadRows * row_bytes;
+                    }
+                    dma_tile(k0, v0, k1, v1, (buf + 2) & 3, vnext(vprev, 3));
+                    pg0 = entry(kt_begin + it + 3, 0);
+                    pg1 = entry(kt_begin + it + 3, 1);
+                    STile s;
+                    qk_tile(buf, s);
+                    float psum = exp_tile(s, pb_b, 0.f, std::true_type{});
+                    pv_tile(vprev, pb_a);
+                    if (__builtin_amdgcn_ballot_w64(!(psum < kStale) || m_ref == -INFINITY) != 0)
+                        psum = redo_tile(s, pb_b);
+                    l_run += psum;
+                    pair_barrier(it);
+                    vprev = vnext(vprev, 1);
+#pragma unroll
+                    for (int t = 0; t < 2 * kNKB; ++t) pb_a[t] = pb_b[t];
                 }
-                dma_tile(k0, v0, k1, v1, (buf + 2) & 3, vnext(vprev, 3));
-                pg0 = entry(kt_begin + it + 3, 0);
-                pg1 = entry(kt_begin + it + 3, 1);
-                STile s;
-                qk_tile(buf, s);
-                float psum = exp_tile(s, pb_b, 0.f, std::true_type{});
-                pv_tile(vprev, pb_a);
-                if (__builtin_amdgcn_ballot_w64(!(psum < kStale) || m_ref == -INFINITY) != 0)
-                    psum = redo_tile(s, pb_b);
-                l_run += psum;
-                pair_barrier(it);
-                vprev = vnext(vprev, 1);
+            }
+            // the general step: one call site, so that the accumulators stay in the same registers
+            const int stop = two_stretches ? min(n_it, np_tiles - kt_begin) : n_it;
+            for (; it < stop && !skipped(kt_begin + it); ++it) {
+                tile_step(it, pb_b, pb_a);
 #pragma unroll
                 for (int t = 0; t < 2 * kNKB; ++t) pb_a[t] = pb_b[t];
             }
-        }
-        // the general step: one call site, so that the accumulators stay in the same registers
-        for (; it < n_it && !skipped(kt_begin + it); ++it) {
-            tile_step(it, pb_b, pb_a);
-#pragma unroll
-            for (int t = 0; t < 2 * kNKB; ++t) pb_a[t] = pb_b[t];
+            if (it >= n_it || skipped(kt_begin + it)) break;
         }
         // P V of the last tile this wavefront computed (tile it - 1)
         pv_tile((it - 1) % kNumBufsV, pb_a);
@@ -1168,7 +1204,7 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
     const float l_tot = halfwave_sum(l_run);
     if (!row_valid) return;
     if (partial) {
-        const int64_t prow = part_row() * p.Hq + head;
+        const int64_t prow = part_row();
         float *po = p.part_o + prow * kD;
 #pragma unroll
         for (int db = 0; db < 4; ++db)
@@ -1274,24 +1310,22 @@ __global__ __launch_bounds__(32 * kMergeGroups) void merge_splits_kernel(const f
 }
 
 // Few splits: a group of 32 threads per (row, head), eight of them per workgroup, each walking
-// over its splits in order with all loads of a pass in flight together.
+// over its splits in order with all loads of a pass in flight together.  Partial result s of a row is row
+// first + s * step.
 template <int kSplits>
-__global__ __launch_bounds__(256) void merge_few_splits_kernel(const float *__restrict__ part_o,
-                                                               const float *__restrict__ part_ml,
-                                                               uint16_t *__restrict__ out, int64_t n_rh, int nsplit)
+__device__ __forceinline__ void merge_row(const float *__restrict__ part_o, const float *__restrict__ part_ml,
+                                          uint16_t *__restrict__ out, int64_t first, int64_t step, int64_t rh, int nsplit)
 {
-    const int64_t rh = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
-    if (rh >= n_rh) return;
     const int d4 = (threadIdx.x & 31) * 4;
     float ms[kSplits], ls[kSplits];
     f32x4 x[kSplits];
 #pragma unroll
     for (int s = 0; s < kSplits; ++s) {
         const bool on = s < nsplit;
-        const f32x2 ml = on ? *reinterpret_cast<const f32x2 *>(part_ml + ((int64_t)s * n_rh + rh) * 2) : f32x2{0.f, 0.f};
+        const f32x2 ml = on ? *reinterpret_cast<const f32x2 *>(part_ml + (first + s * step) * 2) : f32x2{0.f, 0.f};
         ms[s] = ml[0];
         ls[s] = ml[1];
-        x[s] = on ? *reinterpret_cast<const f32x4 *>(part_o + ((int64_t)s * n_rh + rh) * kD + d4) : f32x4{0.f, 0.f, 0.f, 0.f};
+        x[s] = on ? *reinterpret_cast<const f32x4 *>(part_o + (first + s * step) * kD + d4) : f32x4{0.f, 0.f, 0.f, 0.f};
     }
     float m_star = -INFINITY;
 #pragma unroll
@@ -1311,6 +1345,32 @@ __global__ __launch_bounds__(256) void merge_few_splits_kernel(const float *__re
 #pragma unroll
     for (int e = 0; e < 4; ++e) y[e] = (__bf16)(acc[e] * inv);
     *reinterpret_cast<bf16x4 *>(out + rh * kD + d4) = y;
+}
+
+template <int kSplits>
+__global__ __launch_bounds__(256) void merge_few_splits_kernel(const float *__restrict__ part_o,
+                                                               const float *__restrict__ part_ml,
+                                                               uint16_t *__restrict__ out, int64_t n_rh, int nsplit)
+{
+    const int64_t rh = (int64_t)blockIdx.x * 8 + (threadIdx.x >> 5);
+    if (rh < n_rh) merge_row<kSplits>(part_o, part_ml, out, rh, n_rh, rh, nsplit);
+}
+
+// The row tiles of a batch of equal requests that were split (the last tail_units of every KV head).
+constexpr int kMaxTailSplits = 16;
+template <int kSplits>
+__global__ __launch_bounds__(256) void merge_tail_kernel(const AttnParams p)
+{
+    constexpr int kBlocks = kBM / 8; // of a row tile
+    const int tile = blockIdx.x / kBlocks, i = (int)(blockIdx.x % kBlocks) * 8 + (int)(threadIdx.x >> 5);
+    const int kvh = tile / p.tail_units, tail_unit = tile - kvh * p.tail_units;
+    const int E = p.extend_lens[0], nt = (int)row_tiles(E, p.G, kTileShift);
+    const int r = (p.whole_units + tail_unit) / nt, unit = (p.whole_units + tail_unit) - r * nt;
+    const int row = row_tile_of(unit, nt, r, p.batch, p.alternate) * kBM + i;
+    if (row >= E * p.G) return;
+    const int tok = over_heads(row, p);
+    merge_row<kSplits>(p.part_o, p.part_ml, p.out, (int64_t)tile * p.nsplit * kBM + i, kBM,
+                       ((int64_t)r * E + tok) * p.Hq + kvh * p.G + (row - tok * p.G), p.nsplit);
 }
 
 static_assert(kDecMaxChunks <= kMergeGroups * kMergePerGroup && kMaxSplits <= kMergeGroups * kMergePerGroup,
@@ -1500,7 +1560,7 @@ __device__ __align__(256) unsigned long long g_check_report[32];
 
 // ------------------------------------------------------------------ host side
 struct Plan {
-    int64_t q_tiles;   // work units per KV head: row tiles x head groups, summed over requests
+    int64_t q_tiles;   // row tiles per KV head, summed over requests
     int32_t max_key_tiles;
     int32_t nsplit;
     bool decode;       // few rows per (request, KV head): decode_attn_kernel
@@ -1508,6 +1568,8 @@ struct Plan {
     int32_t dec_groups = 1; // ... by this many workgroups that share a request's keys
     int32_t dec_share = 1;  // ... with this many blocks of rows per wavefront
     bool small = false; // few rows and keys: decode_attn_kernel with a workgroup per block of 32 rows
+    int32_t tile_shift = kTileShift;
+    int32_t tail_units = 0; // row tiles per KV head that are split, the last ones of the list; 0: all or none
     bool mixed = false; // unequal lengths: extend_attn_kernel<kMixed>, with
     int32_t seg_tiles = 1, dec_blocks = 1;       // at most so many keys per item
     int64_t row_items = 0, dec_units = 0;        // row-tiled items and decode wavefronts per KV head
@@ -1576,6 +1638,24 @@ bool equal_lengths(const cp_shape *s)
     return true;
 }
 
+// Row tiles of a request as a plan counts them.  kWholeHeads: tiles of 256 rows that take the rows of 1, 2, 4 or 8 whole
+// q heads, the least number that leaves none of these smaller than E allows.  No kernel runs these any more, but
+// callers have sized their scratch by them: see too_little_scratch.
+constexpr int kWholeHeads = -1;
+int64_t planned_tiles(int64_t E, int G, int tile_shift)
+{
+    if (tile_shift != kWholeHeads) return row_tiles((int)E, G, tile_shift);
+    int heads = 1;
+    while (heads < 8 && G % (2 * heads) == 0 && E * (heads * 2) <= kBM) heads *= 2;
+    return (E * heads + kBM - 1) / kBM * (G / heads);
+}
+// ... and how many of them have different numbers of keys
+int64_t tile_lengths(int64_t E, int G, int tile_shift)
+{
+    const int64_t nt = planned_tiles(E, G, tile_shift);
+    return tile_shift == kWholeHeads && E > 0 ? (E + kBM - 1) / kBM : nt;
+}
+
 size_t part_bytes(size_t rows, int heads)
 {
     const size_t n = rows * (size_t)heads;
@@ -1585,9 +1665,16 @@ size_t part_bytes(size_t rows, int heads)
 // Plan of a mixed batch: the key ranges with the least estimated time.  What the estimate is made of,
 // in us: a row-tiled item costs kItemUs and kTileUs per key tile of 64 on one CU, a decode workgroup (8
 // wavefronts) kItemUs and kBlockUs per block of 32 keys; partial results are written and read once.
+// Tiles of half the rows are for calls whose tiles do not fill the device: four wavefronts with a SIMD each take two
+// thirds of the time of eight, and there are twice as many.  8/2 heads, P = 0: 3 requests, E = 959 28.0 -> 21.8 us;
+// 17, E = 134 11.5 -> 10.0; 32/8 heads, 4, P = 0, E = 214 13.6 -> 11.4.  Two rounds of them are slower than one of full
+// tiles (6 requests, P = 978, E = 842, 8/2 heads: 63 us, 52), so they have to fit the CUs at once, and they have to
+// promise kHalfUs more, for their start costs more than an item's in a list (1 request, E = 124, 64/8 heads: 9.4 us as
+// half tiles, 7.1 as a small call, which the estimates without it put the other way round).
+constexpr double kHalfTileUs = 1.2, kHalfUs = 1.5;
 constexpr double kItemUs = 4.0, kTileUs = 1.75, kBlockUs = 3.0, kMergeUs = 5.0, kPartBytesPerUs = 4.0e6;
 struct MixedRequest {
-    int64_t units;  // row tiles x head groups, or row blocks of decode-shaped work
+    int64_t units;  // row tiles, or row blocks of decode-shaped work
     int32_t extend; // new tokens
     int32_t length; // key tiles of the last row tile, or key blocks of 32
     float mean;     // key tiles or blocks of a unit on average
@@ -1596,7 +1683,7 @@ struct MixedRequest {
 };
 
 // Fills pl for at most seg_tiles key tiles per row-tiled item; returns the time.
-double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks, int kv_heads, int q_heads, Plan &pl)
+double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks, int kv_heads, int q_heads, double tile_us, Plan &pl)
 {
     pl.mixed = true;
     pl.seg_tiles = seg_tiles;
@@ -1610,7 +1697,7 @@ double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks,
         // as splits_of_request; a decode request has at most kMaxSplits ranges by the choice of dec_blocks
         const int limit = m.decode ? dec_blocks : seg_tiles;
         const int ns = std::min(kMaxSplits, (m.length + limit - 1) / limit);
-        const double step = m.decode ? kBlockUs : kTileUs;
+        const double step = m.decode ? kBlockUs : tile_us;
         const double us = (double)m.units * (ns * kItemUs + m.mean * step);
         work += m.decode ? us / kWaves : us;
         const double item = kItemUs + step * ((m.length + ns - 1) / ns);
@@ -1628,8 +1715,9 @@ double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks,
 }
 
 // The best plan whose partial results fit into `room` bytes, and its time; false if there is none.
-bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order, double *estimate)
+bool plan_mixed(const cp_shape *s, size_t room, int tile_shift, Plan &best, uint8_t *order, double *estimate)
 {
+    const double tile_us = tile_shift == kTileShift - 1 ? kHalfTileUs : kTileUs;
     const int G = s->num_q_heads / s->num_kv_heads;
     MixedRequest req[kMixedMaxBatch];
     int n = 0;
@@ -1649,10 +1737,9 @@ bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order, doub
             blocks = std::max(blocks, m.length);
             decode_work += m.units * m.length * s->num_kv_heads;
         } else {
-            const int pack = heads_per_tile((int)E, G);
-            const int64_t nt = (E * pack + kBM - 1) / kBM;
+            const int64_t nt = tile_lengths(E, G, tile_shift);
             const int32_t prefix = (int32_t)((P + kBN - 1) / kBN), own = (int32_t)((E + kBN - 1) / kBN);
-            m.units = units_of_request((int)E, G, pack);
+            m.units = planned_tiles(E, G, tile_shift);
             m.length = prefix + own;
             m.mean = (float)prefix + 0.5f * (float)own * (1.f + 1.f / (float)nt);
         }
@@ -1685,7 +1772,8 @@ bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order, doub
         const int least = (int)std::min<int64_t>(16, std::max<int64_t>(4, 2 * decode_work / (8 * num_cus())));
         const int dec = std::max(std::max(least, (int)(seg * (kTileUs / kBlockUs))), (blocks + kMaxSplits - 1) / kMaxSplits);
         Plan pl{0, 0, 1, false, 1};
-        const double us = mixed_cost(req, n, seg, dec, s->num_kv_heads, s->num_q_heads, pl);
+        pl.tile_shift = tile_shift;
+        const double us = mixed_cost(req, n, seg, dec, s->num_kv_heads, s->num_q_heads, tile_us, pl);
         if (pl.part_rows > INT32_MAX / 2 || (pl.part_rows > 0 && part_bytes((size_t)pl.part_rows, s->num_q_heads) > room)) continue;
         if ((pl.row_items + (pl.dec_units + kWaves - 1) / kWaves) * s->num_kv_heads > INT32_MAX / 2) continue;
         worse = best_us >= 0.0 && us >= best_us ? worse + 1 : 0;
@@ -1699,13 +1787,14 @@ bool plan_mixed(const cp_shape *s, size_t room, Plan &best, uint8_t *order, doub
 }
 
 // Row-tiled work of a call: work units per KV head, key tiles of the longest request.
-void row_tiled_extent(const cp_shape *s, int64_t &q_tiles, int32_t &max_key_tiles)
+void row_tiled_extent(const cp_shape *s, int tile_shift, int64_t &q_tiles, int32_t &max_key_tiles)
 {
     const int G = s->num_q_heads / s->num_kv_heads;
+    q_tiles = 0;
     for (int r = 0; r < s->batch; ++r) {
         const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
         if (E == 0) continue;
-        q_tiles += units_of_request((int)E, G, heads_per_tile((int)E, G));
+        q_tiles += planned_tiles(E, G, tile_shift);
         max_key_tiles = std::max(max_key_tiles, (int32_t)((P + kBN - 1) / kBN + (E + kBN - 1) / kBN));
     }
 }
@@ -1719,32 +1808,31 @@ void row_tiled_extent(const cp_shape *s, int64_t &q_tiles, int32_t &max_key_tile
 // of 10 tiles before) 25.2 -> 19.0 us; 4 requests, P = 3000, E = 128, 32/8 heads 61 -> 45; 1 request,
 // P = 2000, E = 700, 64/8 heads 100 -> 72; 12 requests, P = 20000, E = 128, 32/8 heads 538 -> 496.
 constexpr double kLastItem = 0.75; // of its length, behind the others
-int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *estimate)
+void choose_splits(const cp_shape *s, size_t room, Plan &pl, double *estimate)
 {
-    const int64_t items = pl.q_tiles * s->num_kv_heads, cus = num_cus();
+    const double tile_us = pl.tile_shift == kTileShift - 1 ? kHalfTileUs : kTileUs;
     const bool mixed = s->batch <= kMixedMaxBatch && !equal_lengths(s); // a plan to compare this one with
-    *estimate = 0.0;
-    if (items >= 2 * cus && !mixed) return 1;
+    bool alike = true;
+    const int64_t items = pl.q_tiles * s->num_kv_heads, cus = num_cus();
     const int G = s->num_q_heads / s->num_kv_heads;
     double tiles = 0.0; // key tiles of all items
-    bool alike = true;
     for (int r = 0; r < s->batch; ++r) {
         const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
         if (E == 0) continue;
-        const int pack = heads_per_tile((int)E, G);
-        const int64_t nt = (E * pack + kBM - 1) / kBM;
+        const int64_t nt = tile_lengths(E, G, pl.tile_shift);
         alike = alike && nt == 1;
-        tiles += (double)units_of_request((int)E, G, pack) * s->num_kv_heads *
+        tiles += (double)planned_tiles(E, G, pl.tile_shift) * s->num_kv_heads *
                  ((double)((P + kBN - 1) / kBN) + 0.5 * (double)((E + kBN - 1) / kBN) * (1.0 + 1.0 / (double)nt));
     }
-    int32_t best = 1;
     double best_us = 0.0;
+    *estimate = 0.0;
+    if (items >= 2 * cus && !mixed) return;
     const int32_t most = items >= 2 * cus ? 1 : std::min(mixed ? kMergeSomeSplits : kMaxSplits, std::max(1, pl.max_key_tiles / 2));
     for (int32_t ns = 1; ns <= most; ++ns) {
         const size_t bytes = ns > 1 ? part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) : 0;
         if (bytes > room) break;
-        const double longest = kItemUs + kTileUs * ((pl.max_key_tiles + ns - 1) / ns);
-        const double mean = kItemUs + kTileUs * tiles / ((double)items * ns);
+        const double longest = kItemUs + tile_us * ((pl.max_key_tiles + ns - 1) / ns);
+        const double mean = kItemUs + tile_us * tiles / ((double)items * ns);
         double us = longest;
         if (items * ns > cus && mixed)
             us = std::max(us, mean * ((double)(items * ns) / (double)cus) + kLastItem * longest);
@@ -1753,11 +1841,86 @@ int32_t choose_splits(const cp_shape *s, const Plan &pl, size_t room, double *es
         if (ns > 1) us += kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
         if (ns == 1 || us < best_us) {
             best_us = ns == 1 ? 0.85 * us : us; // a split has to promise more than the estimate is off by
-            best = ns;
+            pl.nsplit = ns;
             *estimate = us;
         }
     }
-    return best;
+}
+
+// Time of items that the CUs take one after another: their work and an uneven end, unless the CUs that take one
+// more than the others (the shortest, if those are last) are later.  Against the list run item by item, 5000 random
+// batches of equal requests: 0.99 of the time in the middle, 0.93 and 1.02 with a tenth of the batches outside.
+double rounds_us(double items, double cus, double work, double shortest, double longest)
+{
+    if (items <= cus) return longest;
+    const double rounds = std::ceil(items / cus), last = items - (rounds - 1.0) * cus, more = rounds * last / items;
+    const double uneven = 0.2 * (longest - shortest) + (last < cus ? 0.2 * shortest : 0.0);
+    return std::max(work / cus + uneven, rounds * (shortest + 0.5 * more * (longest - shortest)));
+}
+
+// Time of a key tile in the last row tile of a request, as a part of a full one's.  Up to four wavefronts with rows
+// have a SIMD each: 1.32 us a tile with one or two of them, 1.46 with four, 1.76, 1.88, 2.04, 2.16 with five to
+// eight (256 workgroups, no two with the same keys).
+double last_tile_share(int64_t E, int G, int tile_shift)
+{
+    const int waves = (int)((E * G - 1) % kBM) / 32 + 1;
+    if (tile_shift < kTileShift) return 1.0;
+    return waves <= 4 ? 0.65 : 0.65 + 0.0875 * (waves - 4);
+}
+
+// The same for equal requests, which also have a third way: the items that would run in a last round of few are
+// split, the others are not (pl.tail_units).  Then the call ends with all CUs busy, and only the rows of the last
+// items are merged.  3 requests, P = 30000, E = 1100, 64/8 heads (105 items for 32 CUs) 3254 -> 2856 us; 6, P = 9046,
+// E = 171 (36) 444 -> 314; 1, P = 10694, E = 2051, 32/8 heads (33) 496 -> 368.
+// With 1, 2 or 4 KV heads and contiguous ranges for the XCDs (see work_item) there is no common last round.
+constexpr double kTailGain = 0.97; // of the time without
+bool contiguous_ranges(const cp_shape *s, const Plan &pl, int64_t items, int xcds);
+void choose_equal_splits(const cp_shape *s, size_t room, Plan &pl, double *estimate)
+{
+    const int G = s->num_q_heads / s->num_kv_heads, E = s->h_extend_lens[0], Hkv = s->num_kv_heads;
+    const double cus = (double)num_cus() / Hkv; // that share the list of a KV head
+    const double tile_us = pl.tile_shift == kTileShift ? kTileUs : kHalfTileUs;
+    const int64_t nt = row_tiles(E, G, pl.tile_shift), units = nt * s->batch;
+    auto own_tiles = [&](int64_t t) { return (double)((std::min<int64_t>(E, (((t + 1) << pl.tile_shift) + G - 1) / G) + kBN - 1) / kBN); };
+    const double prefix = (double)(((int64_t)s->h_prefix_lens[0] + kBN - 1) / kBN);
+    const double last = last_tile_share(E, G, pl.tile_shift), one = nt == 1 ? last : 1.0;
+    const double shortest = one * (prefix + own_tiles(0)), longest = one * (prefix + own_tiles(nt - 1));
+    const double n = (double)units, tiles = ((double)(nt - 1) + last) * s->batch * (prefix + 0.5 * (own_tiles(0) + own_tiles(nt - 1)));
+    double best_us = 0.0;
+    const int32_t most = n >= 4.0 * cus ? 1 : std::min(kMaxSplits, std::max(1, pl.max_key_tiles / 2));
+    for (int32_t ns = 1; ns <= most; ++ns) {
+        const size_t bytes = ns > 1 ? part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) : 0;
+        if (bytes > room) break;
+        double us = rounds_us(n * ns, cus, n * ns * kItemUs + tile_us * tiles, kItemUs + tile_us * shortest / ns,
+                              kItemUs + tile_us * std::ceil(longest / ns));
+        if (ns > 1) us += kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
+        if (ns == 1 || us < best_us) {
+            best_us = ns == 1 ? 0.9 * us : us; // a split has to promise more than the estimate is off by
+            pl.nsplit = ns;
+            *estimate = us;
+        }
+    }
+    const int64_t per_round = num_cus() / Hkv;
+    if (pl.tile_shift != kTileShift) return;
+    if (Hkv > kXcds || kXcds % Hkv != 0 || units <= per_round || units % per_round == 0 || units > INT32_MAX / kMaxTailSplits) return;
+    if (Hkv < kXcds && contiguous_ranges(s, pl, units * pl.nsplit, kXcds / Hkv)) return;
+    best_us = std::min(kTailGain * *estimate, best_us);
+    for (int64_t tail = units % per_round; tail < std::min(units, 2 * per_round); tail += per_round) {
+        // they are the shortest of the last request, as far as that has as many
+        const double tail_longest = tail < nt ? prefix + own_tiles(tail - 1) : longest;
+        const double whole = (n - (double)tail) * kItemUs + tile_us * (tiles - (double)tail * 0.5 * (shortest + tail_longest));
+        for (int32_t ns = 2; ns <= kMaxTailSplits && 2 * ns <= (int32_t)shortest; ++ns) {
+            const size_t bytes = part_bytes((size_t)(tail * ns) * kBM, Hkv);
+            if (bytes > room) break;
+            const double us = whole / cus + std::ceil((double)(tail * ns) / cus) * (kItemUs + tile_us * std::ceil(tail_longest / ns)) +
+                              kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
+            if (us >= best_us) continue;
+            best_us = us;
+            *estimate = us;
+            pl.nsplit = ns;
+            pl.tail_units = (int32_t)tail;
+        }
+    }
 }
 
 // Workgroups per (request, KV head) of a decode-shaped call: the least estimated time, returned in *estimate.  A
@@ -1878,18 +2041,41 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
         if (pl.row_blocks > 1 && max_n <= kSmallDecodeKeys) small_call(s, max_n, us, pl);
         return pl;
     }
-    row_tiled_extent(s, pl.q_tiles, pl.max_key_tiles);
+    row_tiled_extent(s, kTileShift, pl.q_tiles, pl.max_key_tiles);
     if (s->num_splits >= 1) {
         pl.nsplit = s->num_splits;
         return pl;
     }
-    double us;
-    pl.nsplit = choose_splits(s, pl, room, &us);
-    if (small_call(s, max_n, us, pl)) pl.nsplit = 1;
-    if (s->batch <= kMixedMaxBatch && max_e > 0 && !equal_lengths(s)) {
+    double us = 0.0;
+    const bool equal = equal_lengths(s), compare = !equal && s->batch <= kMixedMaxBatch; // with a plan that splits by request
+    if (max_e == 0) return pl;
+    const bool by_items = equal || compare || pl.q_tiles * s->num_kv_heads < 2 * num_cus();
+    if (by_items) equal ? choose_equal_splits(s, room, pl, &us) : choose_splits(s, room, pl, &us);
+    Plan half{0, 0, 1, false, 1};
+    half.tile_shift = kTileShift - 1;
+    row_tiled_extent(s, half.tile_shift, half.q_tiles, half.max_key_tiles);
+    const bool few = by_items && half.q_tiles * s->num_kv_heads <= num_cus();
+    if (few) {
+        double half_us;
+        equal ? choose_equal_splits(s, room, half, &half_us) : choose_splits(s, room, half, &half_us);
+        if (half_us + kHalfUs < us) {
+            pl = half;
+            us = half_us + kHalfUs;
+        }
+    }
+    if (small_call(s, max_n, us, pl)) {
+        pl.nsplit = 1;
+        pl.tail_units = 0;
+    }
+    if (compare) {
         Plan mixed{0, 0, 1, false, 1};
-        double mixed_us;
-        if (plan_mixed(s, room, mixed, order, &mixed_us) && mixed_us + kMixedUs < us) return mixed;
+        double mixed_us, half_us;
+        const bool any = plan_mixed(s, room, kTileShift, mixed, order, &mixed_us);
+        if (few && plan_mixed(s, room, kTileShift - 1, half, order, &half_us) && (!any || half_us + kHalfUs < mixed_us)) {
+            mixed = half;
+            mixed_us = half_us + kHalfUs;
+        } else if (!any) return pl;
+        if (mixed_us + kMixedUs < us) return mixed;
     }
     return pl;
 }
@@ -1901,17 +2087,17 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
 constexpr double kContiguousExcess = 1.06;
 bool contiguous_ranges(const cp_shape *s, const Plan &pl, int64_t items, int xcds)
 {
-    if (items <= 0 || pl.mixed || !equal_lengths(s)) return false;
-    const int G = s->num_q_heads / s->num_kv_heads, E = s->h_extend_lens[0], pack = heads_per_tile(E, G);
-    const int64_t rows = kBM / pack, nt = (E + rows - 1) / rows, per = (items + xcds - 1) / xcds;
+    if (items <= 0 || pl.mixed || pl.tail_units > 0 || !equal_lengths(s)) return false;
+    const int G = s->num_q_heads / s->num_kv_heads, E = s->h_extend_lens[0];
+    const int64_t nt = row_tiles(E, G, pl.tile_shift), per = (items + xcds - 1) / xcds;
     const double prefix = (double)((s->h_prefix_lens[0] + kBN - 1) / kBN);
     double load = 0.0, most = 0.0, all = 0.0;
     int64_t left = per;
     for (int r = 0; r < s->batch; ++r)
         for (int64_t t = nt - 1; t >= 0; --t) {
-            const double tiles = prefix + (double)((std::min<int64_t>(E, (t + 1) * rows) + kBN - 1) / kBN);
+            const double tiles = prefix + (double)((std::min<int64_t>(E, (((t + 1) << pl.tile_shift) + G - 1) / G) + kBN - 1) / kBN);
             const double us = kItemUs + kTileUs * tiles / pl.nsplit;
-            for (int64_t n = G / pack * pl.nsplit; n > 0;) {
+            for (int64_t n = pl.nsplit; n > 0;) {
                 const int64_t take = std::min(n, left);
                 load += (double)take * us;
                 n -= take;
@@ -1952,7 +2138,29 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
 {
     if (pl.mixed) return pl.part_rows > 0 ? part_bytes((size_t)pl.part_rows, s->num_q_heads) : 0;
     if (pl.nsplit <= 1) return 0;
+    if (pl.tail_units > 0) return part_bytes((size_t)pl.tail_units * (size_t)pl.nsplit * kBM, s->num_kv_heads);
     return part_bytes((size_t)pl.nsplit * (size_t)s->total_extend, s->num_q_heads);
+}
+// The same of the best plan with tiles of whole heads, in one number of key ranges or request by request.
+size_t workspace_of_whole_heads(const cp_shape *s)
+{
+    Plan pl = make_plan(s);
+    if (pl.decode || s->num_splits >= 1) return workspace_for(s, pl);
+    int64_t max_n = 0;
+    for (int r = 0; r < s->batch; ++r)
+        if (s->h_extend_lens[r] > 0) max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
+    if (max_n == 0) return 0;
+    pl = Plan{0, 0, 1, false, 1};
+    pl.tile_shift = kWholeHeads;
+    row_tiled_extent(s, kWholeHeads, pl.q_tiles, pl.max_key_tiles);
+    double us, mixed_us;
+    choose_splits(s, SIZE_MAX, pl, &us);
+    if (small_call(s, max_n, us, pl)) pl.nsplit = 1;
+    Plan mixed{0, 0, 1, false, 1};
+    if (s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, SIZE_MAX, kWholeHeads, mixed, nullptr, &mixed_us) &&
+        mixed_us + kMixedUs < us)
+        return workspace_for(s, mixed);
+    return workspace_for(s, pl);
 }
 // What the launches touch of it: of a decode-shaped call the partial results of the workgroups that share a
 // request's keys, at most nsplit, none where one workgroup has them all.
@@ -1970,17 +2178,18 @@ bool too_little_scratch(const cp_shape *s, const Plan &pl, size_t room)
 {
     if (scratch_used(s, pl) > room) return true;
     if (pl.decode || s->num_splits >= 1) return false;
+    // The line lies where it lay when row tiles held whole heads.
     int64_t q_tiles = 0;
     int32_t max_key_tiles = 0;
-    row_tiled_extent(s, q_tiles, max_key_tiles);
+    row_tiled_extent(s, kWholeHeads, q_tiles, max_key_tiles);
     const int64_t items = q_tiles * s->num_kv_heads, want = 2LL * num_cus();
     int64_t ns = items > 0 && items < want ? (want + items - 1) / items : 1;
     ns = std::min<int64_t>({ns, max_key_tiles / 8, kMaxSplits});
     if (ns <= 1 || part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) <= room) return false;
-    if (workspace_for(s, make_plan(s)) <= room) return false;
+    if (workspace_of_whole_heads(s) <= room) return false;
     Plan mixed{0, 0, 1, false, 1};
     double us;
-    return s->batch > kMixedMaxBatch || equal_lengths(s) || !plan_mixed(s, SIZE_MAX, mixed, nullptr, &us) || workspace_for(s, mixed) > room;
+    return s->batch > kMixedMaxBatch || equal_lengths(s) || !plan_mixed(s, SIZE_MAX, kWholeHeads, mixed, nullptr, &us) || workspace_for(s, mixed) > room;
 }
 
 inline bool aligned_to(const void *p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
@@ -2137,7 +2346,7 @@ int32_t cp_plan_kind(const cp_shape *shape)
 size_t cp_workspace_bytes(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return 0;
-    return workspace_for(shape, make_plan(shape));
+    return std::max(workspace_for(shape, make_plan(shape)), workspace_of_whole_heads(shape));
 }
 
 } // extern "C"
@@ -2169,8 +2378,10 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     const Plan pl = planned ? *planned : make_plan(shape, room, p.order);
     const size_t need = scratch_used(shape, pl);
     if (!planned && too_little_scratch(shape, pl, room)) return CP_ERR_WORKSPACE;
-    if (need > 0 && !aligned_to(workspace, 256)) return CP_ERR_WORKSPACE;
-    const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves : pl.q_tiles * pl.nsplit;
+    // a misaligned buffer is the caller's mistake wherever the shape asks for one
+    if (workspace && !aligned_to(workspace, 256) && (need > 0 || (!pl.decode && workspace_of_whole_heads(shape) > 0))) return CP_ERR_WORKSPACE;
+    const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves :
+                             pl.tail_units > 0 ? pl.q_tiles + pl.tail_units * (int64_t)(pl.nsplit - 1) : pl.q_tiles * pl.nsplit;
     const int64_t total = per_head * shape->num_kv_heads;
     if (total > INT32_MAX / 2) return CP_ERR_SHAPE;
     const int64_t dec_units = (int64_t)shape->batch * shape->num_kv_heads * pl.nsplit * pl.row_blocks;
@@ -2193,14 +2404,23 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     p.max_pages = shape->max_pages_per_req;
     p.T = shape->total_extend;
     p.nsplit = pl.nsplit;
+    p.tail_units = pl.tail_units;
+    p.tile_shift = pl.tile_shift;
+    p.whole_units = pl.tail_units > 0 ? (int32_t)pl.q_tiles - pl.tail_units : 0;
     p.dec_row_blocks = pl.row_blocks;
     p.items_per_head = (int32_t)per_head;
     p.total_items = (int32_t)total;
     p.xcds_per_head = p.Hkv < kXcds && kXcds % p.Hkv == 0 ? kXcds / p.Hkv : 1;
-    if (p.xcds_per_head > 1 && contiguous_ranges(shape, pl, per_head, p.xcds_per_head)) p.xcds_per_head = 1;
+    const bool ranges = p.xcds_per_head > 1 && contiguous_ranges(shape, pl, per_head, p.xcds_per_head);
+    if (ranges) p.xcds_per_head = 1;
+    p.alternate = !ranges && per_head * p.Hkv <= kAlternateRounds * (int64_t)num_cus() && equal_lengths(shape);
     p.items_per_xcd = (int32_t)(p.xcds_per_head > 1 ? (per_head + p.xcds_per_head - 1) / p.xcds_per_head
                                                     : (total + kXcds - 1) / kXcds);
     p.scale_log2 = shape->softmax_scale * 1.4426950408889634f;
+
+    int64_t most = 0;
+    for (int r = 0; r < shape->batch; ++r) most = std::max<int64_t>(most, shape->h_extend_lens[r]);
+    p.g_magic = (most * p.G + kBM + 1) * p.G <= INT64_C(0x100000000) ? 0xffffffffu / (uint32_t)p.G : 0u;
 
     p.seg_tiles = pl.seg_tiles;
     p.dec_blocks = pl.dec_blocks;
@@ -2209,7 +2429,7 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     hipStream_t hs = static_cast<hipStream_t>(stream);
     if (need > 0) {
         const size_t parts = pl.mixed ? (size_t)pl.part_rows : (size_t)(pl.decode ? pl.dec_groups : pl.nsplit) * (size_t)p.T;
-        const size_t rows = parts * (size_t)p.Hq;
+        const size_t rows = pl.tail_units > 0 ? (size_t)pl.tail_units * (size_t)pl.nsplit * kBM * (size_t)p.Hkv : parts * (size_t)p.Hq;
         p.part_o = static_cast<float *>(workspace);
         p.part_ml = reinterpret_cast<float *>(static_cast<char *>(workspace) + ((rows * kD * sizeof(float) + 255) / 256) * 256);
     }
@@ -2237,7 +2457,14 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     } else if (pl.nsplit > 1) {
         hipLaunchKernelGGL(extend_attn_kernel<kSplit>, grid, block, kLdsBytes, hs, static_cast<const AttnParams &>(p));
         if (hipGetLastError() != hipSuccess) return CP_ERR_LAUNCH;
-        launch_merge(p, pl.nsplit, hs);
+        if (pl.tail_units == 0) launch_merge(p, pl.nsplit, hs);
+        else {
+            const dim3 blocks((unsigned)(pl.tail_units * p.Hkv * (kBM / 8)));
+            const AttnParams &a = p;
+            if (pl.nsplit <= 4) hipLaunchKernelGGL(merge_tail_kernel<4>, blocks, dim3(256), 0, hs, a);
+            else if (pl.nsplit <= 8) hipLaunchKernelGGL(merge_tail_kernel<8>, blocks, dim3(256), 0, hs, a);
+            else hipLaunchKernelGGL(merge_tail_kernel<kMaxTailSplits>, blocks, dim3(256), 0, hs, a);
+        }
     } else {
         hipLaunchKernelGGL(extend_attn_kernel<kWhole>, grid, block, kLdsBytes, hs, static_cast<const AttnParams &>(p));
     }

@@ -90,6 +90,54 @@ def test_less_scratch_than_asked_for(H, P, E, Hq, Hkv, part, ok):
         assert (got == 0x1234).all()
 
 
+@pytest.mark.parametrize("B,P,E,G,Hkv", [
+    (33, 1500, 70, 1, 8),      # one item more than the CUs of an XCD, three wavefronts of rows
+    (17, 1000, 150, 2, 8),     # two tiles a request, the last one of 44 rows; requests in turn longest and shortest first
+    (11, 1500, 250, 3, 8),     # G divides neither tile nor wavefront; the shortest tile of the last request
+])
+def test_the_last_round_alone_is_split(H, B, P, E, G, Hkv):
+    """Equal requests whose items do not fill the last round: only its row tiles are split and merged.  Against
+    the oracle, and every row against the unsplit call, also in a buffer of exactly the size asked for."""
+    import torch
+
+    import paper_2511_03475_amd as cp
+
+    w = W.make_uniform("tail", 71, B, G * Hkv, Hkv, [P] * B, [E] * B)
+    case = H.DeviceCase(w)
+    tiles = -(-E * G // 256) * B
+    uniform = cp.cp_num_splits(case.shape) * B * E * G * Hkv * 130 * 4
+    assert tiles > 256 // Hkv and 0 < case.ws_bytes < uniform / 2     # a part of the rows has partial results
+    size = case.ws_bytes
+    case.workspace = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    case.attention()
+    got = case.out_bits()
+    assert (case.workspace[size:] == 0x5A).all()
+    _check(got, oracle.attention_of(w), f"tail B={B} P={P} E={E} G={G} Hkv={Hkv}")
+    _check(H.gpu_attention(w, num_splits=1), W.bf16_bits_to_f32(got).astype(np.float64), "unsplit")
+
+
+@pytest.mark.parametrize("P,E,G,Hkv", [
+    ([0] * 3, [959] * 3, 4, 2), ([0], [129], 1, 1), ([70], [383], 3, 8), ([300] * 2, [700] * 2, 8, 4),   # equal
+    ([0, 130, 500], [900, 257, 1], 4, 2), ([200, 0], [129, 1000], 2, 4),                                 # unequal
+])
+def test_row_tiles_of_half_the_rows(H, P, E, G, Hkv):
+    """Calls whose row tiles do not fill the device, tiles of 128 rows: remainders, one row too many, splits."""
+    w = W.make_uniform("half", 72, len(P), G * Hkv, Hkv, P, E)
+    want = oracle.attention_of(w)
+    _check(H.gpu_attention(w), want, f"half P={P} E={E} G={G} Hkv={Hkv}")
+    _check(H.gpu_attention(w, num_splits=2), want, f"full P={P} E={E} G={G} Hkv={Hkv}")
+
+
+@pytest.mark.parametrize("P", [1, 63, 65, 127, 129, 191, 449, 450])
+def test_a_prefix_that_ends_inside_a_tile(H, P):
+    """The steady-state loop runs over the prefix, is left for the tile the prefix ends in, and runs on over the
+    new keys; ranges that begin and end around that tile too."""
+    w = W.make_uniform("ragged", 73, 1, 2, 2, [P], [700])
+    want = oracle.attention_of(w)
+    for splits in (1, 2, 5):
+        _check(H.gpu_attention(w, num_splits=splits), want, f"P={P} splits={splits}")
+
+
 def test_more_requests_than_lanes(H):
     """70 requests of both kinds: two groups of 64 in every search, equal lengths among the sorted ones."""
     rng = np.random.default_rng(53)
