@@ -8,6 +8,7 @@ built, loading raises.
 from __future__ import annotations
 
 import ctypes
+import itertools
 import os
 from typing import Optional, Sequence
 
@@ -135,17 +136,17 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.cp_index_insert.argtypes = [vp, i32p, i32, i32p, i32p, i32, i32p]
     lib.cp_index_schedule.restype = ctypes.c_int
     lib.cp_index_schedule.argtypes = [i32p, i32p, i32, i32, i32p]
-    u8p, i64p = ctypes.POINTER(ctypes.c_uint8), ctypes.POINTER(ctypes.c_int64)
+    i64p = ctypes.POINTER(ctypes.c_int64)
     lib.cp_dedup_hash.restype = ctypes.c_uint64
-    lib.cp_dedup_hash.argtypes = [u8p, ctypes.c_int64]
+    lib.cp_dedup_hash.argtypes = [vp, ctypes.c_int64]
     lib.cp_dedup_chunks.restype = ctypes.c_int
-    lib.cp_dedup_chunks.argtypes = [u8p, ctypes.c_int64, ctypes.c_uint64, i64p, i32, i32p]
+    lib.cp_dedup_chunks.argtypes = [vp, ctypes.c_int64, ctypes.c_uint64, i64p, i32, i32p]
     lib.cp_dedup_create.restype = ctypes.c_int
     lib.cp_dedup_create.argtypes = [ctypes.c_uint64, ctypes.POINTER(vp)]
     lib.cp_dedup_free.restype = None
     lib.cp_dedup_free.argtypes = [vp]
     lib.cp_dedup_turn.restype = ctypes.c_int
-    lib.cp_dedup_turn.argtypes = [vp, i32p, u8p, i64p, i32, i32p, ctypes.POINTER(cp_dedup_sub), i32, i32p, i64p]
+    lib.cp_dedup_turn.argtypes = [vp, i32p, vp, i64p, i32, i32p, vp, i32, i32p, i64p]
     lib.cp_status_string.restype = ctypes.c_char_p
     lib.cp_status_string.argtypes = [ctypes.c_int]
     _lib = lib
@@ -453,6 +454,9 @@ def cp_dedup_chunks(data: bytes, modulus: int):
     return [int(ends[i]) for i in range(n.value)]
 
 
+_SUB = np.dtype([("block", np.int32), ("ref", np.int32), ("begin", np.int64), ("end", np.int64)])  # cp_dedup_sub
+
+
 class Conversation:
     """Owner of a cp_dedup handle.  turn() is one C call plus argument marshalling."""
 
@@ -472,21 +476,16 @@ class Conversation:
         """Per block ("block", id) or ("subs", [(begin, end, ref), ...]), and the kept bytes."""
         n = len(ids)
         data = b"".join(blocks)
-        offsets = (ctypes.c_int64 * (n + 1))()
-        at = 0
-        for i, b in enumerate(blocks):
-            offsets[i] = at
-            at += len(b)
-        offsets[n] = at
+        offsets = (ctypes.c_int64 * (n + 1))(0, *itertools.accumulate(map(len, blocks)))
         idv = (ctypes.c_int32 * max(n, 1))(*[int(i) for i in ids])
         ref = (ctypes.c_int32 * max(n, 1))()
-        cap = data.count(b"\n") + n + 1
-        subs = (cp_dedup_sub * cap)()
+        # a sub-block has a byte at least; pages that are not written cost nothing, counting lines does
+        cap = len(data) + 1 if len(data) < 1 << 22 else data.count(b"\n") + n + 1
+        subs = np.empty(cap, dtype=_SUB)
         cnt, kept = ctypes.c_int32(0), ctypes.c_int64(0)
-        _check_index(self._lib.cp_dedup_turn(self._h, idv, _u8(data), offsets, n, ref, subs, cap,
+        _check_index(self._lib.cp_dedup_turn(self._h, idv, data, offsets, n, ref, subs.ctypes.data, cap,
                                              ctypes.byref(cnt), ctypes.byref(kept)), "cp_dedup_turn")
         out = [("block", int(ids[i])) if ref[i] else ("subs", []) for i in range(n)]
-        for k in range(cnt.value):
-            s = subs[k]
-            out[s.block][1].append((int(s.begin), int(s.end), int(s.ref)))
+        for block, owner, begin, end in subs[:cnt.value].tolist():
+            out[block][1].append((begin, end, owner))
         return out, int(kept.value)

@@ -100,6 +100,27 @@ def test_hash_and_chunks_match_oracle():
             assert cp.cp_dedup_chunks(text, M) == want
 
 
+@pytest.mark.parametrize("count", [0, 1, 5, 6, 7, 12, 13, 40])
+@pytest.mark.parametrize("M", [1, 3, 8])
+def test_lines_hashed_side_by_side(count, M):
+    """Fewer lines than are hashed at a time, as many, one more; empty, short and long ones in every place; blocks
+    of which the last lacks the newline, and one without text among them."""
+    rng = np.random.default_rng(count)
+    texts = []
+    for b in range(3):
+        lines = [bytes(rng.integers(97, 123, size=int(n), dtype=np.uint8)) for n in rng.integers(0, 4, size=count) ** 4]
+        texts.append(b"\n".join(lines) + (b"\n" if b == 1 else b""))
+    texts.insert(1, b"")
+    for text in texts:
+        ends = np.cumsum([len(x) for x in OD.cdc(text, M)])
+        assert cp.cp_dedup_chunks(text, M) == ends.tolist()
+    ref, lib = OD.Conversation(M), cp.Conversation(M)
+    for ids in ([1, 2, 3, 4], [5, 6, 7, 8], [4, 9, 10, 11]):      # the same texts under new names
+        want = ref.turn(ids, texts)
+        assert lib.turn(ids, texts) == (want, OD.kept_bytes(want))
+    lib.close()
+
+
 @pytest.mark.parametrize("seed,M", [(1, 4), (2, 1), (3, 16), (4, 7)])
 def test_conversation_matches_oracle_turn_by_turn(seed, M):
     blocks, turns = W.make_conversation(seed)
