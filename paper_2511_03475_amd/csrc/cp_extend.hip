@@ -1673,6 +1673,15 @@ size_t part_bytes(size_t rows, int heads)
 // half tiles, 7.1 as a small call, which the estimates without it put the other way round).
 constexpr double kHalfTileUs = 1.2, kHalfUs = 1.5;
 constexpr double kItemUs = 4.0, kTileUs = 1.75, kBlockUs = 3.0, kMergeUs = 5.0, kPartBytesPerUs = 4.0e6;
+// Batches of unequal lengths: what follows the items of a request at least (a part of its item's length), what the merge
+// takes, and what a plan without a split counts for against one with.  Of sets of constants tried on 373 random batches
+// those below choose plans that take 4.1 % more than the best number of ranges of each; the first ones, with
+// which the line of too_little_scratch was drawn and which stay for it, 5.3 %.
+struct UnequalCosts {
+    double end, merge_us, part_bytes_per_us, last_item, unsplit;
+    bool rounds; // items of one length take whole rounds over the CUs
+};
+constexpr UnequalCosts kUnequal{0.4, 6.0, 3.2e6, 0.5, 1.0, true}, kUnequalOfWholeHeads{0.5, kMergeUs, kPartBytesPerUs, 0.75, 0.85, false};
 struct MixedRequest {
     int64_t units;  // row tiles, or row blocks of decode-shaped work
     int32_t extend; // new tokens
@@ -1683,15 +1692,17 @@ struct MixedRequest {
 };
 
 // Fills pl for at most seg_tiles key tiles per row-tiled item; returns the time.
-double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks, int kv_heads, int q_heads, double tile_us, Plan &pl)
+double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks, int kv_heads, int q_heads, double tile_us,
+                  const UnequalCosts &c, Plan &pl)
 {
     pl.mixed = true;
     pl.seg_tiles = seg_tiles;
     pl.dec_blocks = dec_blocks;
-    // One KV head on its share of the CUs, in the order of the list: the items of the first requests
-    // alone take their sum over the CUs and about half of the last one's length, and no less than the longest.
+    // One KV head on its share of the CUs, in the order of the list: the items of the first requests alone take their sum
+    // over the CUs and a part of the last one's length, no less than the longest, and no less than some CU
+    // takes that has as many of them as the others or one more.
     const double cus = (double)num_cus() / kv_heads;
-    double work = 0.0, most = 0.0;
+    double work = 0.0, most = 0.0, items = 0.0, shortest = 1e30; // of the items so far
     for (int i = 0; i < n; ++i) {
         const MixedRequest &m = req[i];
         // as splits_of_request; a decode request has at most kMaxSplits ranges by the choice of dec_blocks
@@ -1701,7 +1712,10 @@ double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks,
         const double us = (double)m.units * (ns * kItemUs + m.mean * step);
         work += m.decode ? us / kWaves : us;
         const double item = kItemUs + step * ((m.length + ns - 1) / ns);
-        most = std::max(most, std::max(item, work / cus + 0.5 * item));
+        most = std::max(most, std::max(item, work / cus + c.end * item));
+        items += (double)(m.units * ns) / (m.decode ? kWaves : 1);
+        shortest = std::min(shortest, kItemUs + step * m.mean / ns);
+        if (c.rounds) most = std::max(most, std::ceil(items / cus) * shortest);
         (m.decode ? pl.dec_units : pl.row_items) += m.units * ns;
         pl.nsplit = std::max(pl.nsplit, ns);
         if (ns > 1) {
@@ -1710,7 +1724,7 @@ double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks,
         }
     }
     double us = most;
-    if (pl.part_rows > 0) us += kMergeUs + 2.0 * (double)part_bytes((size_t)pl.part_rows, q_heads) / kPartBytesPerUs;
+    if (pl.part_rows > 0) us += c.merge_us + 2.0 * (double)part_bytes((size_t)pl.part_rows, q_heads) / c.part_bytes_per_us;
     return us;
 }
 
@@ -1773,7 +1787,7 @@ bool plan_mixed(const cp_shape *s, size_t room, int tile_shift, Plan &best, uint
         const int dec = std::max(std::max(least, (int)(seg * (kTileUs / kBlockUs))), (blocks + kMaxSplits - 1) / kMaxSplits);
         Plan pl{0, 0, 1, false, 1};
         pl.tile_shift = tile_shift;
-        const double us = mixed_cost(req, n, seg, dec, s->num_kv_heads, s->num_q_heads, tile_us, pl);
+        const double us = mixed_cost(req, n, seg, dec, s->num_kv_heads, s->num_q_heads, tile_us, tile_shift == kWholeHeads ? kUnequalOfWholeHeads : kUnequal, pl);
         if (pl.part_rows > INT32_MAX / 2 || (pl.part_rows > 0 && part_bytes((size_t)pl.part_rows, s->num_q_heads) > room)) continue;
         if ((pl.row_items + (pl.dec_units + kWaves - 1) / kWaves) * s->num_kv_heads > INT32_MAX / 2) continue;
         worse = best_us >= 0.0 && us >= best_us ? worse + 1 : 0;
@@ -1807,12 +1821,12 @@ void row_tiled_extent(const cp_shape *s, int tile_shift, int64_t &q_tiles, int32
 // Against ranges of at least 8 tiles, two workgroups per CU: P = 512, E = 128, 8/2 heads (4 workgroups
 // of 10 tiles before) 25.2 -> 19.0 us; 4 requests, P = 3000, E = 128, 32/8 heads 61 -> 45; 1 request,
 // P = 2000, E = 700, 64/8 heads 100 -> 72; 12 requests, P = 20000, E = 128, 32/8 heads 538 -> 496.
-constexpr double kLastItem = 0.75; // of its length, behind the others
 void choose_splits(const cp_shape *s, size_t room, Plan &pl, double *estimate)
 {
     const double tile_us = pl.tile_shift == kTileShift - 1 ? kHalfTileUs : kTileUs;
     const bool mixed = s->batch <= kMixedMaxBatch && !equal_lengths(s); // a plan to compare this one with
     bool alike = true;
+    const UnequalCosts &c = pl.tile_shift == kWholeHeads ? kUnequalOfWholeHeads : kUnequal;
     const int64_t items = pl.q_tiles * s->num_kv_heads, cus = num_cus();
     const int G = s->num_q_heads / s->num_kv_heads;
     double tiles = 0.0; // key tiles of all items
@@ -1835,12 +1849,12 @@ void choose_splits(const cp_shape *s, size_t room, Plan &pl, double *estimate)
         const double mean = kItemUs + tile_us * tiles / ((double)items * ns);
         double us = longest;
         if (items * ns > cus && mixed)
-            us = std::max(us, mean * ((double)(items * ns) / (double)cus) + kLastItem * longest);
+            us = std::max(us, mean * ((double)(items * ns) / (double)cus) + c.last_item * longest);
         else if (items * ns > cus)
             us = std::max(us, alike ? (double)((items * ns + cus - 1) / cus) * mean : mean * ((double)(items * ns) / (double)cus + 0.5));
         if (ns > 1) us += kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
         if (ns == 1 || us < best_us) {
-            best_us = ns == 1 ? 0.85 * us : us; // a split has to promise more than the estimate is off by
+            best_us = ns == 1 ? c.unsplit * us : us; // a split has to promise more than the estimate is off by
             pl.nsplit = ns;
             *estimate = us;
         }
@@ -2141,15 +2155,15 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
     if (pl.tail_units > 0) return part_bytes((size_t)pl.tail_units * (size_t)pl.nsplit * kBM, s->num_kv_heads);
     return part_bytes((size_t)pl.nsplit * (size_t)s->total_extend, s->num_q_heads);
 }
-// The same of the best plan with tiles of whole heads, in one number of key ranges or request by request.
-size_t workspace_of_whole_heads(const cp_shape *s)
+// The best plan with tiles of whole heads, in one number of key ranges or request by request; nothing runs it.
+Plan plan_of_whole_heads(const cp_shape *s)
 {
     Plan pl = make_plan(s);
-    if (pl.decode || s->num_splits >= 1) return workspace_for(s, pl);
+    if (pl.decode || s->num_splits >= 1) return pl;
     int64_t max_n = 0;
     for (int r = 0; r < s->batch; ++r)
         if (s->h_extend_lens[r] > 0) max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
-    if (max_n == 0) return 0;
+    if (max_n == 0) return pl;
     pl = Plan{0, 0, 1, false, 1};
     pl.tile_shift = kWholeHeads;
     row_tiled_extent(s, kWholeHeads, pl.q_tiles, pl.max_key_tiles);
@@ -2159,9 +2173,10 @@ size_t workspace_of_whole_heads(const cp_shape *s)
     Plan mixed{0, 0, 1, false, 1};
     if (s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, SIZE_MAX, kWholeHeads, mixed, nullptr, &mixed_us) &&
         mixed_us + kMixedUs < us)
-        return workspace_for(s, mixed);
-    return workspace_for(s, pl);
+        return mixed;
+    return pl;
 }
+size_t workspace_of_whole_heads(const cp_shape *s) { return workspace_for(s, plan_of_whole_heads(s)); }
 // What the launches touch of it: of a decode-shaped call the partial results of the workgroups that share a
 // request's keys, at most nsplit, none where one workgroup has them all.
 size_t scratch_used(const cp_shape *s, const Plan &pl)
@@ -2332,7 +2347,9 @@ const char *cp_status_string(int status)
 int32_t cp_num_splits(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return 0;
-    return make_plan(shape).nsplit;
+    const Plan pl = make_plan(shape);
+    // of a batch split request by request a bound, for which cp_workspace_bytes has room
+    return pl.mixed ? std::max(pl.nsplit, plan_of_whole_heads(shape).nsplit) : pl.nsplit;
 }
 
 int32_t cp_plan_kind(const cp_shape *shape)
