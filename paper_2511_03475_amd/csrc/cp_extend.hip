@@ -2024,6 +2024,21 @@ bool small_call(const cp_shape *s, int64_t max_n, double &us, Plan &pl)
 // batches of 2 to 64 requests 92 were more than 6 % slower than with one number of ranges of at least 8 tiles as long as
 // all were split request by request; 10 are.
 constexpr double kMixedUs = 2.0;
+// The best plan with tiles of whole heads, in one number of key ranges or request by request; nothing runs its row tiles.
+// max_n: the most keys of a request.
+Plan plan_of_whole_heads(const cp_shape *s, size_t room, int64_t max_n)
+{
+    Plan pl{0, 0, 1, false, 1}, mixed{0, 0, 1, false, 1};
+    pl.tile_shift = kWholeHeads;
+    row_tiled_extent(s, kWholeHeads, pl.q_tiles, pl.max_key_tiles);
+    double us, mixed_us;
+    choose_splits(s, room, pl, &us);
+    if (small_call(s, max_n, us, pl)) pl.nsplit = 1;
+    if (s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, room, kWholeHeads, mixed, nullptr, &mixed_us) &&
+        mixed_us + kMixedUs < us)
+        return mixed;
+    return pl;
+}
 // `room`: bytes that the caller has for partial results.
 // `order`: receives MixedParams::order of a mixed plan.
 Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullptr)
@@ -2060,9 +2075,27 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
         pl.nsplit = s->num_splits;
         return pl;
     }
+    if (max_e == 0) return pl;
     double us = 0.0;
     const bool equal = equal_lengths(s), compare = !equal && s->batch <= kMixedMaxBatch; // with a plan that splits by request
-    if (max_e == 0) return pl;
+    // The estimates for tiles of whole heads decide which rows the decode kernel's form computes, alone or next to row tiles:
+    // it scales the scores, the row-tiled kernel rounds the scaled query to 16 bits.  By the estimates for today's tiles,
+    // which are lower, 60 of 8022 random equal shapes that are not decode-shaped and 1487 of 10817 unequal ones would go over
+    // to row tiles.
+    bool beside = false; // decode-shaped requests next to others
+    int64_t blocks = 0;
+    for (int r = 0; r < s->batch; ++r) {
+        beside = beside || (compare && s->h_extend_lens[r] > 0 && decode_shaped(s->h_extend_lens[r], G));
+        blocks = std::max(blocks, ((int64_t)s->h_extend_lens[r] * G + kDecRows - 1) / kDecRows);
+    }
+    if (beside || blocks * s->batch * s->num_kv_heads <= num_cus()) {
+        Plan heads = plan_of_whole_heads(s, room, max_n);
+        if (heads.small) {
+            heads.tile_shift = kTileShift;
+            return heads;
+        }
+        beside = beside && heads.mixed;
+    }
     const bool by_items = equal || compare || pl.q_tiles * s->num_kv_heads < 2 * num_cus();
     if (by_items) equal ? choose_equal_splits(s, room, pl, &us) : choose_splits(s, room, pl, &us);
     Plan half{0, 0, 1, false, 1};
@@ -2089,7 +2122,7 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
             mixed = half;
             mixed_us = half_us + kHalfUs;
         } else if (!any) return pl;
-        if (mixed_us + kMixedUs < us) return mixed;
+        if ((beside && !pl.small) || mixed_us + kMixedUs < us) return mixed;
     }
     return pl;
 }
@@ -2155,26 +2188,15 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
     if (pl.tail_units > 0) return part_bytes((size_t)pl.tail_units * (size_t)pl.nsplit * kBM, s->num_kv_heads);
     return part_bytes((size_t)pl.nsplit * (size_t)s->total_extend, s->num_q_heads);
 }
-// The best plan with tiles of whole heads, in one number of key ranges or request by request; nothing runs it.
+// plan_of_whole_heads for any call and room.
 Plan plan_of_whole_heads(const cp_shape *s)
 {
-    Plan pl = make_plan(s);
+    const Plan pl = make_plan(s);
     if (pl.decode || s->num_splits >= 1) return pl;
     int64_t max_n = 0;
     for (int r = 0; r < s->batch; ++r)
         if (s->h_extend_lens[r] > 0) max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
-    if (max_n == 0) return pl;
-    pl = Plan{0, 0, 1, false, 1};
-    pl.tile_shift = kWholeHeads;
-    row_tiled_extent(s, kWholeHeads, pl.q_tiles, pl.max_key_tiles);
-    double us, mixed_us;
-    choose_splits(s, SIZE_MAX, pl, &us);
-    if (small_call(s, max_n, us, pl)) pl.nsplit = 1;
-    Plan mixed{0, 0, 1, false, 1};
-    if (s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, SIZE_MAX, kWholeHeads, mixed, nullptr, &mixed_us) &&
-        mixed_us + kMixedUs < us)
-        return mixed;
-    return pl;
+    return max_n == 0 ? pl : plan_of_whole_heads(s, SIZE_MAX, max_n);
 }
 size_t workspace_of_whole_heads(const cp_shape *s) { return workspace_for(s, plan_of_whole_heads(s)); }
 // What the launches touch of it: of a decode-shaped call the partial results of the workgroups that share a
@@ -2349,7 +2371,7 @@ int32_t cp_num_splits(const cp_shape *shape)
     if (validate(shape) != CP_OK) return 0;
     const Plan pl = make_plan(shape);
     // of a batch split request by request a bound, for which cp_workspace_bytes has room
-    return pl.mixed ? std::max(pl.nsplit, plan_of_whole_heads(shape).nsplit) : pl.nsplit;
+    return pl.mixed && pl.nsplit > 1 ? std::max(pl.nsplit, plan_of_whole_heads(shape).nsplit) : pl.nsplit;
 }
 
 int32_t cp_plan_kind(const cp_shape *shape)

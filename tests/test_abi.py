@@ -114,6 +114,17 @@ def test_long_batches_of_unequal_lengths_are_split_request_by_request(lib):
     assert cp.cp_plan_kind(sh) == 2 and 130 < rows < cp.cp_num_splits(sh) * 160
 
 
+@pytest.mark.parametrize("P,E,Hq,Hkv,kind,splits", [
+    ([4580] * 8, [67] * 8, 12, 1, 3, 1), ([3259] * 3, [55] * 3, 32, 8, 3, 1), ([0] * 8, [23] * 8, 40, 8, 3, 1),   # small
+    ([472, 1, 16, 0, 2961, 157], [47, 8, 1, 158, 2, 170], 8, 2, 2, 24),                     # request by request
+])
+def test_rows_of_the_decode_form_stay_in_it(lib, P, E, Hq, Hkv, kind, splits):
+    """Row tiles round the scaled query to 16 bits, which the decode kernel's form does not: a lower estimate for row
+    tiles takes no small call and no batch with decode-shaped requests over to them."""
+    sh = _shape(P, E, Hq=Hq, Hkv=Hkv)
+    assert (cp.cp_plan_kind(sh), cp.cp_num_splits(sh)) == (kind, splits)
+
+
 def test_invalid_shapes_are_rejected_on_the_host(lib):
     bad = [
         _shape([32], [32], Hq=4, Hkv=3),           # Hq % Hkv != 0
