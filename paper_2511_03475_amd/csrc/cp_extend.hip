@@ -746,9 +746,15 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
     const int np_tiles = (P + kBN - 1) / kBN;        // prefix key tiles
     const int ns_tiles = (rows_end + kBN - 1) / kBN; // suffix key tiles up to the diagonal
     const int n_tiles = np_tiles + ns_tiles;
-    // mixed: a row tile with fewer keys than the last one of its request takes fewer ranges, the rest stay empty
+    // mixed: a row tile with fewer keys than the last one of its request takes fewer ranges, the rest stay empty.  None is
+    // longer than the last one's: with ranges up to seg_tiles, which the last one's need not reach, a tile of 15 key tiles
+    // next to one of 16 in 2 ranges was left whole (20 requests, of which 16 decode, 32/8 heads: 39.4 us with ranges of
+    // at most 15 key tiles, 29.6 of at most 11).  250 random batches take 0.996 of the time, 0.875 to 1.042.
     int n_ranges = nsplit;
-    if constexpr (kMode == kMixed) n_ranges = min(nsplit, (n_tiles + p.seg_tiles - 1) / p.seg_tiles);
+    if constexpr (kMode == kMixed) {
+        const int longest = (np_tiles + (E + kBN - 1) / kBN + nsplit - 1) / nsplit;
+        n_ranges = min(nsplit, (n_tiles + longest - 1) / longest);
+    }
     const int per_split = (n_tiles + n_ranges - 1) / n_ranges;
     const int kt_begin = split * per_split;
     const int kt_end = min(n_tiles, kt_begin + per_split);

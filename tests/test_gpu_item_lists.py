@@ -294,3 +294,14 @@ def test_more_scratch_than_asked_for_changes_nothing(H, Hq, Hkv, P, E):
     cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table, case.prefix_lens,
                            case.extend_lens, case.out, torch.cuda.current_stream(), case.shape, space, space.numel())
     assert (case.out_bits() == want).all()
+
+
+@pytest.mark.parametrize("P,E,Hq,Hkv", [
+    ([86, 2657, 810, 125, 3000], [1, 1, 167, 114, 1], 32, 8),      # row tiles of 14, 15 and 16 key tiles, 2 ranges
+    ([5000, 0, 640, 12], [200, 1, 448, 1], 8, 2),                  # several ranges, more row tiles
+    ([30, 900], [1, 700], 6, 3),
+])
+def test_row_tiles_with_fewer_keys_than_their_requests_last(H, P, E, Hq, Hkv):
+    """The ranges of a request split on its own: none longer than those of its last row tile, some of them empty."""
+    w = W.make_uniform("ranges", 71, len(P), Hq, Hkv, P, E)
+    _check(H.gpu_attention(w), oracle.attention_of(w), f"P={P} E={E}")
