@@ -2197,12 +2197,15 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
 // plan_of_whole_heads for any call and room.
 Plan plan_of_whole_heads(const cp_shape *s)
 {
-    const Plan pl = make_plan(s);
-    if (pl.decode || s->num_splits >= 1) return pl;
-    int64_t max_n = 0;
-    for (int r = 0; r < s->batch; ++r)
-        if (s->h_extend_lens[r] > 0) max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
-    return max_n == 0 ? pl : plan_of_whole_heads(s, SIZE_MAX, max_n);
+    int64_t max_e = 0, max_n = 0;
+    for (int r = 0; r < s->batch; ++r) {
+        if (s->h_extend_lens[r] == 0) continue;
+        max_e = std::max<int64_t>(max_e, s->h_extend_lens[r]);
+        max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
+    }
+    const int G = s->num_q_heads / s->num_kv_heads;
+    if (s->num_splits >= 1 || max_e * G <= kDecRows * kDecMaxRowBlocks) return make_plan(s); // it has no row tiles, or no choice
+    return plan_of_whole_heads(s, SIZE_MAX, max_n);
 }
 size_t workspace_of_whole_heads(const cp_shape *s) { return workspace_for(s, plan_of_whole_heads(s)); }
 // What the launches touch of it: of a decode-shaped call the partial results of the workgroups that share a
