@@ -2194,8 +2194,8 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
     if (pl.tail_units > 0) return part_bytes((size_t)pl.tail_units * (size_t)pl.nsplit * kBM, s->num_kv_heads);
     return part_bytes((size_t)pl.nsplit * (size_t)s->total_extend, s->num_q_heads);
 }
-// plan_of_whole_heads for any call and room.
-Plan plan_of_whole_heads(const cp_shape *s)
+// plan_of_whole_heads for any call.
+Plan plan_of_whole_heads(const cp_shape *s, size_t room = SIZE_MAX)
 {
     int64_t max_e = 0, max_n = 0;
     for (int r = 0; r < s->batch; ++r) {
@@ -2204,8 +2204,8 @@ Plan plan_of_whole_heads(const cp_shape *s)
         max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
     }
     const int G = s->num_q_heads / s->num_kv_heads;
-    if (s->num_splits >= 1 || max_e * G <= kDecRows * kDecMaxRowBlocks) return make_plan(s); // it has no row tiles, or no choice
-    return plan_of_whole_heads(s, SIZE_MAX, max_n);
+    if (s->num_splits >= 1 || max_e * G <= kDecRows * kDecMaxRowBlocks) return make_plan(s, room); // it has no row tiles, or no choice
+    return plan_of_whole_heads(s, room, max_n);
 }
 size_t workspace_of_whole_heads(const cp_shape *s) { return workspace_for(s, plan_of_whole_heads(s)); }
 // What the launches touch of it: of a decode-shaped call the partial results of the workgroups that share a
@@ -2423,11 +2423,16 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
         if (chk != CP_OK) return chk;
     }
     const size_t room = workspace ? workspace_bytes : 0;
-    const Plan pl = planned ? *planned : make_plan(shape, room, p.order);
-    const size_t need = scratch_used(shape, pl);
+    Plan pl = planned ? *planned : make_plan(shape, room, p.order);
     if (!planned && too_little_scratch(shape, pl, room)) return CP_ERR_WORKSPACE;
-    // a misaligned buffer is the caller's mistake wherever the shape asks for one
-    if (workspace && !aligned_to(workspace, 256) && (need > 0 || (!pl.decode && workspace_of_whole_heads(shape) > 0))) return CP_ERR_WORKSPACE;
+    if (workspace && !aligned_to(workspace, 256)) {
+        // The caller's mistake where row tiles of whole heads asked for scratch, which is where this has been one.  Calls that
+        // ask for some only with today's tiles run with such a buffer as without one.
+        const Plan heads = plan_of_whole_heads(shape, room);
+        if (scratch_used(shape, heads) > 0) return CP_ERR_WORKSPACE;
+        if (scratch_used(shape, pl) > 0) pl = make_plan(shape, 0, p.order);
+    }
+    const size_t need = scratch_used(shape, pl);
     const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves :
                              pl.tail_units > 0 ? pl.q_tiles + pl.tail_units * (int64_t)(pl.nsplit - 1) : pl.q_tiles * pl.nsplit;
     const int64_t total = per_head * shape->num_kv_heads;

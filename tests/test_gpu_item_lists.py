@@ -305,3 +305,28 @@ def test_row_tiles_with_fewer_keys_than_their_requests_last(H, P, E, Hq, Hkv):
     """The ranges of a request split on its own: none longer than those of its last row tile, some of them empty."""
     w = W.make_uniform("ranges", 71, len(P), Hq, Hkv, P, E)
     _check(H.gpu_attention(w), oracle.attention_of(w), f"P={P} E={E}")
+
+
+@pytest.mark.parametrize("P,E,Hq,Hkv", [
+    ([1500] * 33, [70] * 33, 8, 8),                        # equal requests, the last round split
+    ([765, 885, 278, 30], [98, 337, 295, 347], 32, 8),     # split request by request
+])
+@pytest.mark.parametrize("off", [16, 128])
+def test_a_misaligned_buffer_where_whole_head_tiles_asked_for_none(H, P, E, Hq, Hkv, off):
+    """Row tiles of whole heads needed no scratch for these shapes, so a buffer that is not aligned was accepted
+    and not looked at: the call runs as one without a buffer does, and leaves it alone."""
+    import torch
+
+    import paper_2511_03475_amd as cp
+
+    case = H.DeviceCase(W.make_uniform("misaligned", 74, len(P), Hq, Hkv, P, E))
+    assert case.ws_bytes > 0
+    run = lambda space, size: cp.cp_extend_attention(case.q, case.k_new, case.v_new, case.kv_pages, case.block_table,  # noqa: E731
+                                                     case.prefix_lens, case.extend_lens, case.out,
+                                                     torch.cuda.current_stream(), case.shape, space, size)
+    run(None, 0)
+    want = case.out_bits().copy()
+    case.out.fill_(0x1234)
+    space = torch.full((case.ws_bytes + 512,), 0x5A, dtype=torch.uint8, device="cuda:0")
+    run(space[off:], case.ws_bytes)
+    assert (case.out_bits() == want).all() and (space == 0x5A).all()
