@@ -82,7 +82,9 @@ struct AttnParams {
     float scale_log2;       // softmax_scale * log2(e)
     uint32_t g_magic;       // see over_heads, 0: plain division
 };
-constexpr int kMixedMaxBatch = 512; // requests of a mixed batch; beyond, planning costs the host more than the call takes
+// Requests of a mixed batch: their order travels in the kernel's arguments.  Planning 512 takes the host 23 us, the call 85 if
+// they are short (up to 100 cached tokens, a fifth of them with up to 60 new ones, the others with one; 32/8 heads).
+constexpr int kMixedMaxBatch = 512;
 struct MixedParams : AttnParams {
     int32_t seg_tiles;  // key tiles per work item of a row-tiled request, at most
     int32_t dec_blocks; // key blocks of 32 per wavefront of a decode-shaped request, at most
@@ -1644,22 +1646,145 @@ bool equal_lengths(const cp_shape *s)
     return true;
 }
 
-// Row tiles of a request as a plan counts them.  kWholeHeads: tiles of 256 rows that take the rows of 1, 2, 4 or 8 whole
-// q heads, the least number that leaves none of these smaller than E allows.  No kernel runs these any more, but
-// callers have sized their scratch by them: see too_little_scratch.
-constexpr int kWholeHeads = -1;
-int64_t planned_tiles(int64_t E, int G, int tile_shift)
+// The row tiles that a plan counts: of 256 rows, of 128, or of the rows of 1, 2, 4 or 8 whole q heads, the least number
+// that leaves no head fewer rows than E.  No kernel runs the last ones any more, but callers have sized
+// their scratch by them: see too_little_scratch.
+enum TileKind { kFullTiles, kHalfTiles, kWholeHeads, kTileKinds };
+constexpr int shift_of(TileKind kind) { return kind == kHalfTiles ? kTileShift - 1 : kTileShift; }
+struct TileCount {
+    int64_t tiles;   // of one request and KV head
+    int64_t lengths; // how many of them have different numbers of keys
+};
+TileCount count_tiles(int64_t E, int G, TileKind kind)
 {
-    if (tile_shift != kWholeHeads) return row_tiles((int)E, G, tile_shift);
-    int heads = 1;
-    while (heads < 8 && G % (2 * heads) == 0 && E * (heads * 2) <= kBM) heads *= 2;
-    return (E * heads + kBM - 1) / kBM * (G / heads);
+    if (kind != kWholeHeads) {
+        const int64_t n = row_tiles((int)E, G, shift_of(kind));
+        return {n, n};
+    }
+    int shift = 0; // the heads' logarithm
+    while (shift < 3 && (G & ((2 << shift) - 1)) == 0 && E << (shift + 1) <= kBM) ++shift;
+    return {((E << shift) + kBM - 1) / kBM * (G >> shift), (E + kBM - 1) / kBM};
 }
-// ... and how many of them have different numbers of keys
-int64_t tile_lengths(int64_t E, int G, int tile_shift)
+
+// What the plans of a call are made from.  A call is planned up to four times (tiles of 256 rows and of 128,
+// tiles of whole heads, less scratch); its lengths are read and its requests sorted once for all of them, and a search ends
+// where its answer is known.  With a table, a sort and a search to the end for every plan the host of an MI355X took 4.0 us for a batch
+// of 40 requests, 32 of which decode, now 1.8; for 512, 410 of which do, 53 and 23; for 32 equal ones, 128 new tokens, 0.54 and 0.06.
+struct RowWork { // of one kind of tile
+    int64_t q_tiles = 0; // row tiles of a KV head
+    double tiles = 0.0;  // key tiles of all row tiles and KV heads
+    bool alike = true;   // no request has row tiles of different lengths
+    bool known = false;
+};
+class Requests {
+public:
+    explicit Requests(const cp_shape *s);
+    const RowWork &work(TileKind kind);                          // fills units[kind] and mean[kind] too
+    void write_order(uint8_t *order) const;                      // MixedParams::order
+
+    const cp_shape *const s;
+    const int G;
+    bool equal = true;        // all requests have the same lengths
+    bool by_request = false;  // a plan that splits request by request is one to look at, and what follows is there
+    bool decode_rows = false; // some, not all, are decode-shaped
+    int64_t max_e = 0, max_n = 0;  // most new tokens, most keys
+    int64_t row_blocks = 0;        // blocks of 32 rows per KV head, the most of a request
+    int32_t max_key_tiles = 0;
+    int64_t decode_work = 0;       // key blocks of all decode wavefronts
+    int64_t all_dec_units = 0;     // row blocks of all decode-shaped requests
+    int32_t key_blocks = 1;        // of 32, the most of a decode-shaped request
+    int32_t range_tiles = 1;       // key tiles of the longest request, with two blocks of a decode-shaped one to a tile
+    // Requests with new tokens: row-tiled ones first, most keys first
+    int32_t n = 0, row_tiled = 0;  // all, and how many are row-tiled
+    int32_t index[kMixedMaxBatch]; // in the batch
+    int32_t extend[kMixedMaxBatch];
+    int32_t length[kMixedMaxBatch];            // key tiles of the last row tile, or key blocks of 32
+    int32_t dec_units[kMixedMaxBatch];         // row blocks of a decode-shaped request
+    int64_t units[kTileKinds][kMixedMaxBatch]; // row tiles of a row-tiled one
+    float mean[kTileKinds][kMixedMaxBatch];    // key tiles of a row tile on average
+
+private:
+    RowWork work_[kTileKinds];
+    int16_t place_[kMixedMaxBatch]; // in the arrays above, by request
+};
+
+Requests::Requests(const cp_shape *shape) : s(shape), G(shape->num_q_heads / shape->num_kv_heads)
 {
-    const int64_t nt = planned_tiles(E, G, tile_shift);
-    return tile_shift == kWholeHeads && E > 0 ? (E + kBM - 1) / kBM : nt;
+    const int32_t *const prefix = s->h_prefix_lens, *const added = s->h_extend_lens;
+    for (int r = 1; r < s->batch && equal; ++r) equal = prefix[r] == prefix[0] && added[r] == added[0];
+    by_request = !equal && s->batch <= kMixedMaxBatch;
+    uint64_t key[kMixedMaxBatch];
+    for (int r = 0; r < (equal ? 1 : s->batch); ++r) {
+        const int32_t P = prefix[r], E = added[r];
+        if (E == 0) continue;
+        max_e = std::max<int64_t>(max_e, E);
+        max_n = std::max<int64_t>(max_n, (int64_t)P + E);
+        const int32_t tiles = (P + kBN - 1) / kBN + (E + kBN - 1) / kBN;
+        max_key_tiles = std::max(max_key_tiles, tiles);
+        if (!by_request) continue;
+        const bool decode = decode_shaped(E, G);
+        const int32_t keys = decode ? (P + E + 31) / 32 : tiles;
+        decode_rows = decode_rows || decode;
+        row_tiled += !decode;
+        key[n++] = (uint64_t)decode << 63 | (uint64_t)(INT32_MAX - keys) << 32 | (uint32_t)r;
+    }
+    row_blocks = (max_e * G + kDecRows - 1) / kDecRows;
+    if (!by_request) return;
+    std::sort(key, key + n);
+    for (int i = 0; i < n; ++i) {
+        const int r = (int)(uint32_t)key[i];
+        index[i] = r;
+        place_[r] = (int16_t)i;
+        extend[i] = added[r];
+        length[i] = INT32_MAX - (int32_t)(key[i] >> 32 & INT32_MAX);
+        if (i < row_tiled) continue;
+        dec_units[i] = (extend[i] * G + kDecRows - 1) / kDecRows;
+        all_dec_units += dec_units[i];
+        decode_work += (int64_t)dec_units[i] * length[i] * s->num_kv_heads;
+    }
+    if (row_tiled > 0) range_tiles = std::max(range_tiles, length[0]);
+    if (row_tiled < n) {
+        key_blocks = std::max(key_blocks, length[row_tiled]);
+        range_tiles = std::max(range_tiles, (length[row_tiled] + 1) / 2);
+    }
+}
+
+const RowWork &Requests::work(TileKind kind)
+{
+    RowWork &w = work_[kind];
+    if (w.known) return w;
+    w.known = true;
+    const int batch = equal ? 1 : s->batch;
+    for (int r = 0; r < batch; ++r) {
+        const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
+        if (E == 0) continue;
+        const TileCount c = count_tiles(E, G, kind);
+        const int64_t before = (P + kBN - 1) / kBN, own = (E + kBN - 1) / kBN;
+        w.alike = w.alike && c.lengths == 1;
+        w.q_tiles += c.tiles;
+        w.tiles += (double)c.tiles * s->num_kv_heads * ((double)before + 0.5 * (double)own * (1.0 + 1.0 / (double)c.lengths));
+        if (!by_request || place_[r] >= row_tiled) continue;
+        units[kind][place_[r]] = c.tiles;
+        mean[kind][place_[r]] = (float)before + 0.5f * (float)own * (1.f + 1.f / (float)c.lengths);
+    }
+    if (equal) {
+        w.q_tiles *= s->batch;
+        w.tiles *= s->batch;
+    }
+    return w;
+}
+
+void Requests::write_order(uint8_t *order) const
+{
+    int at[kMixedMaxBatch / 64];
+    for (int g = 0; g < kMixedMaxBatch / 64; ++g) at[g] = 64 * g;
+    bool placed[kMixedMaxBatch] = {};
+    for (int i = 0; i < n; ++i) {
+        order[at[index[i] / 64]++] = (uint8_t)(index[i] % 64);
+        placed[index[i]] = true;
+    }
+    for (int r = 0; r < (s->batch + 63) / 64 * 64; ++r) // no new tokens, or behind the batch's last request
+        if (!placed[r]) order[at[r / 64]++] = (uint8_t)(r % 64);
 }
 
 size_t part_bytes(size_t rows, int heads)
@@ -1688,99 +1813,64 @@ struct UnequalCosts {
     bool rounds; // items of one length take whole rounds over the CUs
 };
 constexpr UnequalCosts kUnequal{0.4, 6.0, 3.2e6, 0.5, 1.0, true}, kUnequalOfWholeHeads{0.5, kMergeUs, kPartBytesPerUs, 0.75, 0.85, false};
-struct MixedRequest {
-    int64_t units;  // row tiles, or row blocks of decode-shaped work
-    int32_t extend; // new tokens
-    int32_t length; // key tiles of the last row tile, or key blocks of 32
-    float mean;     // key tiles or blocks of a unit on average
-    int32_t r;      // index in the batch
-    bool decode;
-};
+// x rounded up, for 0 <= x < 2^53
+inline double round_up(double x)
+{
+    const double whole = (double)(int64_t)x;
+    return whole < x ? whole + 1.0 : whole;
+}
 
-// Fills pl for at most seg_tiles key tiles per row-tiled item; returns the time.
-double mixed_cost(const MixedRequest *req, int n, int seg_tiles, int dec_blocks, int kv_heads, int q_heads, double tile_us,
-                  const UnequalCosts &c, Plan &pl)
+// Fills pl for at most seg_tiles key tiles per row-tiled item; returns the time, or any that is no less than `bound` if
+// that is too long, and then pl is not filled.
+double mixed_cost(const Requests &q, TileKind kind, int seg_tiles, int dec_blocks, const UnequalCosts &c, double bound, Plan &pl)
 {
     pl.mixed = true;
+    pl.tile_shift = shift_of(kind);
     pl.seg_tiles = seg_tiles;
     pl.dec_blocks = dec_blocks;
     // One KV head on its share of the CUs, in the order of the list: the items of the first requests alone take their sum
     // over the CUs and a part of the last one's length, no less than the longest, and no less than some CU
     // takes that has as many of them as the others or one more.
-    const double cus = (double)num_cus() / kv_heads;
+    const double per_cu = q.s->num_kv_heads / (double)num_cus(), tile_us = kind == kHalfTiles ? kHalfTileUs : kTileUs;
     double work = 0.0, most = 0.0, items = 0.0, shortest = 1e30; // of the items so far
-    for (int i = 0; i < n; ++i) {
-        const MixedRequest &m = req[i];
-        // as splits_of_request; a decode request has at most kMaxSplits ranges by the choice of dec_blocks
-        const int limit = m.decode ? dec_blocks : seg_tiles;
-        const int ns = std::min(kMaxSplits, (m.length + limit - 1) / limit);
-        const double step = m.decode ? kBlockUs : tile_us;
-        const double us = (double)m.units * (ns * kItemUs + m.mean * step);
-        work += m.decode ? us / kWaves : us;
-        const double item = kItemUs + step * ((m.length + ns - 1) / ns);
-        most = std::max(most, std::max(item, work / cus + c.end * item));
-        items += (double)(m.units * ns) / (m.decode ? kWaves : 1);
-        shortest = std::min(shortest, kItemUs + step * m.mean / ns);
-        if (c.rounds) most = std::max(most, std::ceil(items / cus) * shortest);
-        (m.decode ? pl.dec_units : pl.row_items) += m.units * ns;
+    // ranges as in splits_of_request; a decode request has at most kMaxSplits by the choice of dec_blocks
+    auto add = [&](int i, int limit, int64_t units, double mean, double step, double share) {
+        const int length = q.length[i], ns = length <= limit ? 1 : std::min(kMaxSplits, (length + limit - 1) / limit);
+        const double keys = mean * step, each = ns == 1 ? keys : keys / ns;
+        const int longest = ns == 1 ? length : (length + ns - 1) / ns;
+        work += (double)units * (ns * kItemUs + keys) * share;
+        const double item = kItemUs + step * longest;
+        most = std::max(most, std::max(item, work * per_cu + c.end * item));
+        items += (double)(units * ns) * share;
+        shortest = std::min(shortest, kItemUs + each);
+        if (c.rounds) most = std::max(most, round_up(items * per_cu) * shortest);
         pl.nsplit = std::max(pl.nsplit, ns);
         if (ns > 1) {
-            pl.merge_rows += m.extend;
-            pl.part_rows += (int64_t)ns * m.extend;
+            pl.merge_rows += q.extend[i];
+            pl.part_rows += (int64_t)ns * q.extend[i];
         }
-    }
+        return units * ns;
+    };
+    for (int i = 0; i < q.row_tiled && most < bound; ++i)
+        pl.row_items += add(i, seg_tiles, q.units[kind][i], q.mean[kind][i], tile_us, 1.0);
+    for (int i = q.row_tiled; i < q.n && most < bound; ++i)
+        pl.dec_units += add(i, dec_blocks, q.dec_units[i], (float)q.length[i], kBlockUs, 1.0 / kWaves);
     double us = most;
-    if (pl.part_rows > 0) us += c.merge_us + 2.0 * (double)part_bytes((size_t)pl.part_rows, q_heads) / c.part_bytes_per_us;
+    if (pl.part_rows > 0) us += c.merge_us + 2.0 * (double)part_bytes((size_t)pl.part_rows, q.s->num_q_heads) / c.part_bytes_per_us;
     return us;
 }
 
-// The best plan whose partial results fit into `room` bytes, and its time; false if there is none.
-bool plan_mixed(const cp_shape *s, size_t room, int tile_shift, Plan &best, uint8_t *order, double *estimate)
+// The best plan whose partial results fit into `room` bytes, and its time; false if there is none.  One that takes less
+// than `enough` ends the search.
+bool plan_mixed(Requests &q, size_t room, TileKind kind, Plan &best, double *estimate, double enough = -1.0)
 {
-    const double tile_us = tile_shift == kTileShift - 1 ? kHalfTileUs : kTileUs;
-    const int G = s->num_q_heads / s->num_kv_heads;
-    MixedRequest req[kMixedMaxBatch];
-    int n = 0;
-    int32_t tiles = 1, blocks = 1;
-    int64_t decode_work = 0; // key blocks of all decode wavefronts
-    for (int r = 0; r < s->batch; ++r) {
-        const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
-        if (E == 0) continue;
-        MixedRequest &m = req[n++];
-        m.r = r;
-        m.extend = (int32_t)E;
-        m.decode = decode_shaped((int)E, G);
-        if (m.decode) {
-            m.units = (E * G + kDecRows - 1) / kDecRows;
-            m.length = (int32_t)((P + E + 31) / 32);
-            m.mean = (float)m.length;
-            blocks = std::max(blocks, m.length);
-            decode_work += m.units * m.length * s->num_kv_heads;
-        } else {
-            const int64_t nt = tile_lengths(E, G, tile_shift);
-            const int32_t prefix = (int32_t)((P + kBN - 1) / kBN), own = (int32_t)((E + kBN - 1) / kBN);
-            m.units = planned_tiles(E, G, tile_shift);
-            m.length = prefix + own;
-            m.mean = (float)prefix + 0.5f * (float)own * (1.f + 1.f / (float)nt);
-        }
-        tiles = std::max(tiles, m.decode ? (m.length + 1) / 2 : m.length);
-    }
-    // row-tiled requests first, most keys first
-    std::sort(req, req + n, [](const MixedRequest &a, const MixedRequest &b) {
-        if (a.decode != b.decode) return b.decode;
-        return a.length != b.length ? a.length > b.length : a.r < b.r;
-    });
-    if (order) {
-        int at[kMixedMaxBatch / 64];
-        for (int g = 0; g < kMixedMaxBatch / 64; ++g) at[g] = 64 * g;
-        bool placed[kMixedMaxBatch] = {};
-        for (int i = 0; i < n; ++i) {
-            order[at[req[i].r / 64]++] = (uint8_t)(req[i].r % 64);
-            placed[req[i].r] = true;
-        }
-        for (int r = 0; r < (s->batch + 63) / 64 * 64; ++r) // no new tokens, or behind the batch's last request
-            if (!placed[r]) order[at[r / 64]++] = (uint8_t)(r % 64);
-    }
+    const cp_shape *const s = q.s;
+    const int tiles = q.range_tiles;
+    const RowWork &w = q.work(kind);
+    // No plan has more partial results or items than there is room for: then one that turns out too slow need not be
+    // added up to the end.
+    const int64_t most_rows = (int64_t)s->total_extend * kMaxSplits, most_items = (w.q_tiles + q.all_dec_units) * kMaxSplits * s->num_kv_heads;
+    const bool all_fit = most_rows <= INT32_MAX / 2 && most_items <= INT32_MAX / 2 && part_bytes((size_t)most_rows, s->num_q_heads) <= room;
     double best_us = -1.0;
     int worse = 0;
     for (int pieces = 1; pieces <= kMaxSplits && worse < 4; pieces += pieces < 8 ? 1 : pieces / 4) {
@@ -1789,35 +1879,26 @@ bool plan_mixed(const cp_shape *s, size_t room, int tile_shift, Plan &best, uint
         // A decode wavefront's chunk takes about as long as a row-tiled item, but is no shorter than
         // twice its share of the decode work (8 wavefronts per CU), 4 to 16 blocks: finer chunks only
         // give the merge more to read (21 requests, 218 MB of decode K/V: 16 blocks 49 us, 8: 52, 4: 57).
-        const int least = (int)std::min<int64_t>(16, std::max<int64_t>(4, 2 * decode_work / (8 * num_cus())));
-        const int dec = std::max(std::max(least, (int)(seg * (kTileUs / kBlockUs))), (blocks + kMaxSplits - 1) / kMaxSplits);
+        const int least = (int)std::min<int64_t>(16, std::max<int64_t>(4, 2 * q.decode_work / (8 * num_cus())));
+        const int dec = std::max(std::max(least, (int)(seg * (kTileUs / kBlockUs))), (q.key_blocks + kMaxSplits - 1) / kMaxSplits);
         Plan pl{0, 0, 1, false, 1};
-        pl.tile_shift = tile_shift;
-        const double us = mixed_cost(req, n, seg, dec, s->num_kv_heads, s->num_q_heads, tile_us, tile_shift == kWholeHeads ? kUnequalOfWholeHeads : kUnequal, pl);
+        const double us = mixed_cost(q, kind, seg, dec, kind == kWholeHeads ? kUnequalOfWholeHeads : kUnequal,
+                                     all_fit && best_us >= 0.0 ? best_us : HUGE_VAL, pl);
         if (pl.part_rows > INT32_MAX / 2 || (pl.part_rows > 0 && part_bytes((size_t)pl.part_rows, s->num_q_heads) > room)) continue;
         if ((pl.row_items + (pl.dec_units + kWaves - 1) / kWaves) * s->num_kv_heads > INT32_MAX / 2) continue;
         worse = best_us >= 0.0 && us >= best_us ? worse + 1 : 0;
         if (worse == 0) {
             best_us = us;
             best = pl;
+            if (us < enough) break;
         }
     }
     *estimate = best_us;
     return best_us >= 0.0;
 }
 
-// Row-tiled work of a call: work units per KV head, key tiles of the longest request.
-void row_tiled_extent(const cp_shape *s, int tile_shift, int64_t &q_tiles, int32_t &max_key_tiles)
-{
-    const int G = s->num_q_heads / s->num_kv_heads;
-    q_tiles = 0;
-    for (int r = 0; r < s->batch; ++r) {
-        const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
-        if (E == 0) continue;
-        q_tiles += planned_tiles(E, G, tile_shift);
-        max_key_tiles = std::max(max_key_tiles, (int32_t)((P + kBN - 1) / kBN + (E + kBN - 1) / kBN));
-    }
-}
+// A bound that is left out of a search counts for a little less, so that rounding cannot make it one that is not.
+constexpr double kNearly = 1.0 - 1e-9;
 
 // One number of key ranges for all requests: the least estimated time (see above).  A grid
 // of two workgroups per CU is not split: it gains nothing then.  Row tiles of one length run in whole
@@ -1827,23 +1908,17 @@ void row_tiled_extent(const cp_shape *s, int tile_shift, int64_t &q_tiles, int32
 // Against ranges of at least 8 tiles, two workgroups per CU: P = 512, E = 128, 8/2 heads (4 workgroups
 // of 10 tiles before) 25.2 -> 19.0 us; 4 requests, P = 3000, E = 128, 32/8 heads 61 -> 45; 1 request,
 // P = 2000, E = 700, 64/8 heads 100 -> 72; 12 requests, P = 20000, E = 128, 32/8 heads 538 -> 496.
-void choose_splits(const cp_shape *s, size_t room, Plan &pl, double *estimate)
+void choose_splits(Requests &q, TileKind kind, size_t room, Plan &pl, double *estimate)
 {
-    const double tile_us = pl.tile_shift == kTileShift - 1 ? kHalfTileUs : kTileUs;
-    const bool mixed = s->batch <= kMixedMaxBatch && !equal_lengths(s); // a plan to compare this one with
-    bool alike = true;
-    const UnequalCosts &c = pl.tile_shift == kWholeHeads ? kUnequalOfWholeHeads : kUnequal;
-    const int64_t items = pl.q_tiles * s->num_kv_heads, cus = num_cus();
-    const int G = s->num_q_heads / s->num_kv_heads;
-    double tiles = 0.0; // key tiles of all items
-    for (int r = 0; r < s->batch; ++r) {
-        const int64_t P = s->h_prefix_lens[r], E = s->h_extend_lens[r];
-        if (E == 0) continue;
-        const int64_t nt = tile_lengths(E, G, pl.tile_shift);
-        alike = alike && nt == 1;
-        tiles += (double)planned_tiles(E, G, pl.tile_shift) * s->num_kv_heads *
-                 ((double)((P + kBN - 1) / kBN) + 0.5 * (double)((E + kBN - 1) / kBN) * (1.0 + 1.0 / (double)nt));
-    }
+    const cp_shape *const s = q.s;
+    const RowWork &w = q.work(kind);
+    const double tile_us = kind == kHalfTiles ? kHalfTileUs : kTileUs;
+    const bool mixed = q.by_request; // a plan to compare this one with
+    const UnequalCosts &c = kind == kWholeHeads ? kUnequalOfWholeHeads : kUnequal;
+    const int64_t items = w.q_tiles * s->num_kv_heads, cus = num_cus();
+    pl.tile_shift = shift_of(kind);
+    pl.q_tiles = w.q_tiles;
+    pl.max_key_tiles = q.max_key_tiles;
     double best_us = 0.0;
     *estimate = 0.0;
     if (items >= 2 * cus && !mixed) return;
@@ -1851,14 +1926,17 @@ void choose_splits(const cp_shape *s, size_t room, Plan &pl, double *estimate)
     for (int32_t ns = 1; ns <= most; ++ns) {
         const size_t bytes = ns > 1 ? part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) : 0;
         if (bytes > room) break;
+        const double merge = ns > 1 ? kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs : 0.0;
+        // more ranges than CUs: no less than the work, whose part that grows with the ranges takes no more ranges from here on
+        if (ns > 1 && items * ns > cus && ((double)(items * ns) * kItemUs + tile_us * w.tiles) / (double)cus * kNearly + merge >= best_us) break;
         const double longest = kItemUs + tile_us * ((pl.max_key_tiles + ns - 1) / ns);
-        const double mean = kItemUs + tile_us * tiles / ((double)items * ns);
+        const double mean = kItemUs + tile_us * w.tiles / ((double)items * ns);
         double us = longest;
         if (items * ns > cus && mixed)
             us = std::max(us, mean * ((double)(items * ns) / (double)cus) + c.last_item * longest);
         else if (items * ns > cus)
-            us = std::max(us, alike ? (double)((items * ns + cus - 1) / cus) * mean : mean * ((double)(items * ns) / (double)cus + 0.5));
-        if (ns > 1) us += kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
+            us = std::max(us, w.alike ? (double)((items * ns + cus - 1) / cus) * mean : mean * ((double)(items * ns) / (double)cus + 0.5));
+        us += merge;
         if (ns == 1 || us < best_us) {
             best_us = ns == 1 ? c.unsplit * us : us; // a split has to promise more than the estimate is off by
             pl.nsplit = ns;
@@ -1881,10 +1959,10 @@ double rounds_us(double items, double cus, double work, double shortest, double 
 // Time of a key tile in the last row tile of a request, as a part of a full one's.  Up to four wavefronts with rows
 // have a SIMD each: 1.32 us a tile with one or two of them, 1.46 with four, 1.76, 1.88, 2.04, 2.16 with five to
 // eight (256 workgroups, no two with the same keys).
-double last_tile_share(int64_t E, int G, int tile_shift)
+double last_tile_share(int64_t E, int G, TileKind kind)
 {
     const int waves = (int)((E * G - 1) % kBM) / 32 + 1;
-    if (tile_shift < kTileShift) return 1.0;
+    if (kind != kFullTiles) return 1.0;
     return waves <= 4 ? 0.65 : 0.65 + 0.0875 * (waves - 4);
 }
 
@@ -1895,15 +1973,19 @@ double last_tile_share(int64_t E, int G, int tile_shift)
 // With 1, 2 or 4 KV heads and contiguous ranges for the XCDs (see work_item) there is no common last round.
 constexpr double kTailGain = 0.97; // of the time without
 bool contiguous_ranges(const cp_shape *s, const Plan &pl, int64_t items, int xcds);
-void choose_equal_splits(const cp_shape *s, size_t room, Plan &pl, double *estimate)
+void choose_equal_splits(const Requests &q, TileKind kind, size_t room, Plan &pl, double *estimate)
 {
+    const cp_shape *const s = q.s;
     const int G = s->num_q_heads / s->num_kv_heads, E = s->h_extend_lens[0], Hkv = s->num_kv_heads;
     const double cus = (double)num_cus() / Hkv; // that share the list of a KV head
-    const double tile_us = pl.tile_shift == kTileShift ? kTileUs : kHalfTileUs;
+    const double tile_us = kind == kHalfTiles ? kHalfTileUs : kTileUs;
+    pl.tile_shift = shift_of(kind);
     const int64_t nt = row_tiles(E, G, pl.tile_shift), units = nt * s->batch;
+    pl.q_tiles = units;
+    pl.max_key_tiles = q.max_key_tiles;
     auto own_tiles = [&](int64_t t) { return (double)((std::min<int64_t>(E, (((t + 1) << pl.tile_shift) + G - 1) / G) + kBN - 1) / kBN); };
     const double prefix = (double)(((int64_t)s->h_prefix_lens[0] + kBN - 1) / kBN);
-    const double last = last_tile_share(E, G, pl.tile_shift), one = nt == 1 ? last : 1.0;
+    const double last = last_tile_share(E, G, kind), one = nt == 1 ? last : 1.0;
     const double shortest = one * (prefix + own_tiles(0)), longest = one * (prefix + own_tiles(nt - 1));
     const double n = (double)units, tiles = ((double)(nt - 1) + last) * s->batch * (prefix + 0.5 * (own_tiles(0) + own_tiles(nt - 1)));
     double best_us = 0.0;
@@ -1911,9 +1993,9 @@ void choose_equal_splits(const cp_shape *s, size_t room, Plan &pl, double *estim
     for (int32_t ns = 1; ns <= most; ++ns) {
         const size_t bytes = ns > 1 ? part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) : 0;
         if (bytes > room) break;
-        double us = rounds_us(n * ns, cus, n * ns * kItemUs + tile_us * tiles, kItemUs + tile_us * shortest / ns,
-                              kItemUs + tile_us * std::ceil(longest / ns));
-        if (ns > 1) us += kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
+        const double merge = ns > 1 ? kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs : 0.0, work = n * ns * kItemUs + tile_us * tiles;
+        if (ns > 1 && n * ns > cus && work / cus * kNearly + merge >= best_us) break; // nor do more ranges take less
+        const double us = rounds_us(n * ns, cus, work, kItemUs + tile_us * shortest / ns, kItemUs + tile_us * std::ceil(longest / ns)) + merge;
         if (ns == 1 || us < best_us) {
             best_us = ns == 1 ? 0.9 * us : us; // a split has to promise more than the estimate is off by
             pl.nsplit = ns;
@@ -2005,21 +2087,16 @@ constexpr double kSmallStartUs = 5.0, kSmallBlockUs = 2.0; // a workgroup; a blo
 // Of decode-shaped calls those with two row blocks and at most this many keys: 12 requests, 16 new tokens, 32/8
 // heads, P = 3546 34.7 us, 39.6 otherwise; 57, 9 new, 8/2 heads, P = 15646 250, which is more than estimated, and 171.
 constexpr int64_t kSmallDecodeKeys = 4096;
-bool small_call(const cp_shape *s, int64_t max_n, double &us, Plan &pl)
+bool fits_once(const Requests &q) { return q.row_blocks * q.s->batch * q.s->num_kv_heads <= num_cus(); }
+bool small_call(const Requests &q, double &us, Plan &pl)
 {
-    const int G = s->num_q_heads / s->num_kv_heads;
-    int64_t blocks = 0; // of rows, the most of a request
-    for (int r = 0; r < s->batch; ++r) {
-        const int64_t rows = (int64_t)s->h_extend_lens[r] * G;
-        blocks = std::max(blocks, (rows + kDecRows - 1) / kDecRows);
-    }
-    if (blocks * s->batch * s->num_kv_heads > num_cus()) return false;
-    const double length = std::ceil((double)((max_n + 31) / 32) / 8.0) * kSmallBlockUs;
+    if (!fits_once(q)) return false;
+    const double length = std::ceil((double)((q.max_n + 31) / 32) / 8.0) * kSmallBlockUs;
     if (kSmallStartUs + length >= us) return false;
     us = kSmallStartUs + length;
     pl.small = true;
     pl.dec_groups = 1;
-    pl.row_blocks = (int32_t)blocks;
+    pl.row_blocks = (int32_t)q.row_blocks;
     return true;
 }
 
@@ -2031,40 +2108,32 @@ bool small_call(const cp_shape *s, int64_t max_n, double &us, Plan &pl)
 // all were split request by request; 10 are.
 constexpr double kMixedUs = 2.0;
 // The best plan with tiles of whole heads, in one number of key ranges or request by request; nothing runs its row tiles.
-// max_n: the most keys of a request.
-Plan plan_of_whole_heads(const cp_shape *s, size_t room, int64_t max_n)
+// kind_only: whether it is small, or request by request, is all that is asked.
+Plan plan_of_whole_heads(Requests &q, size_t room, bool kind_only)
 {
     Plan pl{0, 0, 1, false, 1}, mixed{0, 0, 1, false, 1};
-    pl.tile_shift = kWholeHeads;
-    row_tiled_extent(s, kWholeHeads, pl.q_tiles, pl.max_key_tiles);
     double us, mixed_us;
-    choose_splits(s, room, pl, &us);
-    if (small_call(s, max_n, us, pl)) pl.nsplit = 1;
-    if (s->batch <= kMixedMaxBatch && !equal_lengths(s) && plan_mixed(s, room, kWholeHeads, mixed, nullptr, &mixed_us) &&
-        mixed_us + kMixedUs < us)
+    choose_splits(q, kWholeHeads, room, pl, &us);
+    if (small_call(q, us, pl)) pl.nsplit = 1;
+    const double limit = us - kMixedUs;
+    if (q.by_request && plan_mixed(q, room, kWholeHeads, mixed, &mixed_us, kind_only ? limit * kNearly : -1.0) && mixed_us + kMixedUs < us)
         return mixed;
     return pl;
 }
 // `room`: bytes that the caller has for partial results.
 // `order`: receives MixedParams::order of a mixed plan.
-Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullptr)
+Plan make_plan(Requests &q, size_t room = SIZE_MAX, uint8_t *order = nullptr)
 {
+    const cp_shape *const s = q.s;
     Plan pl{0, 0, 1, false, 1};
-    const int G = s->num_q_heads / s->num_kv_heads;
-    int64_t max_e = 0, max_n = 0;
-    for (int r = 0; r < s->batch; ++r) {
-        if (s->h_extend_lens[r] == 0) continue;
-        max_e = std::max<int64_t>(max_e, s->h_extend_lens[r]);
-        max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
-    }
-    if (s->num_splits == 0 && max_e > 0 && max_e * G <= kDecRows * kDecMaxRowBlocks) {
+    if (s->num_splits == 0 && q.max_e > 0 && q.max_e * q.G <= kDecRows * kDecMaxRowBlocks) {
         // Decode-shaped.  nsplit bounds the workgroups that may share a request's keys, and is what the
         // queries report: key chunks for 8 wavefronts per CU, at least 2 blocks of 32 keys each, a
         // multiple of the wavefronts of a workgroup.
-        pl.row_blocks = (int32_t)((max_e * G + kDecRows - 1) / kDecRows);
+        pl.row_blocks = (int32_t)q.row_blocks;
         const int64_t pairs = (int64_t)s->batch * s->num_kv_heads * pl.row_blocks;
         int64_t ns = (8LL * num_cus() + pairs - 1) / pairs;
-        const int64_t cap = ((max_n + 31) / 32 + 1) / 2;
+        const int64_t cap = ((q.max_n + 31) / 32 + 1) / 2;
         if (ns > cap) ns = cap;
         ns = (ns + kDecLeastWaves - 1) / kDecLeastWaves * kDecLeastWaves;
         if (ns > kDecMaxChunks) ns = kDecMaxChunks;
@@ -2072,64 +2141,63 @@ Plan make_plan(const cp_shape *s, size_t room = SIZE_MAX, uint8_t *order = nullp
         pl.nsplit = (int32_t)ns;
         pl.decode = true;
         double us;
-        choose_decode_groups(s, max_n, pl, &us);
-        if (pl.row_blocks > 1 && max_n <= kSmallDecodeKeys) small_call(s, max_n, us, pl);
+        choose_decode_groups(s, q.max_n, pl, &us);
+        if (pl.row_blocks > 1 && q.max_n <= kSmallDecodeKeys) small_call(q, us, pl);
         return pl;
     }
-    row_tiled_extent(s, kTileShift, pl.q_tiles, pl.max_key_tiles);
+    pl.q_tiles = q.work(kFullTiles).q_tiles;
+    pl.max_key_tiles = q.max_key_tiles;
     if (s->num_splits >= 1) {
         pl.nsplit = s->num_splits;
         return pl;
     }
-    if (max_e == 0) return pl;
-    double us = 0.0;
-    const bool equal = equal_lengths(s), compare = !equal && s->batch <= kMixedMaxBatch; // with a plan that splits by request
+    if (q.max_e == 0) return pl;
     // The estimates for tiles of whole heads decide which rows the decode kernel's form computes, alone or next to row tiles:
     // it scales the scores, the row-tiled kernel rounds the scaled query to 16 bits.  By the estimates for today's tiles,
     // which are lower, 60 of 8022 random equal shapes that are not decode-shaped and 1487 of 10817 unequal ones would go over
     // to row tiles.
-    bool beside = false; // decode-shaped requests next to others
-    int64_t blocks = 0;
-    for (int r = 0; r < s->batch; ++r) {
-        beside = beside || (compare && s->h_extend_lens[r] > 0 && decode_shaped(s->h_extend_lens[r], G));
-        blocks = std::max(blocks, ((int64_t)s->h_extend_lens[r] * G + kDecRows - 1) / kDecRows);
+    bool beside = false; // decode-shaped requests next to others, in the decode kernel's form
+    if (q.decode_rows || fits_once(q)) {
+        const Plan heads = plan_of_whole_heads(q, room, true);
+        if (heads.small) return heads;
+        beside = q.decode_rows && heads.mixed;
     }
-    if (beside || blocks * s->batch * s->num_kv_heads <= num_cus()) {
-        Plan heads = plan_of_whole_heads(s, room, max_n);
-        if (heads.small) {
-            heads.tile_shift = kTileShift;
-            return heads;
+    const int64_t items = pl.q_tiles * s->num_kv_heads;
+    const bool by_items = q.equal || q.by_request || items < 2 * num_cus();
+    const bool few = by_items && items <= num_cus() && q.work(kHalfTiles).q_tiles * s->num_kv_heads <= num_cus(); // so that half tiles fit the CUs at once
+    double us = 0.0;
+    auto one_number = [&] { // of key ranges for all requests, or small
+        if (by_items) q.equal ? choose_equal_splits(q, kFullTiles, room, pl, &us) : choose_splits(q, kFullTiles, room, pl, &us);
+        if (few) {
+            Plan half{0, 0, 1, false, 1};
+            double half_us;
+            q.equal ? choose_equal_splits(q, kHalfTiles, room, half, &half_us) : choose_splits(q, kHalfTiles, room, half, &half_us);
+            if (half_us + kHalfUs < us) {
+                pl = half;
+                us = half_us + kHalfUs;
+            }
         }
-        beside = beside && heads.mixed;
-    }
-    const bool by_items = equal || compare || pl.q_tiles * s->num_kv_heads < 2 * num_cus();
-    if (by_items) equal ? choose_equal_splits(s, room, pl, &us) : choose_splits(s, room, pl, &us);
-    Plan half{0, 0, 1, false, 1};
-    half.tile_shift = kTileShift - 1;
-    row_tiled_extent(s, half.tile_shift, half.q_tiles, half.max_key_tiles);
-    const bool few = by_items && half.q_tiles * s->num_kv_heads <= num_cus();
-    if (few) {
-        double half_us;
-        equal ? choose_equal_splits(s, room, half, &half_us) : choose_splits(s, room, half, &half_us);
-        if (half_us + kHalfUs < us) {
-            pl = half;
-            us = half_us + kHalfUs;
+        if (small_call(q, us, pl)) {
+            pl.nsplit = 1;
+            pl.tail_units = 0;
         }
+    };
+    const bool settled = beside && !fits_once(q); // request by request, whatever the estimates say
+    if (!settled) one_number();
+    if (!q.by_request) return pl;
+    Plan mixed{0, 0, 1, false, 1}, half{0, 0, 1, false, 1};
+    double mixed_us, half_us;
+    bool any = plan_mixed(q, room, kFullTiles, mixed, &mixed_us);
+    if (few && plan_mixed(q, room, kHalfTiles, half, &half_us) && (!any || half_us + kHalfUs < mixed_us)) {
+        any = true;
+        mixed = half;
+        mixed_us = half_us + kHalfUs;
     }
-    if (small_call(s, max_n, us, pl)) {
-        pl.nsplit = 1;
-        pl.tail_units = 0;
+    if (any && ((beside && !pl.small) || mixed_us + kMixedUs < us)) {
+        if (order) q.write_order(order);
+        return mixed;
     }
-    if (compare) {
-        Plan mixed{0, 0, 1, false, 1};
-        double mixed_us, half_us;
-        const bool any = plan_mixed(s, room, kTileShift, mixed, order, &mixed_us);
-        if (few && plan_mixed(s, room, kTileShift - 1, half, order, &half_us) && (!any || half_us + kHalfUs < mixed_us)) {
-            mixed = half;
-            mixed_us = half_us + kHalfUs;
-        } else if (!any) return pl;
-        if ((beside && !pl.small) || mixed_us + kMixedUs < us) return mixed;
-    }
+    if (settled) one_number();
     return pl;
 }
 
@@ -2195,19 +2263,11 @@ size_t workspace_for(const cp_shape *s, const Plan &pl)
     return part_bytes((size_t)pl.nsplit * (size_t)s->total_extend, s->num_q_heads);
 }
 // plan_of_whole_heads for any call.
-Plan plan_of_whole_heads(const cp_shape *s, size_t room = SIZE_MAX)
+Plan old_plan(Requests &q, size_t room = SIZE_MAX)
 {
-    int64_t max_e = 0, max_n = 0;
-    for (int r = 0; r < s->batch; ++r) {
-        if (s->h_extend_lens[r] == 0) continue;
-        max_e = std::max<int64_t>(max_e, s->h_extend_lens[r]);
-        max_n = std::max<int64_t>(max_n, (int64_t)s->h_prefix_lens[r] + s->h_extend_lens[r]);
-    }
-    const int G = s->num_q_heads / s->num_kv_heads;
-    if (s->num_splits >= 1 || max_e * G <= kDecRows * kDecMaxRowBlocks) return make_plan(s, room); // it has no row tiles, or no choice
-    return plan_of_whole_heads(s, room, max_n);
+    if (q.s->num_splits >= 1 || q.max_e * q.G <= kDecRows * kDecMaxRowBlocks) return make_plan(q, room); // it has no row tiles, or no choice
+    return plan_of_whole_heads(q, room, false);
 }
-size_t workspace_of_whole_heads(const cp_shape *s) { return workspace_for(s, plan_of_whole_heads(s)); }
 // What the launches touch of it: of a decode-shaped call the partial results of the workgroups that share a
 // request's keys, at most nsplit, none where one workgroup has them all.
 size_t scratch_used(const cp_shape *s, const Plan &pl)
@@ -2220,22 +2280,20 @@ size_t scratch_used(const cp_shape *s, const Plan &pl)
 // the call is not decode-shaped, brings less than its best plan wants and also less than key ranges of
 // at least 8 tiles, for two workgroups per CU, take, or than a split request by request does.  Plans
 // without partial results exist for it, but would run several times slower than the call can, without a word.
-bool too_little_scratch(const cp_shape *s, const Plan &pl, size_t room)
+bool too_little_scratch(Requests &q, const Plan &pl, size_t room)
 {
+    const cp_shape *const s = q.s;
     if (scratch_used(s, pl) > room) return true;
     if (pl.decode || s->num_splits >= 1) return false;
     // The line lies where it lay when row tiles held whole heads.
-    int64_t q_tiles = 0;
-    int32_t max_key_tiles = 0;
-    row_tiled_extent(s, kWholeHeads, q_tiles, max_key_tiles);
-    const int64_t items = q_tiles * s->num_kv_heads, want = 2LL * num_cus();
+    const int64_t items = q.work(kWholeHeads).q_tiles * s->num_kv_heads, want = 2LL * num_cus();
     int64_t ns = items > 0 && items < want ? (want + items - 1) / items : 1;
-    ns = std::min<int64_t>({ns, max_key_tiles / 8, kMaxSplits});
+    ns = std::min<int64_t>({ns, q.max_key_tiles / 8, kMaxSplits});
     if (ns <= 1 || part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) <= room) return false;
-    if (workspace_of_whole_heads(s) <= room) return false;
+    if (workspace_for(s, old_plan(q)) <= room) return false;
     Plan mixed{0, 0, 1, false, 1};
     double us;
-    return s->batch > kMixedMaxBatch || equal_lengths(s) || !plan_mixed(s, SIZE_MAX, kWholeHeads, mixed, nullptr, &us) || workspace_for(s, mixed) > room;
+    return !q.by_request || !plan_mixed(q, SIZE_MAX, kWholeHeads, mixed, &us) || workspace_for(s, mixed) > room;
 }
 
 inline bool aligned_to(const void *p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
@@ -2378,15 +2436,17 @@ const char *cp_status_string(int status)
 int32_t cp_num_splits(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return 0;
-    const Plan pl = make_plan(shape);
+    Requests q(shape);
+    const Plan pl = make_plan(q);
     // of a batch split request by request a bound, for which cp_workspace_bytes has room
-    return pl.mixed && pl.nsplit > 1 ? std::max(pl.nsplit, plan_of_whole_heads(shape).nsplit) : pl.nsplit;
+    return pl.mixed && pl.nsplit > 1 ? std::max(pl.nsplit, old_plan(q).nsplit) : pl.nsplit;
 }
 
 int32_t cp_plan_kind(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return CP_PLAN_INVALID;
-    const Plan pl = make_plan(shape);
+    Requests q(shape);
+    const Plan pl = make_plan(q);
     if (pl.decode || pl.small) return CP_PLAN_DECODE;
     return pl.nsplit > 1 ? CP_PLAN_ROW_TILED_SPLIT : CP_PLAN_ROW_TILED;
 }
@@ -2394,22 +2454,23 @@ int32_t cp_plan_kind(const cp_shape *shape)
 size_t cp_workspace_bytes(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return 0;
-    return std::max(workspace_for(shape, make_plan(shape)), workspace_of_whole_heads(shape));
+    Requests q(shape);
+    return std::max(workspace_for(shape, make_plan(q)), workspace_for(shape, old_plan(q)));
 }
 
 } // extern "C"
 
 namespace {
 // Everything behind cp_extend_attention: argument checks, plan, launches.  `workspace` is
-// whatever scratch the entry point brings: the caller's buffer or the library's own array.  `planned`: the
-// plan for it where the entry point has made and checked one, with its order in p.
+// whatever scratch the entry point brings: the caller's buffer or the library's own array.  `lengths` are those of
+// the shape, which the entry point has validated.  `planned`: the plan for the scratch where the entry point has made and
+// checked one, with its order in p.
 int run_attention(const void *q, const void *k_new, const void *v_new, const void *kv_pages,
                   const int32_t *block_table, const int32_t *prefix_lens, const int32_t *extend_lens, void *out,
-                  void *stream, const cp_shape *shape, void *workspace, size_t workspace_bytes, MixedParams &p,
+                  void *stream, Requests &lengths, void *workspace, size_t workspace_bytes, MixedParams &p,
                   const Plan *planned)
 {
-    const int st = validate(shape);
-    if (st != CP_OK) return st;
+    const cp_shape *const shape = lengths.s;
     if (!block_table || !prefix_lens || !extend_lens) return CP_ERR_NULL;
     if (shape->total_extend == 0) return CP_OK;
     if (!q || !k_new || !v_new || !kv_pages || !out) return CP_ERR_NULL;
@@ -2423,14 +2484,14 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
         if (chk != CP_OK) return chk;
     }
     const size_t room = workspace ? workspace_bytes : 0;
-    Plan pl = planned ? *planned : make_plan(shape, room, p.order);
-    if (!planned && too_little_scratch(shape, pl, room)) return CP_ERR_WORKSPACE;
+    Plan pl = planned ? *planned : make_plan(lengths, room, p.order);
+    if (!planned && too_little_scratch(lengths, pl, room)) return CP_ERR_WORKSPACE;
     if (workspace && !aligned_to(workspace, 256)) {
         // The caller's mistake where row tiles of whole heads asked for scratch, which is where this has been one.  Calls that
         // ask for some only with today's tiles run with such a buffer as without one.
-        const Plan heads = plan_of_whole_heads(shape, room);
+        const Plan heads = old_plan(lengths, room);
         if (scratch_used(shape, heads) > 0) return CP_ERR_WORKSPACE;
-        if (scratch_used(shape, pl) > 0) pl = make_plan(shape, 0, p.order);
+        if (scratch_used(shape, pl) > 0) pl = make_plan(lengths, 0, p.order);
     }
     const size_t need = scratch_used(shape, pl);
     const int64_t per_head = pl.mixed ? pl.row_items + (pl.dec_units + kWaves - 1) / kWaves :
@@ -2466,14 +2527,12 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
     p.xcds_per_head = p.Hkv < kXcds && kXcds % p.Hkv == 0 ? kXcds / p.Hkv : 1;
     const bool ranges = p.xcds_per_head > 1 && contiguous_ranges(shape, pl, per_head, p.xcds_per_head);
     if (ranges) p.xcds_per_head = 1;
-    p.alternate = !ranges && per_head * p.Hkv <= kAlternateRounds * (int64_t)num_cus() && equal_lengths(shape);
+    p.alternate = !ranges && per_head * p.Hkv <= kAlternateRounds * (int64_t)num_cus() && lengths.equal;
     p.items_per_xcd = (int32_t)(p.xcds_per_head > 1 ? (per_head + p.xcds_per_head - 1) / p.xcds_per_head
                                                     : (total + kXcds - 1) / kXcds);
     p.scale_log2 = shape->softmax_scale * 1.4426950408889634f;
 
-    int64_t most = 0;
-    for (int r = 0; r < shape->batch; ++r) most = std::max<int64_t>(most, shape->h_extend_lens[r]);
-    p.g_magic = (most * p.G + kBM + 1) * p.G <= INT64_C(0x100000000) ? 0xffffffffu / (uint32_t)p.G : 0u;
+    p.g_magic = (lengths.max_e * p.G + kBM + 1) * p.G <= INT64_C(0x100000000) ? 0xffffffffu / (uint32_t)p.G : 0u;
 
     p.seg_tiles = pl.seg_tiles;
     p.dec_blocks = pl.dec_blocks;
@@ -2533,8 +2592,11 @@ int cp_extend_attention(const void *q, const void *k_new, const void *v_new, con
                         const int32_t *extend_lens, void *out, void *stream, const cp_shape *shape,
                         void *workspace, size_t workspace_bytes)
 {
+    const int st = validate(shape);
+    if (st != CP_OK) return st;
     MixedParams p;
-    return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, shape,
+    Requests lengths(shape);
+    return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, lengths,
                          workspace, workspace_bytes, p, nullptr);
 }
 
@@ -2548,11 +2610,12 @@ int cp_extend_attention_noalloc(const void *q, const void *k_new, const void *v_
     if (st != CP_OK) return st;
     // sizes beyond the library's own array are refused here, before anything is looked up or launched
     MixedParams p;
-    const Plan pl = make_plan(shape, CP_NOALLOC_SCRATCH_BYTES, p.order);
-    if (too_little_scratch(shape, pl, CP_NOALLOC_SCRATCH_BYTES)) return CP_ERR_WORKSPACE;
+    Requests lengths(shape);
+    const Plan pl = make_plan(lengths, CP_NOALLOC_SCRATCH_BYTES, p.order);
+    if (too_little_scratch(lengths, pl, CP_NOALLOC_SCRATCH_BYTES)) return CP_ERR_WORKSPACE;
     void *ptr = scratch_address(); // the array's address on the current device, never the array's name
     if (!ptr) return CP_ERR_LAUNCH;
-    return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, shape, ptr,
+    return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, lengths, ptr,
                          CP_NOALLOC_SCRATCH_BYTES, p, &pl);
 }
 
