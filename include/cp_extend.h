@@ -79,8 +79,8 @@ typedef struct cp_shape {
 
 /*
  * Bytes of device scratch with which cp_extend_attention takes its best plan for this shape (0 when
- * the keys are not split; an upper bound for a decode-shaped call, room for a partial result per
- * cp_num_splits, and for others where the best plan takes less than one with row tiles of whole heads); see `workspace` below for calls with less.  A pure function of *shape, including the
+ * the keys are not split; for a decode-shaped call an upper bound, room for a partial result per
+ * cp_num_splits); see `workspace` below for calls with less.  A pure function of *shape, including the
  * host length arrays.  Returns 0 for an invalid shape (cp_extend_attention then reports the error).
  */
 size_t cp_workspace_bytes(const cp_shape *shape);
@@ -88,7 +88,7 @@ size_t cp_workspace_bytes(const cp_shape *shape);
 /* The number of key ranges whose partial results cp_extend_attention will merge for this shape
  * (1 = no split; up to 64 when forced, up to 256 when chosen by the library; 0 if invalid).  For a
  * batch of unequal lengths, whose requests are split one by one, and where only the last items of a
- * batch are: the largest, or for the former a bound on it.  For a decode-shaped
+ * batch are: the largest.  For a decode-shaped
  * call: an upper bound; a row has as many partial results as workgroups share its request's keys, and
  * none to merge where one workgroup has them all. */
 int32_t cp_num_splits(const cp_shape *shape);
@@ -132,7 +132,8 @@ int32_t cp_plan_kind(const cp_shape *shape);
  * of 64 keys for two workgroups per compute unit (in a batch of unequal lengths, if that is less, of every
  * request split by its own length); a decode-shaped call runs the same with what its
  * workgroups leave behind, nothing where one has all keys of a request; below that, and any other call,
- * is refused, and so is a buffer that the plan for its size uses and that is not aligned.  Its contents are undefined afterwards.
+ * is refused, and so is a buffer that is not aligned, for a decode-shaped call or a forced split where it is used, otherwise where
+ * the call's plan with row tiles of whole heads would use it (elsewhere the call runs as without one).  Its contents are undefined afterwards.
  * Requests with E_r = 0 produce no rows.  Asynchronous on `stream`.
  */
 int cp_extend_attention(const void *q, const void *k_new, const void *v_new,

@@ -1568,11 +1568,11 @@ __device__ __align__(256) unsigned long long g_check_report[32];
 
 // ------------------------------------------------------------------ host side
 struct Plan {
-    int64_t q_tiles;   // row tiles per KV head, summed over requests
-    int32_t max_key_tiles;
-    int32_t nsplit;
-    bool decode;       // few rows per (request, KV head): decode_attn_kernel
-    int32_t row_blocks; // ... in this many blocks of 32 rows
+    int64_t q_tiles = 0; // row tiles per KV head, summed over requests
+    int32_t max_key_tiles = 0;
+    int32_t nsplit = 1;
+    bool decode = false;    // few rows per (request, KV head): decode_attn_kernel
+    int32_t row_blocks = 1; // ... in this many blocks of 32 rows
     int32_t dec_groups = 1; // ... by this many workgroups that share a request's keys
     int32_t dec_share = 1;  // ... with this many blocks of rows per wavefront
     bool small = false; // few rows and keys: decode_attn_kernel with a workgroup per block of 32 rows
@@ -1881,7 +1881,7 @@ bool plan_mixed(Requests &q, size_t room, TileKind kind, Plan &best, double *est
         // give the merge more to read (21 requests, 218 MB of decode K/V: 16 blocks 49 us, 8: 52, 4: 57).
         const int least = (int)std::min<int64_t>(16, std::max<int64_t>(4, 2 * q.decode_work / (8 * num_cus())));
         const int dec = std::max(std::max(least, (int)(seg * (kTileUs / kBlockUs))), (q.key_blocks + kMaxSplits - 1) / kMaxSplits);
-        Plan pl{0, 0, 1, false, 1};
+        Plan pl;
         const double us = mixed_cost(q, kind, seg, dec, kind == kWholeHeads ? kUnequalOfWholeHeads : kUnequal,
                                      all_fit && best_us >= 0.0 ? best_us : HUGE_VAL, pl);
         if (pl.part_rows > INT32_MAX / 2 || (pl.part_rows > 0 && part_bytes((size_t)pl.part_rows, s->num_q_heads) > room)) continue;
@@ -2111,7 +2111,7 @@ constexpr double kMixedUs = 2.0;
 // kind_only: whether it is small, or request by request, is all that is asked.
 Plan plan_of_whole_heads(Requests &q, size_t room, bool kind_only)
 {
-    Plan pl{0, 0, 1, false, 1}, mixed{0, 0, 1, false, 1};
+    Plan pl, mixed;
     double us, mixed_us;
     choose_splits(q, kWholeHeads, room, pl, &us);
     if (small_call(q, us, pl)) pl.nsplit = 1;
@@ -2125,7 +2125,7 @@ Plan plan_of_whole_heads(Requests &q, size_t room, bool kind_only)
 Plan make_plan(Requests &q, size_t room = SIZE_MAX, uint8_t *order = nullptr)
 {
     const cp_shape *const s = q.s;
-    Plan pl{0, 0, 1, false, 1};
+    Plan pl;
     if (s->num_splits == 0 && q.max_e > 0 && q.max_e * q.G <= kDecRows * kDecMaxRowBlocks) {
         // Decode-shaped.  nsplit bounds the workgroups that may share a request's keys, and is what the
         // queries report: key chunks for 8 wavefronts per CU, at least 2 blocks of 32 keys each, a
@@ -2169,7 +2169,7 @@ Plan make_plan(Requests &q, size_t room = SIZE_MAX, uint8_t *order = nullptr)
     auto one_number = [&] { // of key ranges for all requests, or small
         if (by_items) q.equal ? choose_equal_splits(q, kFullTiles, room, pl, &us) : choose_splits(q, kFullTiles, room, pl, &us);
         if (few) {
-            Plan half{0, 0, 1, false, 1};
+            Plan half;
             double half_us;
             q.equal ? choose_equal_splits(q, kHalfTiles, room, half, &half_us) : choose_splits(q, kHalfTiles, room, half, &half_us);
             if (half_us + kHalfUs < us) {
@@ -2185,7 +2185,7 @@ Plan make_plan(Requests &q, size_t room = SIZE_MAX, uint8_t *order = nullptr)
     const bool settled = beside && !fits_once(q); // request by request, whatever the estimates say
     if (!settled) one_number();
     if (!q.by_request) return pl;
-    Plan mixed{0, 0, 1, false, 1}, half{0, 0, 1, false, 1};
+    Plan mixed, half;
     double mixed_us, half_us;
     bool any = plan_mixed(q, room, kFullTiles, mixed, &mixed_us);
     if (few && plan_mixed(q, room, kHalfTiles, half, &half_us) && (!any || half_us + kHalfUs < mixed_us)) {
@@ -2291,9 +2291,19 @@ bool too_little_scratch(Requests &q, const Plan &pl, size_t room)
     ns = std::min<int64_t>({ns, q.max_key_tiles / 8, kMaxSplits});
     if (ns <= 1 || part_bytes((size_t)ns * (size_t)s->total_extend, s->num_q_heads) <= room) return false;
     if (workspace_for(s, old_plan(q)) <= room) return false;
-    Plan mixed{0, 0, 1, false, 1};
+    Plan mixed;
     double us;
     return !q.by_request || !plan_mixed(q, SIZE_MAX, kWholeHeads, mixed, &us) || workspace_for(s, mixed) > room;
+}
+
+// The plan of a call with `room` bytes of scratch: the best one if that is enough for it, otherwise the best that fits;
+// false if the call is refused.
+bool plan_for(Requests &q, size_t room, Plan &pl, uint8_t *order)
+{
+    pl = make_plan(q, SIZE_MAX, order);
+    if (scratch_used(q.s, pl) <= room) return true;
+    pl = make_plan(q, room, order);
+    return !too_little_scratch(q, pl, room);
 }
 
 inline bool aligned_to(const void *p, uintptr_t a) { return reinterpret_cast<uintptr_t>(p) % a == 0; }
@@ -2437,9 +2447,7 @@ int32_t cp_num_splits(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return 0;
     Requests q(shape);
-    const Plan pl = make_plan(q);
-    // of a batch split request by request a bound, for which cp_workspace_bytes has room
-    return pl.mixed && pl.nsplit > 1 ? std::max(pl.nsplit, old_plan(q).nsplit) : pl.nsplit;
+    return make_plan(q).nsplit;
 }
 
 int32_t cp_plan_kind(const cp_shape *shape)
@@ -2455,7 +2463,7 @@ size_t cp_workspace_bytes(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return 0;
     Requests q(shape);
-    return std::max(workspace_for(shape, make_plan(q)), workspace_for(shape, old_plan(q)));
+    return workspace_for(shape, make_plan(q));
 }
 
 } // extern "C"
@@ -2484,8 +2492,9 @@ int run_attention(const void *q, const void *k_new, const void *v_new, const voi
         if (chk != CP_OK) return chk;
     }
     const size_t room = workspace ? workspace_bytes : 0;
-    Plan pl = planned ? *planned : make_plan(lengths, room, p.order);
-    if (!planned && too_little_scratch(lengths, pl, room)) return CP_ERR_WORKSPACE;
+    Plan pl;
+    if (planned) pl = *planned;
+    else if (!plan_for(lengths, room, pl, p.order)) return CP_ERR_WORKSPACE;
     if (workspace && !aligned_to(workspace, 256)) {
         // The caller's mistake where row tiles of whole heads asked for scratch, which is where this has been one.  Calls that
         // ask for some only with today's tiles run with such a buffer as without one.
@@ -2611,8 +2620,8 @@ int cp_extend_attention_noalloc(const void *q, const void *k_new, const void *v_
     // sizes beyond the library's own array are refused here, before anything is looked up or launched
     MixedParams p;
     Requests lengths(shape);
-    const Plan pl = make_plan(lengths, CP_NOALLOC_SCRATCH_BYTES, p.order);
-    if (too_little_scratch(lengths, pl, CP_NOALLOC_SCRATCH_BYTES)) return CP_ERR_WORKSPACE;
+    Plan pl;
+    if (!plan_for(lengths, CP_NOALLOC_SCRATCH_BYTES, pl, p.order)) return CP_ERR_WORKSPACE;
     void *ptr = scratch_address(); // the array's address on the current device, never the array's name
     if (!ptr) return CP_ERR_LAUNCH;
     return run_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out, stream, lengths, ptr,

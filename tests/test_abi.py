@@ -125,6 +125,31 @@ def test_rows_of_the_decode_form_stay_in_it(lib, P, E, Hq, Hkv, kind, splits):
     assert (cp.cp_plan_kind(sh), cp.cp_num_splits(sh)) == (kind, splits)
 
 
+def test_scratch_and_ranges_are_those_of_the_plan_that_runs(lib):
+    """Row-tiled calls ask for scratch where their keys are split and only there, and for no more than a partial result
+    of every row and range; also where row tiles of whole heads, which nothing runs, would want some."""
+    import random
+
+    rng = random.Random(9)
+    shapes = [([0, 130, 500], [900, 257, 1], 8, 2), ([300] * 2, [700] * 2, 32, 4)]
+    while len(shapes) < 400:
+        n = rng.randint(1, 40)
+        P, E = [rng.randint(0, 9000) for _ in range(n)], [rng.choice((1, rng.randint(17, 3000))) for _ in range(n)]
+        Hq, Hkv = rng.choice(((8, 2), (32, 8), (64, 8), (12, 1)))
+        shapes.append((P[:1] * n, E[-1:] * n, Hq, Hkv) if rng.random() < 0.3 else (P, E, Hq, Hkv))
+    kinds = set()
+    for P, E, Hq, Hkv in shapes:
+        sh = _shape(P, E, Hq=Hq, Hkv=Hkv)
+        kind, splits, size = cp.cp_plan_kind(sh), cp.cp_num_splits(sh), cp.cp_workspace_bytes(sh)
+        kinds.add(kind)
+        if splits == 1:
+            assert size == 0, (P, E, Hq, Hkv)
+        else:
+            rows = sum(-(-e * (Hq // Hkv) // 256) * 256 * Hkv for e in E)      # row tiles, with what fills the last
+            assert 0 < size <= splits * rows * 130 * 4 + 512, (P, E, Hq, Hkv)
+    assert kinds == {1, 2, 3}
+
+
 def test_decode_shaped_requests_do_not_multiply_the_cost_of_planning(lib):
     """512 requests of unequal lengths, once with a chunk of a prompt each and once with one new token for four of
     five: the second kind is compared with a plan more, for which nothing is read or sorted again.  Least times of
