@@ -2007,21 +2007,21 @@ void choose_equal_splits(const Requests &q, TileKind kind, size_t room, Plan &pl
     if (Hkv > kXcds || kXcds % Hkv != 0 || units <= per_round || units % per_round == 0 || units > INT32_MAX / kMaxTailSplits) return;
     if (Hkv < kXcds && contiguous_ranges(s, pl, units * pl.nsplit, kXcds / Hkv)) return;
     best_us = std::min(kTailGain * *estimate, best_us);
-    for (int64_t tail = units % per_round; tail < std::min(units, 2 * per_round); tail += per_round) {
-        // they are the shortest of the last request, as far as that has as many
-        const double tail_longest = tail < nt ? prefix + own_tiles(tail - 1) : longest;
-        const double whole = (n - (double)tail) * kItemUs + tile_us * (tiles - (double)tail * 0.5 * (shortest + tail_longest));
-        for (int32_t ns = 2; ns <= kMaxTailSplits && 2 * ns <= (int32_t)shortest; ++ns) {
-            const size_t bytes = part_bytes((size_t)(tail * ns) * kBM, Hkv);
-            if (bytes > room) break;
-            const double us = whole / cus + std::ceil((double)(tail * ns) / cus) * (kItemUs + tile_us * std::ceil(tail_longest / ns)) +
-                              kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
-            if (us >= best_us) continue;
-            best_us = us;
-            *estimate = us;
-            pl.nsplit = ns;
-            pl.tail_units = (int32_t)tail;
-        }
+    // They are the shortest of the last request, as far as that has as many.  With a whole round more split the estimate was never
+    // lower (60000 random shapes of equal requests, 1008 with a last round split).
+    const int64_t tail = units % per_round;
+    const double tail_longest = tail < nt ? prefix + own_tiles(tail - 1) : longest;
+    const double whole = (n - (double)tail) * kItemUs + tile_us * (tiles - (double)tail * 0.5 * (shortest + tail_longest));
+    for (int32_t ns = 2; ns <= kMaxTailSplits && 2 * ns <= (int32_t)shortest; ++ns) {
+        const size_t bytes = part_bytes((size_t)(tail * ns) * kBM, Hkv);
+        if (bytes > room) break;
+        const double us = whole / cus + std::ceil((double)(tail * ns) / cus) * (kItemUs + tile_us * std::ceil(tail_longest / ns)) +
+                          kMergeUs + 2.0 * (double)bytes / kPartBytesPerUs;
+        if (us >= best_us) continue;
+        best_us = us;
+        *estimate = us;
+        pl.nsplit = ns;
+        pl.tail_units = (int32_t)tail;
     }
 }
 
