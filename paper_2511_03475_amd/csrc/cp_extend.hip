@@ -643,6 +643,11 @@ constexpr int kTileBytesK = kBN * kPitchK;
 constexpr int kTileBytesV = kBN * kPitchV;
 constexpr int kNumBufsV = 5;
 constexpr int kLdsBytes = kNumBufs * kTileBytesK + kNumBufsV * kTileBytesV;
+// The operand reads find the 16-byte chunks of a row by exclusive or in bits 4 to 7 of an address: rows and buffers begin
+// at multiples of this, and so does the array that holds them.
+constexpr int kLdsAlign = 256;
+static_assert(kPitchK % kLdsAlign == 0 && kPitchV % kLdsAlign == 0 && kTileBytesK % kLdsAlign == 0 && kTileBytesV % kLdsAlign == 0,
+              "exclusive or in place of an addition");
 
 constexpr int kMixedLdsBytes = kWaves * kDecLdsPerWave > kLdsBytes ? kWaves * kDecLdsPerWave : kLdsBytes;
 
@@ -658,7 +663,7 @@ enum Mode { kWhole, kSplit, kMixed };
 template <Mode kMode>
 __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::conditional_t<kMode == kMixed, MixedParams, AttnParams> p)
 {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
+    extern __shared__ __attribute__((aligned(kLdsAlign))) char lds[];
     char *const lds_k = lds;                          // [4][64 rows][256 B]
     char *const lds_v = lds + kNumBufs * kTileBytesK; // [5][64 rows][256 B]
 
@@ -911,7 +916,7 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
     // offset for db = 0 with bits 6 and 7 exchanged.
     const int v_lane = (4 * h + ((lane & 15) >> 2)) * kPitchV + (((lane >> 2) & 3) << 6) + ((lane >> 4) & 1) * 32 + (lane & 3) * 8;
     typedef __attribute__((address_space(3))) const char *lptr;
-    const uint32_t lds_k0 = (uint32_t)(uintptr_t)(lptr)lds_k, lds_v0 = (uint32_t)(uintptr_t)(lptr)lds_v; // multiples of 256
+    const uint32_t lds_k0 = (uint32_t)(uintptr_t)(lptr)lds_k, lds_v0 = (uint32_t)(uintptr_t)(lptr)lds_v; // multiples of kLdsAlign
 
     f32x16 o[4];
 #pragma unroll
