@@ -109,6 +109,10 @@ enum {
 };
 int32_t cp_plan_kind(const cp_shape *shape);
 
+/* Rows of the row tiles that cp_extend_attention launches for this shape: 256, or 128 where those would leave
+ * compute units without work; 0 if it launches none or the shape is invalid.  A pure function of *shape. */
+int32_t cp_plan_tile_rows(const cp_shape *shape);
+
 /*
  * Extend attention (paper, Section 1: prefill over a prefix cache).  For request r, q head h,
  * g = h / G and extend row i in [0, E_r):

@@ -25,7 +25,7 @@ CP_ERR_ALIGN = -5
 CP_ERR_TABLE = -6
 CP_ERR_LENGTHS = -7
 
-EXPORTS = ("cp_workspace_bytes", "cp_num_splits", "cp_plan_kind", "cp_extend_attention", "cp_write_kv",
+EXPORTS = ("cp_workspace_bytes", "cp_num_splits", "cp_plan_kind", "cp_plan_tile_rows", "cp_extend_attention", "cp_write_kv",
            "cp_extend_attention_noalloc", "cp_noalloc_scratch_bytes",
            "cp_status_string", "cp_check_tables", "cp_set_debug_validate", "cp_context_distance", "cp_probe_mfma", "cp_probe_mix", "cp_probe_copy", "cp_probe_fill_lds",
            "cp_probe_mfma_sink_floats", "cp_probe_mfma_flops",
@@ -82,6 +82,8 @@ def load_library(path: Optional[str] = None) -> ctypes.CDLL:
     lib.cp_num_splits.argtypes = [sp]
     lib.cp_plan_kind.restype = ctypes.c_int32
     lib.cp_plan_kind.argtypes = [sp]
+    lib.cp_plan_tile_rows.restype = ctypes.c_int32
+    lib.cp_plan_tile_rows.argtypes = [sp]
     lib.cp_extend_attention.restype = ctypes.c_int
     lib.cp_extend_attention.argtypes = [vp, vp, vp, vp, i32p, i32p, i32p, vp, vp, sp, vp, ctypes.c_size_t]
     lib.cp_extend_attention_noalloc.restype = ctypes.c_int
@@ -208,6 +210,10 @@ PLAN_KERNELS = {1: "extend_attn_kernel", 2: "extend_attn_kernel + a merge kernel
 
 def cp_plan_kind(shape: Shape) -> int:
     return int(load_library().cp_plan_kind(shape.ref()))
+
+
+def cp_plan_tile_rows(shape: Shape) -> int:
+    return int(load_library().cp_plan_tile_rows(shape.ref()))
 
 
 def cp_extend_attention(q, k_new, v_new, kv_pages, block_table, prefix_lens, extend_lens, out,

@@ -2464,6 +2464,14 @@ int32_t cp_plan_kind(const cp_shape *shape)
     return pl.nsplit > 1 ? CP_PLAN_ROW_TILED_SPLIT : CP_PLAN_ROW_TILED;
 }
 
+int32_t cp_plan_tile_rows(const cp_shape *shape)
+{
+    if (validate(shape) != CP_OK || shape->total_extend == 0) return 0;
+    Requests q(shape);
+    const Plan pl = make_plan(q);
+    return pl.decode || pl.small ? 0 : 1 << pl.tile_shift;
+}
+
 size_t cp_workspace_bytes(const cp_shape *shape)
 {
     if (validate(shape) != CP_OK) return 0;

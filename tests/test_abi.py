@@ -125,6 +125,16 @@ def test_rows_of_the_decode_form_stay_in_it(lib, P, E, Hq, Hkv, kind, splits):
     assert (cp.cp_plan_kind(sh), cp.cp_num_splits(sh)) == (kind, splits)
 
 
+@pytest.mark.parametrize("P,E,Hq,Hkv,splits,rows", [
+    ([24576] * 4, [8192] * 4, 64, 8, 0, 256), ([0] * 3, [959] * 3, 8, 2, 0, 128), ([0] * 3, [959] * 3, 8, 2, 1, 256),
+    ([0, 1213, 36, 98, 7, 119], [1, 74, 87, 25, 406, 103], 16, 4, 0, 128),          # split request by request
+    ([836, 0, 0, 0, 27, 0], [3, 75, 551, 195, 265, 216], 8, 4, 0, 256),
+    ([512], [128], 8, 2, 0, 0), ([10240] * 32, [1] * 32, 32, 8, 0, 0), ([16, 0], [0, 0], 4, 2, 0, 0),   # no row tiles
+])
+def test_rows_of_the_row_tiles(lib, P, E, Hq, Hkv, splits, rows):
+    assert cp.cp_plan_tile_rows(_shape(P, E, Hq=Hq, Hkv=Hkv, splits=splits)) == rows
+
+
 def test_scratch_and_ranges_are_those_of_the_plan_that_runs(lib):
     """Row-tiled calls ask for scratch where their keys are split and only there, and for no more than a partial result
     of every row and range; also where row tiles of whole heads, which nothing runs, would want some."""

@@ -90,24 +90,30 @@ def test_less_scratch_than_asked_for(H, P, E, Hq, Hkv, part, ok):
         assert (got == 0x1234).all()
 
 
-@pytest.mark.parametrize("B,P,E,G,Hkv", [
-    (33, 1500, 70, 1, 8),      # one item more than the CUs of an XCD, three wavefronts of rows
-    (17, 1000, 150, 2, 8),     # two tiles a request, the last one of 44 rows; requests in turn longest and shortest first
-    (11, 1500, 250, 3, 8),     # G divides neither tile nor wavefront; the shortest tile of the last request
+@pytest.mark.parametrize("B,P,E,G,Hkv,ranges,tail", [
+    (33, 1500, 70, 1, 8, 6, 1),       # one item more than the CUs of an XCD, three wavefronts of rows
+    (17, 1000, 150, 2, 8, 5, 2),      # two tiles a request, the last one of 44 rows; requests in turn longest and shortest first
+    (11, 1500, 250, 3, 8, 9, 1),      # G divides neither tile nor wavefront; the shortest tile of the last request
+    (17, 489, 136, 2, 8, 4, 2),       # the merge of up to 4 ranges
+    (19, 1539, 36, 8, 8, 4, 6),
+    (3, 0, 5382, 1, 4, 2, 2),         # several XCDs to a KV head, their items dealt out: 2, 4 and 8
+    (1, 1533, 1040, 16, 4, 9, 1),
+    (3, 213, 5427, 2, 2, 3, 1),
+    (2, 1958, 1119, 16, 2, 7, 12),
+    (1, 143, 5707, 12, 1, 2, 12),
 ])
-def test_the_last_round_alone_is_split(H, B, P, E, G, Hkv):
-    """Equal requests whose items do not fill the last round: only its row tiles are split and merged.  Against
-    the oracle, and every row against the unsplit call, also in a buffer of exactly the size asked for."""
+def test_the_last_round_alone_is_split(H, B, P, E, G, Hkv, ranges, tail):
+    """Equal requests whose items do not fill the last round: only its row tiles are split and merged, `tail` of each
+    KV head in `ranges` key ranges.  Against the oracle, and every row against the unsplit call, also in a buffer of
+    exactly the size asked for."""
     import torch
 
     import paper_2511_03475_amd as cp
 
     w = W.make_uniform("tail", 71, B, G * Hkv, Hkv, [P] * B, [E] * B)
     case = H.DeviceCase(w)
-    tiles = -(-E * G // 256) * B
-    uniform = cp.cp_num_splits(case.shape) * B * E * G * Hkv * 130 * 4
-    assert tiles > 256 // Hkv and 0 < case.ws_bytes < uniform / 2     # a part of the rows has partial results
     size = case.ws_bytes
+    assert (cp.cp_num_splits(case.shape), size) == (ranges, tail * ranges * 256 * Hkv * 130 * 4)   # of its row tiles only
     case.workspace = torch.full((size + 4096,), 0x5A, dtype=torch.uint8, device="cuda:0")
     case.attention()
     got = case.out_bits()
@@ -116,13 +122,23 @@ def test_the_last_round_alone_is_split(H, B, P, E, G, Hkv):
     _check(H.gpu_attention(w, num_splits=1), W.bf16_bits_to_f32(got).astype(np.float64), "unsplit")
 
 
-@pytest.mark.parametrize("P,E,G,Hkv", [
-    ([0] * 3, [959] * 3, 4, 2), ([0], [129], 1, 1), ([70], [383], 3, 8), ([300] * 2, [700] * 2, 8, 4),   # equal
-    ([0, 130, 500], [900, 257, 1], 4, 2), ([200, 0], [129, 1000], 2, 4),                                 # unequal
+@pytest.mark.parametrize("P,E,G,Hkv,ranges,by_request", [
+    ([0] * 3, [959] * 3, 4, 2, 1, False), ([70], [383], 3, 8, 1, False),       # equal requests
+    ([2], [66], 16, 8, 1, False), ([0] * 3, [215] * 3, 3, 8, 1, False),        # ... 32 rows in the last tile, 5 in it
+    ([1345] * 2, [58] * 2, 4, 1, 8, False), ([0], [1287], 1, 8, 3, False),     # ... in key ranges
+    ([0, 130, 500], [900, 257, 1], 4, 2, 1, False), ([200, 0], [129, 1000], 2, 4, 1, False),       # unequal
+    ([843, 285, 54, 0, 0], [66, 3, 229, 1, 436], 4, 1, 4, False),              # ... in one number of key ranges
+    ([0, 1213, 36, 98, 7, 119], [1, 74, 87, 25, 406, 103], 4, 4, 6, True),     # ... split request by request
 ])
-def test_row_tiles_of_half_the_rows(H, P, E, G, Hkv):
+def test_row_tiles_of_half_the_rows(H, P, E, G, Hkv, ranges, by_request):
     """Calls whose row tiles do not fill the device, tiles of 128 rows: remainders, one row too many, splits."""
+    import paper_2511_03475_amd as cp
+
     w = W.make_uniform("half", 72, len(P), G * Hkv, Hkv, P, E)
+    case = H.DeviceCase(w)
+    assert (cp.cp_plan_tile_rows(case.shape), cp.cp_num_splits(case.shape)) == (128, ranges)
+    if ranges > 1:
+        assert by_request == (case.ws_bytes < ranges * sum(E) * G * Hkv * 130 * 4)   # not every request in as many
     want = oracle.attention_of(w)
     _check(H.gpu_attention(w), want, f"half P={P} E={E} G={G} Hkv={Hkv}")
     _check(H.gpu_attention(w, num_splits=2), want, f"full P={P} E={E} G={G} Hkv={Hkv}")
@@ -299,11 +315,16 @@ def test_more_scratch_than_asked_for_changes_nothing(H, Hq, Hkv, P, E):
 @pytest.mark.parametrize("P,E,Hq,Hkv", [
     ([86, 2657, 810, 125, 3000], [1, 1, 167, 114, 1], 32, 8),      # row tiles of 14, 15 and 16 key tiles, 2 ranges
     ([5000, 0, 640, 12], [200, 1, 448, 1], 8, 2),                  # several ranges, more row tiles
-    ([30, 900], [1, 700], 6, 3),
+    ([836, 0, 0, 0, 27, 0], [3, 75, 551, 195, 265, 216], 8, 4),    # tiles of 256 rows
 ])
 def test_row_tiles_with_fewer_keys_than_their_requests_last(H, P, E, Hq, Hkv):
     """The ranges of a request split on its own: none longer than those of its last row tile, some of them empty."""
+    import paper_2511_03475_amd as cp
+
     w = W.make_uniform("ranges", 71, len(P), Hq, Hkv, P, E)
+    case = H.DeviceCase(w)
+    ranges = cp.cp_num_splits(case.shape)
+    assert ranges > 1 and 0 < case.ws_bytes < ranges * sum(E) * Hq * 130 * 4       # not every request in as many
     _check(H.gpu_attention(w), oracle.attention_of(w), f"P={P} E={E}")
 
 
