@@ -482,7 +482,9 @@ class Conversation:
         """Per block ("block", id) or ("subs", [(begin, end, ref), ...]), and the kept bytes."""
         n = len(ids)
         data = b"".join(blocks)
-        offsets = (ctypes.c_int64 * (n + 1))(0, *itertools.accumulate(map(len, blocks)))
+        starts = [0, *itertools.accumulate(map(len, blocks))]
+        offsets = (ctypes.c_int64 * (n + 1))(*starts[:-1])
+        offsets[n] = starts[-1]   # with one block too many, the last id has the text of two
         idv = (ctypes.c_int32 * max(n, 1))(*[int(i) for i in ids])
         ref = (ctypes.c_int32 * max(n, 1))()
         # a sub-block has a byte at least; pages that are not written cost nothing, counting lines does

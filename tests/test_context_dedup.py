@@ -121,6 +121,25 @@ def test_lines_hashed_side_by_side(count, M):
     lib.close()
 
 
+@pytest.mark.parametrize("ids,blocks,want", [
+    ([1, 2], [b"x\ny\n"], ([("subs", []), ("subs", [(0, 2, -1), (2, 4, -1)])], 4)),
+    ([1, 2, 3], [b"x\n"], ([("subs", []), ("subs", []), ("subs", [(0, 2, -1)])], 2)),
+    ([1], [b"x\n", b"y\nz\n"], ([("subs", [(0, 2, -1), (2, 4, -1), (4, 6, -1)])], 6)),
+    ([], [b"x"], ([], 0)), ([], [], ([], 0)),
+    ([1, 2, 3], [b"x\n", b"y\nz\n"], cp.CpError), ([1], [b"a", b"b", b"c"], IndexError),
+])
+def test_other_numbers_of_blocks_than_of_ids(ids, blocks, want):
+    """What a turn makes of them is part of its results: text without an id goes to the last one, two missing blocks
+    are an error."""
+    talk = cp.Conversation(1)
+    if isinstance(want, tuple):
+        assert talk.turn(ids, blocks) == want
+    else:
+        with pytest.raises(want):
+            talk.turn(ids, blocks)
+    talk.close()
+
+
 @pytest.mark.parametrize("seed,M", [(1, 4), (2, 1), (3, 16), (4, 7)])
 def test_conversation_matches_oracle_turn_by_turn(seed, M):
     blocks, turns = W.make_conversation(seed)
