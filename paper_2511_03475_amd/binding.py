@@ -469,6 +469,7 @@ class Conversation:
     def __init__(self, modulus: int):
         self._lib = load_library()
         self._h = ctypes.c_void_p()
+        self._modulus = int(modulus)
         _check_index(self._lib.cp_dedup_create(int(modulus), ctypes.byref(self._h)), "cp_dedup_create")
 
     def close(self) -> None:
@@ -487,12 +488,18 @@ class Conversation:
         offsets[n] = starts[-1]   # with one block too many, the last id has the text of two
         idv = (ctypes.c_int32 * max(n, 1))(*[int(i) for i in ids])
         ref = (ctypes.c_int32 * max(n, 1))()
-        # a sub-block has a byte at least; pages that are not written cost nothing, counting lines does
-        cap = len(data) + 1 if len(data) < 1 << 22 else data.count(b"\n") + n + 1
-        subs = np.empty(cap, dtype=_SUB)
+        # One line in `modulus` ends a sub-block.  Lines of 8 bytes and more are expected, and counting them costs a pass over
+        # the text; a turn of shorter ones, or of more ends, leaves the conversation as it is and says how many it has.
+        cap = len(data) // (8 * min(self._modulus, 64)) + 2 * n + 64
         cnt, kept = ctypes.c_int32(0), ctypes.c_int64(0)
-        _check_index(self._lib.cp_dedup_turn(self._h, idv, data, offsets, n, ref, subs.ctypes.data, cap,
-                                             ctypes.byref(cnt), ctypes.byref(kept)), "cp_dedup_turn")
+        while True:
+            subs = np.empty(cap, dtype=_SUB)
+            status = self._lib.cp_dedup_turn(self._h, idv, data, offsets, n, ref, subs.ctypes.data, cap, ctypes.byref(cnt),
+                                             ctypes.byref(kept))
+            if status == CP_OK or cnt.value <= cap:
+                break
+            cap = cnt.value
+        _check_index(status, "cp_dedup_turn")
         out = [("block", int(ids[i])) if ref[i] else ("subs", []) for i in range(n)]
         for block, owner, begin, end in subs[:cnt.value].tolist():
             out[block][1].append((begin, end, owner))

@@ -121,6 +121,31 @@ def test_lines_hashed_side_by_side(count, M):
     lib.close()
 
 
+def test_room_for_sub_blocks_follows_the_text():
+    """A turn asks for memory by the sub-blocks that its text may have, not a record per byte; text of short lines, every
+    one of which ends a sub-block, has more than expected and is taken all the same, once."""
+    import tracemalloc
+
+    rng = np.random.default_rng(3)
+    line = lambda n: bytes(rng.integers(97, 123, size=n, dtype=np.uint8))  # noqa: E731
+    text = b"\n".join(line(44) for _ in range(40000))
+    talk = cp.Conversation(8)
+    tracemalloc.start()
+    parts, kept = talk.turn([1], [text])
+    peak = tracemalloc.get_traced_memory()[1]
+    tracemalloc.stop()
+    talk.close()
+    assert kept == len(text) and 3000 < len(parts[0][1]) < 7000
+    assert peak < 3 * len(text)
+    for M in (1, 64):
+        short = b"".join(line(2) + b"\n" for _ in range(3000)) if M == 1 else b"".join(b"%d\n" % (i % 9) for i in range(20000))
+        ref, lib = OD.Conversation(M), cp.Conversation(M)
+        for ids in ([1, 2], [3, 1]):
+            want = ref.turn(ids, [short, b""])
+            assert lib.turn(ids, [short, b""]) == (want, OD.kept_bytes(want))
+        lib.close()
+
+
 @pytest.mark.parametrize("ids,blocks,want", [
     ([1, 2], [b"x\ny\n"], ([("subs", []), ("subs", [(0, 2, -1), (2, 4, -1)])], 4)),
     ([1, 2, 3], [b"x\n"], ([("subs", []), ("subs", []), ("subs", [(0, 2, -1)])], 2)),
