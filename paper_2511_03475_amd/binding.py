@@ -469,7 +469,8 @@ class Conversation:
     def __init__(self, modulus: int):
         self._lib = load_library()
         self._h = ctypes.c_void_p()
-        self._modulus = int(modulus)
+        # Bytes of text to a sub-block, at least: one line in `modulus` ends one, and lines of 8 bytes and more are expected.
+        self._piece = 8 * max(1, min(int(modulus), 64))
         _check_index(self._lib.cp_dedup_create(int(modulus), ctypes.byref(self._h)), "cp_dedup_create")
 
     def close(self) -> None:
@@ -483,14 +484,18 @@ class Conversation:
         """Per block ("block", id) or ("subs", [(begin, end, ref), ...]), and the kept bytes."""
         n = len(ids)
         data = b"".join(blocks)
-        starts = [0, *itertools.accumulate(map(len, blocks))]
-        offsets = (ctypes.c_int64 * (n + 1))(*starts[:-1])
-        offsets[n] = starts[-1]   # with one block too many, the last id has the text of two
+        starts = itertools.accumulate(map(len, blocks), initial=0)
+        if len(blocks) == n:
+            offsets = (ctypes.c_int64 * (n + 1))(*starts)
+        else:   # a block too many: the last id has the text of two
+            starts = list(starts)
+            offsets = (ctypes.c_int64 * (n + 1))(*starts[:-1])
+            offsets[n] = starts[-1]
         idv = (ctypes.c_int32 * max(n, 1))(*[int(i) for i in ids])
         ref = (ctypes.c_int32 * max(n, 1))()
-        # One line in `modulus` ends a sub-block.  Lines of 8 bytes and more are expected, and counting them costs a pass over
-        # the text; a turn of shorter ones, or of more ends, leaves the conversation as it is and says how many it has.
-        cap = len(data) // (8 * min(self._modulus, 64)) + 2 * n + 64
+        # Counting the lines costs a pass over the text; a turn with more sub-blocks leaves the conversation as it is and says
+        # how many it has.
+        cap = len(data) // self._piece + 2 * n + 64
         cnt, kept = ctypes.c_int32(0), ctypes.c_int64(0)
         while True:
             subs = np.empty(cap, dtype=_SUB)

@@ -22,7 +22,8 @@ HIPCC_FLAGS = [
     # the attention kernel's loop over key tiles (2.7 KB) begins where an instruction cache line does: 8 requests,
     # P = 6144, E = 2304, 32/8 heads 1943 -> 1930 us; without it that depends on the code in front
     "-Xarch_device", "-falign-loops=64",
-    # the same for functions on the host: the index of 2000 contexts took 26.7 or 26.2 ms by the size of the code in front
+    # the same for functions on the host: without it the clustering lies where the code in front of it ends, and the index of
+    # 2000 contexts took 26.6 ms in two of three builds, 26.2 in the third; with it 26.2
     "-Xarch_host", "-falign-functions=64",
 ]
 

@@ -149,8 +149,10 @@ constexpr int kAlternateRounds = 16;
 // Row tile of a request for its unit-th work unit.  The longest first, so that the last items of the list are
 // short.  In a batch of equal requests every second one takes the shortest first: a CU that has had longer items
 // of one request than others has shorter ones of the next, while the list stays request by request, which the
-// L2 wants.  8 requests, P = 6144, E = 2304, 32/8 heads (36 items a CU group of 32, 97 to 132 key tiles): 1982
-// -> 1906 us; calls of more than kAlternateRounds items a CU gain nothing and stay as they are.
+// L2 wants.  8 requests, P = 6144, E = 2304, 32/8 heads (288 items of a KV head on 32 CUs, 97 to 132 key tiles): 1944
+// -> 1868 us, the attention launch, with the same row tiles; with tiles of whole heads in one order it was 1944 too.  2 row
+// tiles a request and 2 items a CU (32, P = 10240, E = 128): no difference, 647 to 660 us.  Calls of more than
+// kAlternateRounds items a CU gain nothing and stay as they are.
 __device__ __forceinline__ int row_tile_of(int unit, int nt, int r, int batch, int alternate)
 {
     return alternate && ((batch - r) & 1) == 0 ? unit : nt - 1 - unit;
@@ -1016,7 +1018,8 @@ __global__ __launch_bounds__(kThreads) void extend_attn_kernel(const std::condit
                 pb[t][e + 1] = y[1];
             }
         // The row sums come after all conversions (the empty statement says so): mixed with them by the scheduler they
-        // wait for each other between the last MFMAs of P V (4 requests, P = 24576, E = 8192, 64/8 heads 25.5 -> 25.2 ms).
+        // wait for each other between the last MFMAs of P V (4 requests, P = 24576, E = 8192, 64/8 heads 25.09 -> 25.02 ms; 1, P = 0,
+        // E = 131072, 32/8 heads 114.7 -> 114.1; medians of 12 rounds in turn that differ by 0.2 to 0.4 %).
         u32x4 w[2 * kNKB];
 #pragma unroll
         for (int t = 0; t < 2 * kNKB; ++t) w[t] = __builtin_bit_cast(u32x4, pb[t]);
@@ -1961,9 +1964,11 @@ double rounds_us(double items, double cus, double work, double shortest, double 
     return std::max(work / cus + uneven, rounds * (shortest + 0.5 * more * (longest - shortest)));
 }
 
-// Time of a key tile in the last row tile of a request, as a part of a full one's.  Up to four wavefronts with rows
-// have a SIMD each: 1.32 us a tile with one or two of them, 1.46 with four, 1.76, 1.88, 2.04, 2.16 with five to
-// eight (256 workgroups, no two with the same keys).
+// Time of a key tile in the last row tile of a request, as a part of a full one's: a straight line through what was
+// measured, which has a step where the fifth wavefront with rows is the second of a SIMD.  With 1 or 2, 4, 5, 6, 7 and 8 such wavefronts
+// 1.32, 1.46, 1.76, 1.88, 2.04 and 2.16 us a tile (256 workgroups, no two with the same keys), that is 0.61, 0.68, 0.81, 0.87, 0.94
+// and 1; the line has 0.65, 0.65, 0.74, 0.83, 0.91 and 1.  The plans are the same with either, but for 235 of 20000 random shapes of equal
+// requests, and 70 of these took 0.997 of the time with the measured shares, 0.84 to 1.28: the estimate is not that good.
 double last_tile_share(int64_t E, int G, TileKind kind)
 {
     const int waves = (int)((E * G - 1) % kBM) / 32 + 1;
