@@ -30,7 +30,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 # valid only for the kernel source they were taken with: reported as null as soon as that source
 # changes.  They are not measured by this script.
 TRAFFIC = {
-    "source_sha256_16": "65043040fba2cfb6",
+    "source_sha256_16": "b02d4a77b53b6767",
     "from": "profiles/extend_attn_kernel_long_context_32k.md, profiles/decode_attn_kernel_decode_b32_p10k.md",
     "long_context_32k": (2130381 * 2.0 + 524301) * 1024.0,      # extend_attn_kernel
     "decode_b32_p10k": (656295 * 2.0 + 256) * 1024.0,          # decode_attn_kernel

@@ -6,7 +6,7 @@
 //                         (paper, Section 1 / Section 2.1: prefill over a prefix cache); in batches of
 //                         unequal lengths also the decode-shaped requests, next to the others
 //   decode_attn_kernel    the same for calls with few rows per KV head or few keys (wavefronts share the keys)
-//   merge_splits_kernel, merge_few_splits_kernel, merge_mixed_kernel   combine partial results over key ranges
+//   merge_splits_kernel, merge_few_splits_kernel, merge_tail_kernel, merge_mixed_kernel   combine partial results over key ranges
 //   check_tables_kernel   optional check of block_table against the pool size
 //
 // Attention kernel layout.  One workgroup = 8 wavefronts = 256 (token, q head) rows of one KV
@@ -25,6 +25,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <cmath>
 #include <mutex>
 #include <type_traits>
 #include <vector>
@@ -1978,8 +1979,8 @@ double last_tile_share(int64_t E, int G, TileKind kind)
 
 // The same for equal requests, which also have a third way: the items that would run in a last round of few are
 // split, the others are not (pl.tail_units).  Then the call ends with all CUs busy, and only the rows of the last
-// items are merged.  3 requests, P = 30000, E = 1100, 64/8 heads (105 items for 32 CUs) 3254 -> 2856 us; 6, P = 9046,
-// E = 171 (36) 444 -> 314; 1, P = 10694, E = 2051, 32/8 heads (33) 496 -> 368.
+// items are merged.  3 requests, P = 30000, E = 1100, 64/8 heads (105 items for 32 CUs) 3090 -> 2787 us; 6, P = 9046,
+// E = 171 (36) 329 -> 290; 1, P = 10694, E = 2051, 32/8 heads (33) 405 -> 346; 33, P = 1500, E = 70, 8/8 heads (33) 67 -> 56.
 // With 1, 2 or 4 KV heads and contiguous ranges for the XCDs (see work_item) there is no common last round.
 constexpr double kTailGain = 0.97; // of the time without
 bool contiguous_ranges(const cp_shape *s, const Plan &pl, int64_t items, int xcds);
@@ -2213,8 +2214,8 @@ Plan make_plan(Requests &q, size_t room = SIZE_MAX, uint8_t *order = nullptr)
 
 // Whether XCDs that share a KV head take a contiguous range of its items each (see work_item): for equal requests, if
 // no range takes more than 6 % longer than the mean.  Then the XCDs stream different keys; dealt out, all the same
-// ones.  9 requests, P = 5548, E = 817, 8/2 heads 260 us, dealt out 301; 20, P = 0, E = 1511 122 and 137; but with a
-// range 15 % over the mean (3 requests, P = 0, E = 5067, 16/4 heads) 342, dealt out 303.
+// ones.  20 requests, P = 0, E = 1511, 8/2 heads 121 us, dealt out 130; 9, P = 5548, E = 817 170 and 168; but with a
+// range 15 % over the mean (3 requests, P = 0, E = 5067, 16/4 heads) 347, dealt out 296.
 constexpr double kContiguousExcess = 1.06;
 bool contiguous_ranges(const cp_shape *s, const Plan &pl, int64_t items, int xcds)
 {
