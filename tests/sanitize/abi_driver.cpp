@@ -72,6 +72,20 @@ int main()
         CHECK(cp_num_splits(&s) == 0 && cp_plan_kind(&s) == CP_PLAN_INVALID);
         CHECK(cp_write_kv(ptr, ptr, ptr, iptr, iptr, iptr, nullptr, &s) == CP_ERR_SHAPE);
     }
+    for (int n : {2, 40, 512, 513}) { // unequal lengths, with and without requests that decode or bring nothing
+        std::vector<int32_t> P(n), E(n);
+        for (int kind = 0; kind < 3; ++kind)
+            for (int Hkv : {1, 3, 8}) {
+                for (int r = 0; r < n; ++r) {
+                    P[r] = (r * 7919) % 9001;
+                    E[r] = kind > 0 && r % 5 ? (kind == 1 ? 1 : r % 3) : 20 + (r * 613) % 2000;
+                }
+                cp_shape s = shape_of(P, E, 4 * Hkv, Hkv, 0);
+                const int32_t plan = cp_plan_kind(&s), rows = cp_plan_tile_rows(&s);
+                CHECK(plan != CP_PLAN_INVALID && (rows == 128 || rows == 256));
+                CHECK((cp_num_splits(&s) > 1) == (cp_workspace_bytes(&s) > 0));
+            }
+    }
     {
         const std::vector<int32_t> P{0, 16}, E{0, 0}; // nothing to do: returns before any pointer is looked at
         cp_shape s = shape_of(P, E, 4, 2, 0);
